@@ -148,32 +148,52 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
     hipLaunchKernelGGL(k_set_seg, g1, g1, 0, st, dadj, Sa);
     hipLaunchKernelGGL(k_adj_init, g, b, 0, st, P.dtiles, dadj, A);
     // the stop test is relative to the starting projected residual of the
-    // source a (whose scale is the caller's): first read that residual
-    CgCtl ctl{1e-300, ctx->opts.cg_maxit};
-    hipLaunchKernelGGL(k_fin_w0, g1, b, 0, st, sid, dadj);
-    hipLaunchKernelGGL(k_shift_stats, g, b, 0, st, P.dtiles, dadj);
-    hipLaunchKernelGGL(k_fin_assemble, g1, b, 0, st, sid, dadj, ctl);
-    HIPCHK(hipGetLastError());
-    double res0 = 0.0;
-    HIPCHK(hipMemcpyAsync(&res0, &asst->res0, sizeof(double), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
-    ctl.tol = std::max(ctx->opts.cg_tol * res0, 1e-300);
-    // the single-reduction solve of the forward one (its first finalize
-    // counts no iteration)
-    hipLaunchKernelGGL((k_cg1_update<true>), g, b, 0, st, P.dtiles, dadj);
-    int done_it = 0;
-    for (;;) {
-        for (int c = 0; c < ctx->opts.cg_check; c++) {
-            hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), g, b, 0, st, P.dtiles, dadj);
-            hipLaunchKernelGGL(k_cg1_sum, dim3(FIN_SPLIT), b, 0, st, sid, dadj);
-            hipLaunchKernelGGL(k_cg1_fin, g1, b, 0, st, sid, dadj, ctl);
-            hipLaunchKernelGGL((k_cg1_update<false>), g, b, 0, st, P.dtiles, dadj);
-        }
-        done_it += ctx->opts.cg_check;
+    // source a (whose scale is the caller's)
+    int *flag = ctx->host_flag;
+    bool solved = false;
+    if (const int lpr = solve_lpr(ctx, P.L.seg.n)) {
+        launch_solve_prep<R>(lpr, P.dtiles, P.L.ntile, dadj, st);
+        launch_solve<R>(lpr, ctx->ncu, P.dtiles, P.L.ntile, dadj, SolveCtl{ctx->opts.cg_tol, ctx->opts.cg_maxit, 1}, st);
         HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(ctx->host_flag, &asst->done, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(flag, &asst->done, 3 * sizeof(int), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
-        if (ctx->host_flag[0] || done_it >= ctx->opts.cg_maxit + 2) break;
+        solved = flag[0] && !flag[2];
+        if (!solved) {
+                // given up: the solver's copy of the rows, which the forward
+                // evaluation did not make, then the multi-launch solve afresh
+                hipLaunchKernelGGL((k_hslice<R>), g, b, 0, st, P.dtiles, P.dseg);
+                hipLaunchKernelGGL(k_zero, g1, dim3(64), 0, st, (double *)asst, (int)(sizeof(SegState) / sizeof(double)));
+                hipLaunchKernelGGL(k_adj_init, g, b, 0, st, P.dtiles, dadj, A);
+            }
+        }
+        if (!solved) {
+        // first read the starting residual
+        CgCtl ctl{1e-300, ctx->opts.cg_maxit};
+        hipLaunchKernelGGL(k_fin_w0, g1, b, 0, st, sid, dadj);
+        hipLaunchKernelGGL(k_shift_stats, g, b, 0, st, P.dtiles, dadj);
+        hipLaunchKernelGGL(k_fin_assemble, g1, b, 0, st, sid, dadj, ctl);
+        HIPCHK(hipGetLastError());
+        double res0 = 0.0;
+        HIPCHK(hipMemcpyAsync(&res0, &asst->res0, sizeof(double), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        ctl.tol = std::max(ctx->opts.cg_tol * res0, 1e-300);
+        // the single-reduction solve of the forward one (its first finalize
+        // counts no iteration)
+        hipLaunchKernelGGL((k_cg1_update<true>), g, b, 0, st, P.dtiles, dadj);
+        int done_it = 0;
+        for (;;) {
+            for (int c = 0; c < ctx->opts.cg_check; c++) {
+                hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), g, b, 0, st, P.dtiles, dadj);
+                hipLaunchKernelGGL(k_cg1_sum, dim3(FIN_SPLIT), b, 0, st, sid, dadj);
+                hipLaunchKernelGGL(k_cg1_fin, g1, b, 0, st, sid, dadj, ctl);
+                hipLaunchKernelGGL((k_cg1_update<false>), g, b, 0, st, P.dtiles, dadj);
+            }
+            done_it += ctx->opts.cg_check;
+            HIPCHK(hipGetLastError());
+            HIPCHK(hipMemcpyAsync(ctx->host_flag, &asst->done, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
+            HIPCHK(hipStreamSynchronize(st));
+            if (ctx->host_flag[0] || done_it >= ctx->opts.cg_maxit + 2) break;
+        }
     }
     if (cg_iters) *cg_iters = ctx->host_flag[1];
     hipLaunchKernelGGL(k_adj_keep_lam_shift, g1, dim3(64), 0, st, sid, dadj, A);

@@ -19,6 +19,7 @@
 #include "k_lists.h"
 #include "k_tersoff.h"
 #include "k_qeq.h"
+#include "k_solve.h"
 #include "k_md.h"
 #include "k_fq.h"
 
@@ -87,6 +88,7 @@ struct ctbop_ctx {
     // tiles per launch of the side stream's kernels: two blocks per CU, so
     // that they leave room for the solve's product beside them
     int side_chunk = 512;
+    int ncu = 0;                 // compute units of the device, at most SV_MAX_BLOCKS (0: not asked yet)
     // optional per-kernel timing with HIP events on the caller's stream
     int profile = 0;
     unsigned profile_mask = 0xffffu;   // kernel classes timed while profiling is on
@@ -515,6 +517,58 @@ int prepare(ctbop_ctx *ctx, int n, const double *box, const int *pbc, void *sys,
     return CTBOP_OK;
 }
 
+// starting charges of an evaluation (k_gather's warm)
+int start_mode(const Prep &P, int flags)
+{
+    if (!(flags & CTBOP_FLAG_WARM_START) || P.fresh) return 0;
+    return (flags & CTBOP_FLAG_EXTRAPOLATE) ? 2 : 1;
+}
+
+// Lanes per row of the one-launch charge solve for a system of n atoms, 0
+// where the multi-launch solve runs.  The rule is on n alone (and the
+// device), so a system is solved alike alone and in the server: the blocks of
+// one system have to be on the device together, one per CU.  Up to 64 rows a
+// CU take 8 lanes per row, up to SV_MAX_ATOMS (16-bit halo positions, a
+// bitmap of all rows in LDS) 4 lanes; the charge coupling's nonlinear solve
+// has its own kernels.
+int solve_lpr(ctbop_ctx *ctx, int n)
+{
+    if (ctx->opts.fq_kappa > 0.0 || n > SV_MAX_ATOMS) return 0;
+    if (ctx->ncu == 0) {
+        int dev = 0, ncu = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            return 0;
+        ctx->ncu = std::min(ncu, SV_MAX_BLOCKS);
+    }
+    if (n <= sv_rows(8) * ctx->ncu) return 8;
+    return n <= sv_rows(4) * ctx->ncu ? 4 : 0;
+}
+
+// The one-launch solve over nt tiles of systems of one solve_lpr class, and
+// the kernel that prepares it.
+template <typename R>
+void launch_solve_prep(int lpr, const Tile *tiles, int nt, Seg *segs, hipStream_t st)
+{
+    const dim3 b(SV_T);
+    if (lpr == 8) hipLaunchKernelGGL((k_solve_prep<8, R>), dim3(nt * (TILE / sv_rows(8))), b, 0, st, tiles, segs);
+    else hipLaunchKernelGGL((k_solve_prep<4, R>), dim3(nt * (TILE / sv_rows(4))), b, 0, st, tiles, segs);
+}
+template <typename R>
+void launch_solve(int lpr, int ncu, const Tile *tiles, int nt, Seg *segs, SolveCtl ctl, hipStream_t st)
+{
+    const int rb = sv_rows(lpr), nb = nt * (TILE / rb);
+    const dim3 g(nb), b(SV_T);
+    // more blocks than CUs (a batch of systems): the build with two blocks
+    // per CU, the same arithmetic in fewer registers
+    const bool two = sizeof(R) == 4 && nb > ncu;
+    constexpr int OCC2 = sizeof(R) == 4 ? 4 : 2;
+    if (lpr == 8 && two) hipLaunchKernelGGL((k_solve<8, R, OCC2>), g, b, 0, st, tiles, segs, ctl);
+    else if (lpr == 8) hipLaunchKernelGGL((k_solve<8, R, 2>), g, b, 0, st, tiles, segs, ctl);
+    else if (two) hipLaunchKernelGGL((k_solve<4, R, OCC2>), g, b, 0, st, tiles, segs, ctl);
+    else hipLaunchKernelGGL((k_solve<4, R, 2>), g, b, 0, st, tiles, segs, ctl);
+}
+
 // Sorted frame and neighbour lists for the current positions (the lists are
 // rebuilt when an atom has moved more than half the skin, or on request).
 template <typename R>
@@ -524,8 +578,7 @@ void launch_lists(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags)
     const dim3 g(nt), b(TILE), g1(1);
     hipStream_t st = P.st;
     const int force = (flags & CTBOP_FLAG_FORCE_REBUILD) || P.fresh;
-    int warm = 0;
-    if ((flags & CTBOP_FLAG_WARM_START) && !P.fresh) warm = (flags & CTBOP_FLAG_EXTRAPOLATE) ? 2 : 1;
+    const int warm = start_mode(P, flags);
     const int *sid = P.dsegid;
     hipLaunchKernelGGL(k_call_init, g1, dim3(64), 0, st, sid, P.dseg, 1, force);
     hipLaunchKernelGGL(k_check_disp, g, b, 0, st, P.dtiles, P.dseg);
@@ -599,86 +652,116 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         if (P.own) HIPCHK(hipEventRecord(ctx->ev_join, ctx->side));
         return CTBOP_OK;
     };
-    if (fq) {
+    const int lpr = solve_lpr(ctx, P.L.seg.n);
+    if (fq || lpr) {
         const int rc = side_launch();
         if (rc) return rc;
     }
     CgCtl ctl{ctx->opts.cg_tol, ctx->opts.cg_maxit};
-    {
-        Timed t(ctx, 2, st);
-        hipLaunchKernelGGL((k_assemble<R, LPR>), g, b, 0, st, P.dtiles, P.dseg, ctx->pd);
-    }
-    if (fq) {
-        // the starting residual needs the coupling weights of this step
-        if (P.own) HIPCHK(hipStreamWaitEvent(st, ctx->ev_join, 0));
-        hipLaunchKernelGGL(k_fq_r0, g, b, 0, st, P.dtiles, P.dseg);
-    }
-    {
-        Timed t(ctx, 8, st);
-        hipLaunchKernelGGL((k_hslice<R>), g, b, 0, st, P.dtiles, P.dseg);
-    }
-    if (!fq) {
-        const int rc = side_launch();
-        if (rc) return rc;
-    }
-    hipLaunchKernelGGL(k_fin_w0, g1, b, 0, st, sid, P.dseg);
-    if (fq) {
-        hipLaunchKernelGGL(k_shift_stats, g, b, 0, st, P.dtiles, P.dseg);
-        hipLaunchKernelGGL(k_fin_assemble, g1, b, 0, st, sid, P.dseg, ctl);
-    } else {
-        // the single-reduction solve's start: the residual's shift, y = M r
-        Timed t(ctx, 6, st);
-        hipLaunchKernelGGL((k_cg1_update<true>), g, b, 0, st, P.dtiles, P.dseg);
-    }
-    HIPCHK(hipGetLastError());
-    // charge solve: launch iterations in batches, then read the convergence flag
-    int done_it = 0;
-    int chunk = ctx->opts.cg_check;
-    // (the single-reduction solve's first finalize counts no iteration: n
-    // iterations take n + 1 rounds)
-    if (P.own) chunk = std::max(chunk, std::min(ctx->last_iters[P.base], ctx->opts.cg_maxit) + (fq ? 0 : 1));
     int *flag = P.flag_host;
-    for (;;) {
-        for (int c = 0; c < chunk; c++) {
-            if (!fq) {
-                {
-                    Timed t(ctx, 0, st);
-                    hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), g, b, 0, st, P.dtiles, P.dseg);
-                }
-                hipLaunchKernelGGL(k_cg1_sum, dim3(FIN_SPLIT), b, 0, st, sid, P.dseg);
-                hipLaunchKernelGGL(k_cg1_fin, g1, b, 0, st, sid, P.dseg, ctl);
-                Timed t(ctx, 5, st);
-                hipLaunchKernelGGL((k_cg1_update<false>), g, b, 0, st, P.dtiles, P.dseg);
-                continue;
-            }
-            {
-                Timed t(ctx, 6, st);
-                hipLaunchKernelGGL(k_cg_dir, g, b, 0, st, P.dtiles, P.dseg);
-            }
-            {
-                Timed t(ctx, 0, st);
-                hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_FQ>), g, b, 0, st, P.dtiles, P.dseg);
-            }
-            // two Newton steps on the step length
-            for (int pass = 0; pass < 2; pass++) {
-                hipLaunchKernelGGL(k_fq_ls, g, b, 0, st, P.dtiles, P.dseg, pass);
-                hipLaunchKernelGGL(k_fq_fin_ls, g1, b, 0, st, sid, P.dseg, pass);
-            }
-            hipLaunchKernelGGL(k_fq_step, g, b, 0, st, P.dtiles, P.dseg);
-            {
-                Timed t(ctx, 5, st);
-                hipLaunchKernelGGL(k_fq_resid, g, b, 0, st, P.dtiles, P.dseg);
-            }
-            hipLaunchKernelGGL(k_fq_fin_update, g1, b, 0, st, sid, P.dseg, ctl);
+    bool solved = false;
+    if (lpr) {
+        {
+            Timed t(ctx, 2, st);
+            hipLaunchKernelGGL((k_assemble<R, LPR>), g, b, 0, st, P.dtiles, P.dseg, ctx->pd);
         }
-        done_it += chunk;
+        {
+            Timed t(ctx, 8, st);
+            launch_solve_prep<R>(lpr, P.dtiles, nt, P.dseg, st);
+        }
+        {
+            Timed t(ctx, 0, st);
+            launch_solve<R>(lpr, ctx->ncu, P.dtiles, nt, P.dseg, SolveCtl{ctl.tol, ctl.maxit, 0}, st);
+        }
         HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(flag, &P.L.seg.sst->done, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(flag, &P.L.seg.sst->done, 3 * sizeof(int), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         if (ctx->profile) ev_harvest(ctx);
-        // (the single-reduction solve's first finalize counts no iteration)
-        if (flag[0] || done_it >= ctx->opts.cg_maxit + 2) break;
-        chunk = ctx->opts.cg_check;
+        solved = flag[0] && !flag[2];
+        if (!solved) {
+            // given up: the starting charges again, then the multi-launch solve
+            hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, P.dtiles, P.dseg, start_mode(P, flags));
+            hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
+            hipLaunchKernelGGL(k_qfix, g, b, 0, st, P.dtiles, P.dseg);
+            hipLaunchKernelGGL(k_solve_retry, g1, g1, 0, st, sid, P.dseg);
+        }
+    }
+    if (!solved) {
+        {
+            Timed t(ctx, 2, st);
+            hipLaunchKernelGGL((k_assemble<R, LPR>), g, b, 0, st, P.dtiles, P.dseg, ctx->pd);
+        }
+        if (fq) {
+            // the starting residual needs the coupling weights of this step
+            if (P.own) HIPCHK(hipStreamWaitEvent(st, ctx->ev_join, 0));
+            hipLaunchKernelGGL(k_fq_r0, g, b, 0, st, P.dtiles, P.dseg);
+        }
+        {
+            Timed t(ctx, 8, st);
+            hipLaunchKernelGGL((k_hslice<R>), g, b, 0, st, P.dtiles, P.dseg);
+        }
+        if (!fq && !lpr) {
+            const int rc = side_launch();
+            if (rc) return rc;
+        }
+        hipLaunchKernelGGL(k_fin_w0, g1, b, 0, st, sid, P.dseg);
+        if (fq) {
+            hipLaunchKernelGGL(k_shift_stats, g, b, 0, st, P.dtiles, P.dseg);
+            hipLaunchKernelGGL(k_fin_assemble, g1, b, 0, st, sid, P.dseg, ctl);
+        } else {
+            // the single-reduction solve's start: the residual's shift, y = M r
+            Timed t(ctx, 6, st);
+            hipLaunchKernelGGL((k_cg1_update<true>), g, b, 0, st, P.dtiles, P.dseg);
+        }
+        HIPCHK(hipGetLastError());
+        // charge solve: launch iterations in batches, then read the convergence flag
+        int done_it = 0;
+        int chunk = ctx->opts.cg_check;
+        // (the single-reduction solve's first finalize counts no iteration: n
+        // iterations take n + 1 rounds)
+        if (P.own) chunk = std::max(chunk, std::min(ctx->last_iters[P.base], ctx->opts.cg_maxit) + (fq ? 0 : 1));
+        for (;;) {
+            for (int c = 0; c < chunk; c++) {
+                if (!fq) {
+                    {
+                        Timed t(ctx, 0, st);
+                        hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), g, b, 0, st, P.dtiles, P.dseg);
+                    }
+                    hipLaunchKernelGGL(k_cg1_sum, dim3(FIN_SPLIT), b, 0, st, sid, P.dseg);
+                    hipLaunchKernelGGL(k_cg1_fin, g1, b, 0, st, sid, P.dseg, ctl);
+                    Timed t(ctx, 5, st);
+                    hipLaunchKernelGGL((k_cg1_update<false>), g, b, 0, st, P.dtiles, P.dseg);
+                    continue;
+                }
+                {
+                    Timed t(ctx, 6, st);
+                    hipLaunchKernelGGL(k_cg_dir, g, b, 0, st, P.dtiles, P.dseg);
+                }
+                {
+                    Timed t(ctx, 0, st);
+                    hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_FQ>), g, b, 0, st, P.dtiles, P.dseg);
+                }
+                // two Newton steps on the step length
+                for (int pass = 0; pass < 2; pass++) {
+                    hipLaunchKernelGGL(k_fq_ls, g, b, 0, st, P.dtiles, P.dseg, pass);
+                    hipLaunchKernelGGL(k_fq_fin_ls, g1, b, 0, st, sid, P.dseg, pass);
+                }
+                hipLaunchKernelGGL(k_fq_step, g, b, 0, st, P.dtiles, P.dseg);
+                {
+                    Timed t(ctx, 5, st);
+                    hipLaunchKernelGGL(k_fq_resid, g, b, 0, st, P.dtiles, P.dseg);
+                }
+                hipLaunchKernelGGL(k_fq_fin_update, g1, b, 0, st, sid, P.dseg, ctl);
+            }
+            done_it += chunk;
+            HIPCHK(hipGetLastError());
+            HIPCHK(hipMemcpyAsync(flag, &P.L.seg.sst->done, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
+            HIPCHK(hipStreamSynchronize(st));
+            if (ctx->profile) ev_harvest(ctx);
+            // (the single-reduction solve's first finalize counts no iteration)
+            if (flag[0] || done_it >= ctx->opts.cg_maxit + 2) break;
+            chunk = ctx->opts.cg_check;
+        }
     }
     if (P.own) ctx->last_iters[P.base] = flag[1];
     if (iters_out) *iters_out = flag[1];

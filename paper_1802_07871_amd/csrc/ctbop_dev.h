@@ -68,6 +68,7 @@ struct SegState {
     int ticket;        // last-block detection counter (returns to 0)
     int done;          // charge solve finished
     int iters;
+    int pabort;        // one-launch solve: given up (the host takes the multi-launch path)
     int status;        // ST_* bits, sticky until the next rebuild/call reset
     int maxl, maxs;    // largest list rows at the last build
     int built;         // lists exist
@@ -97,6 +98,7 @@ struct SegState {
     // phi'(0) along the current direction (line search)
     double pr, ps, A0;
     double m1s;        // single-reduction solve: m1^T s of the current direction
+    double den;        // and its p^T H p
 };
 
 // ---------------------------------------------------------------------------

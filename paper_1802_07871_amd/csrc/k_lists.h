@@ -30,6 +30,7 @@ __global__ void k_call_init(const int *seg_ids, Seg *segs, int nseg, int force_r
     st->iters = 0;
     st->status = 0;
     st->forces_done = 0;
+    st->pabort = 0;
 }
 
 // A neighbour list rebuild is needed once any atom moved more than skin/2

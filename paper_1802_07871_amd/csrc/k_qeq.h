@@ -802,19 +802,69 @@ __global__ void __launch_bounds__(TILE) k_cg1_update(const Tile *tiles, Seg *seg
     tile_partials_at<8>(S, T.row0 / TILE, v, lds, P_UPD);
 }
 
-// The residual after the last update and the stop test; then gamma = r^T y,
-// delta = y^T H y, beta = gamma / gamma_old, alpha = gamma / (delta -
-// beta gamma / alpha_old) (= gamma / p^T H p), the next shift c and the
-// projected norm of the next residual, which marks the coming update as the
-// last when it meets the tolerance.
 // First stage of the finalize: FIN_SPLIT blocks per segment, each summing
-// the 15 partials over its range of tiles.
+// the 14 partials over its range of tiles.
 __global__ void __launch_bounds__(TILE) k_cg1_sum(const int *seg_ids, Seg *segs)
 {
     const Seg &S = segs[seg_ids[blockIdx.x / FIN_SPLIT]];
     if (S.sst->done) return;
     __shared__ double lds[4 * P_CG1];
     seg_group_sum<P_CG1>(S, blockIdx.x % FIN_SPLIT, lds);
+}
+
+// The scalar step of an iteration from its 14 sums: the residual after the
+// last update and the stop test; then gamma = r^T y, delta = y^T H y, beta =
+// gamma / gamma_old, alpha = gamma / (delta - beta gamma / alpha_old) (= gamma
+// / p^T H p), the next shift c and the projected norm of the next residual,
+// which marks the coming update as the last when it meets the tolerance.
+// Returns the status bits of a failed solve.  inv_n = 1/n and inv_sd = 1 /
+// 1^T M 1: one thread takes the step between two kernels (or two halves of an
+// iteration), so its divisions are the two that depend on the sums, and the
+// root of the residual is taken at the start and the end only.
+__device__ __forceinline__ int cg1_step(SegState &st, double inv_n, double inv_sd, double Q,
+                                        const double (&t)[P_CG1], double tol, int maxit)
+{
+    const double rr = t[P_UPD + 3] - t[P_UPD + 2] * t[P_UPD + 2] * inv_n;
+    const double res2 = fmax(rr * inv_n, 0.0);
+    const bool first = st.cg_first != 0;
+    if (!first) {
+        st.iters += 1;
+        st.iters_total += 1;
+    }
+    const bool met = st.cg_last || res2 <= tol * tol, out = st.iters >= maxit;
+    const double gam = t[P_UPD + 1], del = t[P_PRD + 0];
+    const double beta = first ? 0.0 : gam / st.rho;
+    const double den = first ? del : del - beta * beta * st.den;   // (beta gamma / alpha_old)
+    const bool bad = !(den > 0.0) || !(gam > 0.0);
+    if (first) st.res0 = sqrt(res2);
+    if (met || out || bad) {
+        st.res = sqrt(res2);
+        st.qshift = (Q - t[P_UPD + 4]) * inv_n;
+        st.done = 1;
+        return met ? 0 : out ? ST_NOCONV : ST_NOT_PD;
+    }
+    const double alpha = gam / den;
+    // sums of the new s = H y + beta s_old (m1^T s by its own recurrence:
+    // an error in it only leaves m1^T r of the next residual slightly off
+    // zero, and the next shift, from the measured m1^T r, removes that)
+    const double m1s = first ? t[P_PRD + 1] : t[P_PRD + 1] + beta * st.m1s;
+    const double rs = t[P_PRD + 2] + beta * t[P_UPD + 5];
+    const double ss = t[P_PRD + 3] + 2.0 * beta * t[P_PRD + 4] + beta * beta * t[P_UPD + 6];
+    const double sum_s = t[P_PRD + 5] + beta * t[P_UPD + 7];
+    const double c = (t[P_UPD + 0] - alpha * m1s) * inv_sd;
+    const double rs_p = rs - t[P_UPD + 2] * sum_s * inv_n;
+    const double ss_p = ss - sum_s * sum_s * inv_n;
+    const double next2 = (rr - 2.0 * alpha * rs_p + alpha * alpha * ss_p) * inv_n;
+    st.cg_first = 0;
+    st.m1s = m1s;
+    st.rho = gam;
+    st.den = den;
+    st.alpha = alpha;
+    st.beta = beta;
+    st.w = c;
+    st.mshift -= c;
+    if (next2 < tol * tol) st.cg_last = 1;
+    return 0;
 }
 
 __global__ void __launch_bounds__(TILE) k_cg1_fin(const int *seg_ids, Seg *segs, CgCtl ctl)
@@ -825,55 +875,8 @@ __global__ void __launch_bounds__(TILE) k_cg1_fin(const int *seg_ids, Seg *segs,
     double t[P_CG1];
     seg_total_groups<P_CG1>(S, lds, t);
     if (threadIdx.x == 0) {
-        SegState *st = S.sst;
-        const double n = S.n;
-        const double rr = t[P_UPD + 3] - t[P_UPD + 2] * t[P_UPD + 2] / n;
-        st->res = sqrt(fmax(rr / n, 0.0));
-        st->qshift = (S.Q - t[P_UPD + 4]) / n;
-        const bool first = st->cg_first != 0;
-        if (first) {
-            st->res0 = st->res;
-        } else {
-            st->iters += 1;
-            st->iters_total += 1;
-        }
-        if (st->cg_last || st->res < ctl.tol) {
-            st->done = 1;
-            return;
-        }
-        if (st->iters >= ctl.maxit) {
-            st->done = 1;
-            atomicOr(&st->status, ST_NOCONV);
-            return;
-        }
-        const double gam = t[P_UPD + 1], del = t[P_PRD + 0];
-        const double beta = first ? 0.0 : gam / st->rho;
-        const double den = first ? del : del - beta * gam / st->alpha;
-        if (!(den > 0.0) || !(gam > 0.0)) {
-            atomicOr(&st->status, ST_NOT_PD);
-            st->done = 1;
-            return;
-        }
-        const double alpha = gam / den;
-        // sums of the new s = H y + beta s_old (m1^T s by its own recurrence:
-        // an error in it only leaves m1^T r of the next residual slightly off
-        // zero, and the next shift, from the measured m1^T r, removes that)
-        const double m1s = first ? t[P_PRD + 1] : t[P_PRD + 1] + beta * st->m1s;
-        const double rs = t[P_PRD + 2] + beta * t[P_UPD + 5];
-        const double ss = t[P_PRD + 3] + 2.0 * beta * t[P_PRD + 4] + beta * beta * t[P_UPD + 6];
-        const double sum_s = t[P_PRD + 5] + beta * t[P_UPD + 7];
-        const double c = (t[P_UPD + 0] - alpha * m1s) / st->sdinv;
-        const double rs_p = rs - t[P_UPD + 2] * sum_s / n;
-        const double ss_p = ss - sum_s * sum_s / n;
-        const double next2 = (rr - 2.0 * alpha * rs_p + alpha * alpha * ss_p) / n;
-        st->cg_first = 0;
-        st->m1s = m1s;
-        st->rho = gam;
-        st->alpha = alpha;
-        st->beta = beta;
-        st->w = c;
-        st->mshift -= c;
-        if (next2 < ctl.tol * ctl.tol) st->cg_last = 1;
+        const int bad = cg1_step(*S.sst, 1.0 / S.n, 1.0 / S.sst->sdinv, S.Q, t, ctl.tol, ctl.maxit);
+        if (bad) atomicOr(&S.sst->status, bad);
     }
 }
 
@@ -885,7 +888,7 @@ __global__ void __launch_bounds__(TILE) k_force_coul(const Tile *tiles, Seg *seg
     using V4 = typename Vec4<R>::type;
     const Tile T = my_tile(tiles);
     const Seg &S = segs[T.seg];
-    if (gate && (!S.sst->done || S.sst->forces_done)) return;
+    if (gate && (!S.sst->done || S.sst->pabort || S.sst->forces_done)) return;
     __shared__ V4 dtab[NCODE];
     __shared__ double lds[4 * 3];
     load_dtab2<R>(S, dtab);
@@ -976,7 +979,7 @@ __global__ void __launch_bounds__(TILE) k_force_coul(const Tile *tiles, Seg *seg
 __global__ void k_fin_energy(const int *seg_ids, Seg *segs, int gate)
 {
     const Seg &S = segs[seg_ids[blockIdx.x]];
-    if (gate && (!S.sst->done || S.sst->forces_done)) return;
+    if (gate && (!S.sst->done || S.sst->pabort || S.sst->forces_done)) return;
     __shared__ double lds[4 * 3];
     double tot[3];
     seg_total<3>(S, lds, tot);
@@ -999,7 +1002,7 @@ __global__ void k_collect(const int *seg_ids, Seg *segs, int nseg, int4 *out)
     int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nseg) return;
     const SegState *st = segs[seg_ids[k]].sst;
-    out[k] = make_int4(st->done, st->forces_done, st->status, st->iters);
+    out[k] = make_int4(st->done && !st->pabort, st->forces_done, st->status, st->iters);
 }
 
 } // namespace ctbop

@@ -353,7 +353,7 @@ __global__ void __launch_bounds__(TILE) k_force_cov(const Tile *tiles, Seg *segs
     const Tile T = my_tile(tiles);
     const Seg &S = segs[T.seg];
     // serving: only segments whose charge solve finished and whose forces are pending
-    if (gate && (!S.sst->done || S.sst->forces_done)) return;
+    if (gate && (!S.sst->done || S.sst->pabort || S.sst->forces_done)) return;
     __shared__ V4 dtab[NCODE];
     __shared__ Params<R> Pl;
     // the first BOND_CACHE bonds of each thread's atom: vector, length, pair type

@@ -59,6 +59,7 @@ struct SrvSlot {
     Layout L;
     size_t io_off = 0;              // I/O arrays at the start of the region
     int phase = 0;                  // 0 = needs set-up, 1 = solving/finishing
+    bool many = false;              // its one-launch solve gave up: multi-launch solve
     long sys_id = -1;
     double last_use = 0;
     Sig sig;
@@ -219,6 +220,7 @@ int admit_one(ctbop_server *S, SrvReq &r, bool &placed)
     sl.sys_id = r.sys_id;
     sl.state = ACTIVE;
     sl.phase = 0;
+    sl.many = false;
     sl.req = std::move(r);
     sl.req.t_admit = now_s();
     sl.last_use = sl.req.t_admit;
@@ -281,18 +283,32 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
     if (total_tiles > S->max_tiles) return fail(CTBOP_E_NOMEM, "server tile table too small");
     Tile *hts = S->htiles, *hta = S->htiles + S->max_tiles;
     int *his = S->hids, *hia = S->hids + S->max_slots;
-    for (int k : act) {
-        SrvSlot &sl = S->slots[k];
-        for (int t = 0; t < sl.L.ntile; t++) {
-            Tile tt;
-            tt.seg = k;
-            tt.row0 = t * TILE;
-            if (sl.phase == 0) hts[nts++] = tt;
-            hta[nta++] = tt;
+    // Set-up tables: the systems of each one-launch class (8 and 4 lanes per
+    // row), then those of the multi-launch solve.  Active tables: the
+    // multi-launch systems first, which the iterations below run over.
+    constexpr int CLS[3] = {8, 4, 0};
+    int cls_tiles[3] = {0, 0, 0}, nis_many = 0, nta_many = 0, nia_many = 0;
+    auto cls_of = [&](const SrvSlot &sl) { return sl.many ? 0 : solve_lpr(ctx, sl.L.seg.n); };
+    for (int c = 0; c < 3; c++)
+        for (int k : act) {
+            SrvSlot &sl = S->slots[k];
+            if (sl.phase != 0 || cls_of(sl) != CLS[c]) continue;
+            for (int t = 0; t < sl.L.ntile; t++) hts[nts++] = Tile{k, t * TILE};
+            cls_tiles[c] += sl.L.ntile;
+            his[nis++] = k;
+            if (CLS[c] == 0) nis_many++;
         }
-        if (sl.phase == 0) his[nis++] = k;
-        hia[nia++] = k;
-    }
+    for (int many = 1; many >= 0; many--)
+        for (int k : act) {
+            SrvSlot &sl = S->slots[k];
+            if ((cls_of(sl) == 0) != (many != 0)) continue;
+            for (int t = 0; t < sl.L.ntile; t++) hta[nta++] = Tile{k, t * TILE};
+            hia[nia++] = k;
+            if (many) {
+                nta_many = nta;
+                nia_many = nia;
+            }
+        }
     HIPCHK(hipMemcpyAsync(S->dtiles_setup, hts, sizeof(Tile) * std::max(nts, 1), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(S->dtiles_act, hta, sizeof(Tile) * nta, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(S->dids_setup, his, sizeof(int) * std::max(nis, 1), hipMemcpyHostToDevice, st));
@@ -318,16 +334,26 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         hipLaunchKernelGGL(k_rev, g, b, 0, st, T, S->dsegs);
         hipLaunchKernelGGL(k_mark_built, dim3((nis + 63) / 64), dim3(64), 0, st, sid, S->dsegs, nis);
         hipLaunchKernelGGL((k_assemble<R, LPR>), g, b, 0, st, T, S->dsegs, ctx->pd);
-        hipLaunchKernelGGL((k_hslice<R>), g, b, 0, st, T, S->dsegs);
         // covalent energy and forces need only the lists: side stream, forked
-        // after the sliced copy so that they run beside the solve
+        // after the assembly so that they run beside the solve
         HIPCHK(hipEventRecord(S->ev_fork, st));
         HIPCHK(hipStreamWaitEvent(S->side, S->ev_fork, 0));
         hipLaunchKernelGGL((k_bond<R>), g, b, 0, S->side, T, S->dsegs, ctx->pd);
         hipLaunchKernelGGL((k_force_cov<R>), g, b, 0, S->side, T, S->dsegs, prm, 0);
         HIPCHK(hipEventRecord(S->ev_join, S->side));
-        hipLaunchKernelGGL(k_fin_w0, gs, b, 0, st, sid, S->dsegs);
-        hipLaunchKernelGGL((k_cg1_update<true>), g, b, 0, st, T, S->dsegs);
+        for (int c = 0, t0 = 0; c < 2; t0 += cls_tiles[c++])
+            if (cls_tiles[c]) {
+                launch_solve_prep<R>(CLS[c], T + t0, cls_tiles[c], S->dsegs, st);
+                launch_solve<R>(CLS[c], ctx->ncu, T + t0, cls_tiles[c], S->dsegs,
+                                SolveCtl{ctx->opts.cg_tol, ctx->opts.cg_maxit, 0}, st);
+            }
+        if (nis_many) {
+            const dim3 gm(cls_tiles[2]);
+            const Tile *Tm = T + (nts - cls_tiles[2]);
+            hipLaunchKernelGGL((k_hslice<R>), gm, b, 0, st, Tm, S->dsegs);
+            hipLaunchKernelGGL(k_fin_w0, dim3(nis_many), b, 0, st, sid + (nis - nis_many), S->dsegs);
+            hipLaunchKernelGGL((k_cg1_update<true>), gm, b, 0, st, Tm, S->dsegs);
+        }
     }
     {
         const dim3 g(nta), gs(nia);
@@ -336,24 +362,25 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         CgCtl ctl{ctx->opts.cg_tol, ctx->opts.cg_maxit};
         // single-reduction solve: a solve of n iterations takes n + 1 rounds
         // (its first finalize counts none)
-        const int limit = poll ? ctx->opts.cg_maxit + 2 : cg_iters;
+        const dim3 gm(nta_many), gsm(nia_many);
+        const int limit = nia_many == 0 ? 0 : poll ? ctx->opts.cg_maxit + 2 : cg_iters;
         for (int c = 0; c < limit;) {
             const int first = std::max(ctx->opts.cg_check, std::min(S->iters_hint, ctx->opts.cg_maxit) + 1);
             const int chunk = poll ? std::min(limit - c, c == 0 ? first : ctx->opts.cg_check) : cg_iters;
             for (int k = 0; k < chunk; k++) {
-                hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), g, b, 0, st, T, S->dsegs);
-                hipLaunchKernelGGL(k_cg1_sum, dim3(nia * FIN_SPLIT), b, 0, st, sid, S->dsegs);
-                hipLaunchKernelGGL(k_cg1_fin, gs, b, 0, st, sid, S->dsegs, ctl);
-                hipLaunchKernelGGL((k_cg1_update<false>), g, b, 0, st, T, S->dsegs);
+                hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), gm, b, 0, st, T, S->dsegs);
+                hipLaunchKernelGGL(k_cg1_sum, dim3(nia_many * FIN_SPLIT), b, 0, st, sid, S->dsegs);
+                hipLaunchKernelGGL(k_cg1_fin, gsm, b, 0, st, sid, S->dsegs, ctl);
+                hipLaunchKernelGGL((k_cg1_update<false>), gm, b, 0, st, T, S->dsegs);
             }
             c += chunk;
             if (!poll || c >= limit) break;
-            hipLaunchKernelGGL(k_collect, dim3((nia + 63) / 64), dim3(64), 0, st, sid, S->dsegs, nia, S->dflags);
+            hipLaunchKernelGGL(k_collect, dim3((nia_many + 63) / 64), dim3(64), 0, st, sid, S->dsegs, nia_many, S->dflags);
             HIPCHK(hipGetLastError());
-            HIPCHK(hipMemcpyAsync(S->hflags, S->dflags, sizeof(int4) * nia, hipMemcpyDeviceToHost, st));
+            HIPCHK(hipMemcpyAsync(S->hflags, S->dflags, sizeof(int4) * nia_many, hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
             bool any_done = false;
-            for (int a = 0; a < nia; a++) any_done = any_done || S->hflags[a].x != 0;
+            for (int a = 0; a < nia_many; a++) any_done = any_done || S->hflags[a].x != 0;
             if (any_done) break;
             if (c >= cg_iters) {
                 std::lock_guard<std::mutex> lk(S->mu);
@@ -373,7 +400,13 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
     for (int a = 0; a < nia; a++) {
         SrvSlot &sl = S->slots[hia[a]];
         sl.phase = 1;
-        if (S->hflags[a].y) fin.push_back(a);
+        if (S->hflags[a].y) {
+            fin.push_back(a);
+        } else if (cls_of(sl) != 0) {
+            // its one-launch solve gave up: set up again, multi-launch
+            sl.many = true;
+            sl.phase = 0;
+        }
     }
     for (int a : fin) {
         SrvSlot &sl = S->slots[hia[a]];
@@ -395,7 +428,7 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         r.ticket = sl.req.ticket;
         r.status = map_status(S->hflags[a].z);
         r.cg_iters = S->hflags[a].w;
-        S->iters_hint = r.cg_iters;
+        if (cls_of(sl) == 0) S->iters_hint = r.cg_iters;
         r.n_atoms = sl.req.n;
         r.t_submit = sl.req.t_submit;
         r.t_admit = sl.req.t_admit;

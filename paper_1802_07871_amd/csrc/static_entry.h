@@ -74,7 +74,7 @@ extern "C" int ctbop_compute_energy_forces_charges_static(ctbop_ctx *ctx, int n,
     // every call starts over (state cleared, lists rebuilt, cold charges)
     P.fresh = true;
     P.own = false;
-    int flag[2] = {0, 0};
+    int flag[3] = {0, 0, 0};
     P.flag_host = flag;
     hipLaunchKernelGGL(k_reset_state, dim3((P.L.ntile + 255) / 256), dim3(256), 0, P.st, P.L.seg.sst, P.dtiles,
                        P.L.ntile, P.dsegid);

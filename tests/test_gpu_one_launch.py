@@ -1,0 +1,59 @@
+"""The charge solve in one launch (systems of up to 32,512 atoms) against the
+oracle, at the sizes where its layout changes: one row block and its
+neighbours (64 rows of 8 lanes), the change from 8 to 4 lanes per row (16,384
+atoms on 256 CUs), the last size that takes it and the first that takes the
+multi-launch solve, and rows longer than the entries a lane keeps in
+registers (192: dense carbon has ~340 neighbours inside the cutoff), with
+both numbers of lanes.  Tolerances as in the other parity tests: mixed 1e-5
+relative RMS forces, 1e-6 eV/atom, 1e-6 e; FP64 1e-10 (charges solved to
+1e-13 there).
+"""
+import numpy as np
+import pytest
+
+from ctbop_inputs import generators as G
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"mixed": dict(F=1e-5, E=1e-6, q=1e-6), "fp64": dict(F=1e-10, E=1e-10, q=1e-10)}
+
+# (atoms, periodic, carbon fraction, density g/cm^3)
+CASES = [(63, False, 0.7, 2.6), (64, False, 0.7, 2.6), (65, True, 0.7, 2.6), (257, True, 0.6, 3.0),
+         (900, True, 0.9, 3.2), (16384, True, 0.7, 2.8), (16385, False, 0.7, 2.8), (17000, True, 0.9, 3.2),
+         (32512, True, 0.7, 2.4), (32513, True, 0.7, 2.4)]
+
+
+@pytest.fixture(scope="module")
+def ct():
+    import paper_1802_07871_amd as ct
+    return ct
+
+
+@pytest.fixture(scope="module")
+def reference(orc, theta):
+    done = {}
+
+    def get(case):
+        if case not in done:
+            n, periodic, c_frac, density = case
+            s = G.random_system(n, c_frac, density, periodic, seed=3000 + n)
+            done[case] = s, orc.evaluate(s.pos, s.types, s.box, s.pbc, theta, tol=1e-13)
+        return done[case]
+    return get
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("case", CASES, ids=[str(c[0]) for c in CASES])
+def test_matches_oracle(ct, theta, reference, case, prec):
+    s, (Eo, Fo, qo, _) = reference(case)
+    print(f"[one launch] n={s.n} {prec}", flush=True)
+    pot = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=1e-9 if prec == "mixed" else 1e-13)
+    E, F, q, info = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)
+    F, q, t = F.cpu().numpy(), q.cpu().numpy(), TOL[prec]
+    assert info["status"] == 0
+    assert abs(E - Eo) / s.n <= t["E"]
+    assert np.linalg.norm(F - Fo) / np.linalg.norm(Fo) <= t["F"]
+    assert np.abs(q - qo).max() <= t["q"]
+    again = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=1e-9 if prec == "mixed" else 1e-13).compute(
+        s.pos, s.types, s.box, s.pbc, warm=False)
+    assert again[0] == E and np.array_equal(again[1].cpu().numpy(), F) and np.array_equal(again[2].cpu().numpy(), q)
