@@ -29,6 +29,10 @@ namespace {
 
 constexpr int LPR = 16;             // lanes per Coulomb row (assembly, force gather)
 constexpr int BUILD_L = 4;          // lanes per atom in the list build (tuned: 2, 4, 8, 16 lanes)
+constexpr int FINE_L = 16;          // lanes per atom in the list build of small systems (a row per group)
+// systems up to this size take the Coulomb row kernels in blocks of FINE rows
+// (16 blocks per tile): 256 tiles and more fill the chip by themselves
+constexpr int FINE_MAX = 256 * TILE;
 constexpr int SPMV_U = 8;           // list entries in flight per row in the charge-solve product (tuned)
 
 thread_local std::string g_err;
@@ -569,6 +573,45 @@ void launch_solve(int lpr, int ncu, const Tile *tiles, int nt, Seg *segs, SolveC
     else hipLaunchKernelGGL((k_solve<4, R, 2>), g, b, 0, st, tiles, segs, ctl);
 }
 
+// The row kernels over nt tiles, a tile or FINE rows per block.  The list
+// build of FINE-row blocks leaves out the halos, which only the multi-launch
+// solve reads; lists, reverse slots and Coulomb rows are the same either way.
+template <typename R>
+void launch_build(bool fine, const Tile *tiles, int nt, Seg *segs, const Params<R> &prm, hipStream_t st)
+{
+    const dim3 b(TILE);
+    if (fine) hipLaunchKernelGGL((k_build<R, FINE_L, FINE>), dim3(nt * (TILE / FINE)), b, 0, st, tiles, segs, prm);
+    else hipLaunchKernelGGL((k_build<R, BUILD_L, TILE>), dim3(nt), b, 0, st, tiles, segs, prm);
+}
+void launch_rev(bool fine, const Tile *tiles, int nt, Seg *segs, hipStream_t st)
+{
+    const dim3 b(TILE);
+    if (fine) hipLaunchKernelGGL(k_rev<FINE>, dim3(nt * (TILE / FINE)), b, 0, st, tiles, segs);
+    else hipLaunchKernelGGL(k_rev<TILE>, dim3(nt), b, 0, st, tiles, segs);
+}
+template <typename R>
+void launch_assemble(bool fine, const Tile *tiles, int nt, Seg *segs, const Params<double> &pd, hipStream_t st)
+{
+    const dim3 b(TILE);
+    if (fine) hipLaunchKernelGGL((k_assemble<R, LPR, FINE>), dim3(nt * (TILE / FINE)), b, 0, st, tiles, segs, pd);
+    else hipLaunchKernelGGL((k_assemble<R, LPR, TILE>), dim3(nt), b, 0, st, tiles, segs, pd);
+}
+// (the energy's order of summation depends on the choice: fine is n <=
+// FINE_MAX, so that a system gives the same bits alone and in the server)
+template <typename R>
+void launch_force_coul(bool fine, const Tile *tiles, int nt, const int *ids, int nid, Seg *segs,
+                       const Params<double> &pd, int gate, hipStream_t st)
+{
+    const dim3 b(TILE);
+    if (fine) {
+        hipLaunchKernelGGL((k_force_coul<R, LPR, FINE>), dim3(nt * (TILE / FINE)), b, 0, st, tiles, segs, pd, gate);
+        hipLaunchKernelGGL(k_fin_energy<FINE>, dim3(nid), b, 0, st, ids, segs, gate);
+    } else {
+        hipLaunchKernelGGL((k_force_coul<R, LPR, TILE>), dim3(nt), b, 0, st, tiles, segs, pd, gate);
+        hipLaunchKernelGGL(k_fin_energy<TILE>, dim3(nid), b, 0, st, ids, segs, gate);
+    }
+}
+
 // Sorted frame and neighbour lists for the current positions (the lists are
 // rebuilt when an atom has moved more than half the skin, or on request).
 template <typename R>
@@ -592,12 +635,14 @@ void launch_lists(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags)
     hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, P.dtiles, P.dseg, warm);
     hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
     hipLaunchKernelGGL(k_qfix, g, b, 0, st, P.dtiles, P.dseg);
+    const bool fine = solve_lpr(ctx, P.L.seg.n) != 0;
     {
         Timed t(ctx, 7, st);
-        hipLaunchKernelGGL((k_build<R, BUILD_L>), g, b, 0, st, P.dtiles, P.dseg, prm);
+        launch_build<R>(fine, P.dtiles, nt, P.dseg, prm, st);
     }
-    hipLaunchKernelGGL(k_rev, g, b, 0, st, P.dtiles, P.dseg);
-    hipLaunchKernelGGL(k_mark_built, g1, dim3(64), 0, st, sid, P.dseg, 1);
+    launch_rev(fine, P.dtiles, nt, P.dseg, st);
+    if (fine) hipLaunchKernelGGL(k_mark_built_fine, g1, b, 0, st, sid, P.dseg);
+    else hipLaunchKernelGGL(k_mark_built, g1, dim3(64), 0, st, sid, P.dseg, 1);
 }
 
 // One evaluation: sorted frame and lists, bond pass, Coulomb rows, charge
@@ -653,6 +698,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         return CTBOP_OK;
     };
     const int lpr = solve_lpr(ctx, P.L.seg.n);
+    const bool fine = P.L.seg.n <= FINE_MAX;
     if (fq || lpr) {
         const int rc = side_launch();
         if (rc) return rc;
@@ -663,7 +709,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
     if (lpr) {
         {
             Timed t(ctx, 2, st);
-            hipLaunchKernelGGL((k_assemble<R, LPR>), g, b, 0, st, P.dtiles, P.dseg, ctx->pd);
+            launch_assemble<R>(fine, P.dtiles, nt, P.dseg, ctx->pd, st);
         }
         {
             Timed t(ctx, 8, st);
@@ -689,7 +735,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
     if (!solved) {
         {
             Timed t(ctx, 2, st);
-            hipLaunchKernelGGL((k_assemble<R, LPR>), g, b, 0, st, P.dtiles, P.dseg, ctx->pd);
+            launch_assemble<R>(fine, P.dtiles, nt, P.dseg, ctx->pd, st);
         }
         if (fq) {
             // the starting residual needs the coupling weights of this step
@@ -773,9 +819,8 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
     }
     {
         Timed t(ctx, 1, st);
-        hipLaunchKernelGGL((k_force_coul<R, LPR>), g, b, 0, st, P.dtiles, P.dseg, ctx->pd, 0);
+        launch_force_coul<R>(fine, P.dtiles, nt, sid, 1, P.dseg, ctx->pd, 0, st);
     }
-    hipLaunchKernelGGL(k_fin_energy, g1, b, 0, st, sid, P.dseg, 0);
     HIPCHK(hipGetLastError());
     return CTBOP_OK;
 }

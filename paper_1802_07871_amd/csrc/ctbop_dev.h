@@ -23,6 +23,7 @@ constexpr int CODE_CENTER = 171;       // offset (0,0,0)
 constexpr int MAX_ATOMS = (1 << CODE_SHIFT) - 1;
 constexpr int SLICE = 64;              // rows per slice of the sliced list layout (one wave)
 constexpr int BK = 16;                 // rows per block of the block-Jacobi preconditioner
+constexpr int FINE = 16;               // rows per block of the row kernels in small launches
 constexpr int WB = 32;                 // bond-row capacity (bonds inside S_ij per atom)
 constexpr int NHIST = 3;               // charge solutions kept before the latest (predictor history)
 constexpr int PRED_ORDER = 4;          // points of the starting-charge extrapolation (1..NHIST+1)
@@ -245,6 +246,18 @@ __device__ __forceinline__ Tile my_tile(const Tile *tiles)
     return tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
 }
 
+// The rows of this block when a tile is shared by TILE / ROWS blocks: a tile
+// whose row0 is the block's first row.
+template <int ROWS>
+__device__ __forceinline__ Tile my_rows(const Tile *tiles)
+{
+    constexpr int SUB = TILE / ROWS;
+    const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    Tile t = tiles[b / SUB];
+    t.row0 += (b % SUB) * ROWS;
+    return t;
+}
+
 // ---------------------------------------------------------------------------
 // helpers
 // ---------------------------------------------------------------------------
@@ -462,6 +475,22 @@ __device__ __forceinline__ void seg_total(const Seg &S, double *lds, double (&ou
     for (int t = threadIdx.x; t < nt; t += TILE) {
 #pragma unroll
         for (int k = 0; k < K; k++) v[k] += part[(size_t)k * nt + t];
+    }
+    block_sum<K>(v, lds, out);
+}
+
+// The same over cnt blocks' partials in v (partial k of block b at k * cnt + b).
+template <int K>
+__device__ __forceinline__ void block_total(const double *v_, int cnt, double *lds, double (&out)[K])
+{
+    double v[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) v[k] = 0.0;
+    const auto part = gbl(v_);
+#pragma unroll 4
+    for (int t = threadIdx.x; t < cnt; t += TILE) {
+#pragma unroll
+        for (int k = 0; k < K; k++) v[k] += part[(size_t)k * cnt + t];
     }
     block_sum<K>(v, lds, out);
 }

@@ -378,18 +378,24 @@ __device__ __forceinline__ void write_halo(const Seg &S, const Tile &T, const un
 // atom take L consecutive atoms of a cell at a time (one coalesced read of
 // their coordinates); group ballots place the accepted ones in list order.
 // Per-row statistics are reduced over the block before one atomic each.
-template <typename R, int L>
+// ROWS = TILE: also the tile's halo, for the multi-launch solve.  ROWS = FINE
+// (systems of the one-launch solve, which finds its blocks' neighbours
+// itself): a block per 16 rows with 16 lanes each, the rows' statistics left
+// in S.Fcov for k_mark_built; 20,000 atoms 535 -> 78 us.
+template <typename R, int L, int ROWS>
 __global__ void __launch_bounds__(TILE) k_build(const Tile *tiles, Seg *segs, Params<R> P)
 {
     using V4 = typename Vec4<R>::type;
-    const Tile T = my_tile(tiles);
+    constexpr bool HALO = ROWS == TILE;
+    const Tile T = my_rows<ROWS>(tiles);
     const Seg &S = segs[T.seg];
     if (!S.sst->rebuild) return;
     __shared__ V4 dtab[NCODE];
     __shared__ int red[4][5];
-    __shared__ unsigned long long hbm[HALO_WORDS];
+    __shared__ unsigned long long hbm[HALO ? HALO_WORDS : 1];
     __shared__ int wsum[TILE / 64];
-    for (int w = threadIdx.x; w < HALO_WORDS; w += TILE) hbm[w] = 0ull;
+    if constexpr (HALO)
+        for (int w = threadIdx.x; w < HALO_WORDS; w += TILE) hbm[w] = 0ull;
     load_dtab<R>(S, dtab);
     __syncthreads();
     const V4 *xs = reinterpret_cast<const V4 *>(S.xs);
@@ -404,7 +410,7 @@ __global__ void __launch_bounds__(TILE) k_build(const Tile *tiles, Seg *segs, Pa
     const int lane = threadIdx.x % L;
     const unsigned below = (1u << lane) - 1u;
     int st_or = 0, mx_l = 0, mx_s = 0, sum_l = 0, sum_s = 0;
-    for (int k = threadIdx.x / L; k < TILE; k += G) {
+    for (int k = threadIdx.x / L; k < ROWS; k += G) {
         const int s = T.row0 + k;
         if (s >= n) continue;                  // the whole group skips together
         const V4 li = ld4<R>(xs, s);
@@ -484,8 +490,10 @@ __global__ void __launch_bounds__(TILE) k_build(const Tile *tiles, Seg *segs, Pa
                         if (inl) {
                             const int at = nl + __popc(gl & below);
                             if (at < Wl) lrow[at] = ent;
-                            const int hw = m - T.row0 + HALO_WIN / 2;
-                            if ((unsigned)hw < (unsigned)HALO_WIN) atomicOr(&hbm[hw >> 6], 1ull << (hw & 63));
+                            if constexpr (HALO) {
+                                const int hw = m - T.row0 + HALO_WIN / 2;
+                                if ((unsigned)hw < (unsigned)HALO_WIN) atomicOr(&hbm[hw >> 6], 1ull << (hw & 63));
+                            }
                         }
                         if (ins) {
                             const int at = ns + __popc(gs & below);
@@ -537,21 +545,30 @@ __global__ void __launch_bounds__(TILE) k_build(const Tile *tiles, Seg *segs, Pa
             red[0][3] += red[w][3];
             red[0][4] += red[w][4];
         }
-        if (red[0][0]) atomicOr(&S.sst->status, red[0][0]);
-        atomicMax(&S.sst->maxl, red[0][1]);
-        atomicMax(&S.sst->maxs, red[0][2]);
-        atomicAdd(&S.sst->nnz_long, (unsigned long long)red[0][3]);
-        atomicAdd(&S.sst->nnz_short, (unsigned long long)red[0][4]);
+        if constexpr (HALO) {
+            if (red[0][0]) atomicOr(&S.sst->status, red[0][0]);
+            atomicMax(&S.sst->maxl, red[0][1]);
+            atomicMax(&S.sst->maxs, red[0][2]);
+            atomicAdd(&S.sst->nnz_long, (unsigned long long)red[0][3]);
+            atomicAdd(&S.sst->nnz_short, (unsigned long long)red[0][4]);
+        } else {
+            int *out = reinterpret_cast<int *>(S.Fcov) + 5 * (T.row0 / ROWS);
+            for (int k = 0; k < 5; k++) out[k] = red[0][k];
+            // (no halo: the multi-launch solve, should it have to run, then
+            // takes its 16-bit offsets)
+            if (T.row0 % TILE == 0) S.nhalo[T.row0 / TILE] = HALO_MAX + 1;
+        }
     }
-    write_halo(S, T, hbm, wsum);
+    if constexpr (HALO) write_halo(S, T, hbm, wsum);
 }
 
 // For every covalent entry (i -> j, d) the slot of (j -> i, -d) in row j:
 // 16 lanes per row, one entry each, every lane searching its partner's row.
+template <int ROWS>
 __global__ void __launch_bounds__(TILE) k_rev(const Tile *tiles, Seg *segs)
 {
     constexpr int LR = 16;
-    const Tile T = my_tile(tiles);
+    const Tile T = my_rows<ROWS>(tiles);
     const Seg &S = segs[T.seg];
     if (!S.sst->rebuild) return;
     const int lane = threadIdx.x % LR;
@@ -559,7 +576,7 @@ __global__ void __launch_bounds__(TILE) k_rev(const Tile *tiles, Seg *segs)
     const auto sidx = gbl(S.sidx);
     const auto scnt = gbl(S.scnt);
     bool bad = false;
-    for (int k = threadIdx.x / LR; k < TILE; k += TILE / LR) {
+    for (int k = threadIdx.x / LR; k < ROWS; k += TILE / LR) {
         const int s = T.row0 + k;
         if (s >= S.n) break;                     // rows past n come last: the group is done
         const int ns = scnt[s];
@@ -584,6 +601,53 @@ __global__ void k_mark_built(const int *seg_ids, Seg *segs, int nseg)
     if (k >= nseg) return;
     SegState *st = segs[seg_ids[k]].sst;
     if (st->rebuild) {
+        st->built = 1;
+        st->nrebuild += 1;
+    }
+}
+
+// The same for systems built in FINE-row blocks: one block per segment adds
+// up their rows' statistics.
+__global__ void __launch_bounds__(TILE) k_mark_built_fine(const int *seg_ids, Seg *segs)
+{
+    const Seg &S = segs[seg_ids[blockIdx.x]];
+    SegState *st = S.sst;
+    if (!st->rebuild) return;
+    __shared__ int red[TILE / 64][5];
+    const int *v = reinterpret_cast<const int *>(S.Fcov);
+    // (a segment of FINE-row blocks has under 2^31 entries)
+    int r[5] = {0, 0, 0, 0, 0};
+    for (int b = threadIdx.x; b < S.npad / FINE; b += TILE) {
+        r[0] |= v[5 * b];
+        r[1] = max(r[1], v[5 * b + 1]);
+        r[2] = max(r[2], v[5 * b + 2]);
+        r[3] += v[5 * b + 3];
+        r[4] += v[5 * b + 4];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        r[0] |= __shfl_xor(r[0], o, 64);
+        r[1] = max(r[1], __shfl_xor(r[1], o, 64));
+        r[2] = max(r[2], __shfl_xor(r[2], o, 64));
+        r[3] += __shfl_xor(r[3], o, 64);
+        r[4] += __shfl_xor(r[4], o, 64);
+    }
+    if ((threadIdx.x & 63) == 0)
+        for (int k = 0; k < 5; k++) red[threadIdx.x >> 6][k] = r[k];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < TILE / 64; w++) {
+            r[0] |= red[w][0];
+            r[1] = max(r[1], red[w][1]);
+            r[2] = max(r[2], red[w][2]);
+            r[3] += red[w][3];
+            r[4] += red[w][4];
+        }
+        if (r[0]) atomicOr(&st->status, r[0]);
+        st->maxl = r[1];
+        st->maxs = r[2];
+        st->nnz_long = (unsigned long long)r[3];
+        st->nnz_short = (unsigned long long)r[4];
         st->built = 1;
         st->nrebuild += 1;
     }

@@ -112,11 +112,16 @@ __device__ __forceinline__ double entry_r(const typename Vec4<R>::type &li, cons
 // starting residual r = -(H q0 + chi) + mu_prev.  A row is flagged (hwide)
 // when one of its entries lies further from the tile than a 16-bit offset
 // from any slice of the tile reaches (which keeps it in the halo window too).
-template <typename R, int LPR>
+//
+// ROWS rows per block: a tile per block where the launch fills the chip, FINE
+// rows where it does not (a group then takes one row instead of sixteen one
+// after another: the rows' loads, not the chip, set the time: 512 atoms 166 ->
+// 16 us, 20,000 atoms 202 -> 27 us).
+template <typename R, int LPR, int ROWS>
 __global__ void __launch_bounds__(TILE) k_assemble(const Tile *tiles, Seg *segs, Params<double> PD)
 {
     using V4 = typename Vec4<R>::type;
-    const Tile T = my_tile(tiles);
+    const Tile T = my_rows<ROWS>(tiles);
     const Seg &S = segs[T.seg];
     __shared__ V4 dtab[NCODE];
     load_dtab2<R>(S, dtab);
@@ -135,7 +140,7 @@ __global__ void __launch_bounds__(TILE) k_assemble(const Tile *tiles, Seg *segs,
     __shared__ R bval_lds[G][FL + LPR];
     uint32_t *bi = bidx_lds[threadIdx.x / LPR];
     R *bv = bval_lds[threadIdx.x / LPR];
-    for (int k = threadIdx.x / LPR; k < TILE; k += G) {
+    for (int k = threadIdx.x / LPR; k < ROWS; k += G) {
         const int s = T.row0 + k;
         if (s >= S.n) {
             if (s < S.npad && lane == 0) {
@@ -882,11 +887,13 @@ __global__ void __launch_bounds__(TILE) k_cg1_fin(const int *seg_ids, Seg *segs,
 
 // Coulomb forces and energy at the equilibrated charges, plus the covalent
 // forces and energies: writes F, q (user order) and the tile's energy.
-template <typename R, int LPR>
+// With ROWS < TILE (small launches, as in the assembly: 20,000 atoms 137 ->
+// 18 us) the blocks' sums go to S.s, free after the solve.
+template <typename R, int LPR, int ROWS>
 __global__ void __launch_bounds__(TILE) k_force_coul(const Tile *tiles, Seg *segs, Params<double> PD, int gate)
 {
     using V4 = typename Vec4<R>::type;
-    const Tile T = my_tile(tiles);
+    const Tile T = my_rows<ROWS>(tiles);
     const Seg &S = segs[T.seg];
     if (gate && (!S.sst->done || S.sst->pabort || S.sst->forces_done)) return;
     __shared__ V4 dtab[NCODE];
@@ -903,11 +910,11 @@ __global__ void __launch_bounds__(TILE) k_force_coul(const Tile *tiles, Seg *seg
     double esum = 0.0;
     // bond statistics of the step (for the measurement): bonds and ordered bond pairs
     double nb = 0.0, nt = 0.0;
-    if (T.row0 + (int)threadIdx.x < S.n) {
+    if ((int)threadIdx.x < ROWS && T.row0 + (int)threadIdx.x < S.n) {
         nb = (double)S.bcnt[T.row0 + threadIdx.x];
         nt = nb * (nb - 1.0);
     }
-    for (int k = threadIdx.x / LPR; k < TILE; k += G) {
+    for (int k = threadIdx.x / LPR; k < ROWS; k += G) {
         const int s = T.row0 + k;
         if (s >= S.n) continue;
         const V4 li = xs[s];
@@ -973,16 +980,27 @@ __global__ void __launch_bounds__(TILE) k_force_coul(const Tile *tiles, Seg *seg
         }
     }
     double v[3] = {esum, nb, nt};
-    tile_partials<3>(S, T.row0 / TILE, v, lds);
+    if constexpr (ROWS == TILE) {
+        tile_partials<3>(S, T.row0 / TILE, v, lds);
+    } else {
+        double tot[3];
+        block_sum<3>(v, lds, tot);
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int k = 0; k < 3; k++) S.s[(size_t)k * (S.npad / ROWS) + T.row0 / ROWS] = tot[k];
+        }
+    }
 }
 
+template <int ROWS>
 __global__ void k_fin_energy(const int *seg_ids, Seg *segs, int gate)
 {
     const Seg &S = segs[seg_ids[blockIdx.x]];
     if (gate && (!S.sst->done || S.sst->pabort || S.sst->forces_done)) return;
     __shared__ double lds[4 * 3];
     double tot[3];
-    seg_total<3>(S, lds, tot);
+    if constexpr (ROWS == TILE) seg_total<3>(S, lds, tot);
+    else block_total<3>(S.s, S.npad / ROWS, lds, tot);
     if (threadIdx.x == 0) {
         SegState *st = S.sst;
         st->energy = tot[0];

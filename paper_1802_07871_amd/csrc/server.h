@@ -298,13 +298,19 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
             his[nis++] = k;
             if (CLS[c] == 0) nis_many++;
         }
-    for (int many = 1; many >= 0; many--)
+    int nta_coarse = 0, nia_coarse = 0;
+    for (int c = 0; c < 3; c++)        // multi-launch above and up to FINE_MAX, one-launch
         for (int k : act) {
             SrvSlot &sl = S->slots[k];
-            if ((cls_of(sl) == 0) != (many != 0)) continue;
+            const int mine = cls_of(sl) != 0 ? 2 : sl.L.seg.n > FINE_MAX ? 0 : 1;
+            if (mine != c) continue;
             for (int t = 0; t < sl.L.ntile; t++) hta[nta++] = Tile{k, t * TILE};
             hia[nia++] = k;
-            if (many) {
+            if (c == 0) {
+                nta_coarse = nta;
+                nia_coarse = nia;
+            }
+            if (c <= 1) {
                 nta_many = nta;
                 nia_many = nia;
             }
@@ -330,10 +336,20 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, T, S->dsegs, -1);
         hipLaunchKernelGGL(k_fin_qshift, gs, b, 0, st, sid, S->dsegs);
         hipLaunchKernelGGL(k_qfix, g, b, 0, st, T, S->dsegs);
-        hipLaunchKernelGGL((k_build<R, BUILD_L>), g, b, 0, st, T, S->dsegs, prm);
-        hipLaunchKernelGGL(k_rev, g, b, 0, st, T, S->dsegs);
-        hipLaunchKernelGGL(k_mark_built, dim3((nis + 63) / 64), dim3(64), 0, st, sid, S->dsegs, nis);
-        hipLaunchKernelGGL((k_assemble<R, LPR>), g, b, 0, st, T, S->dsegs, ctx->pd);
+        const int nto = nts - cls_tiles[2], nio = nis - nis_many;   // of the one-launch solve
+        if (nto) {
+            launch_build<R>(true, T, nto, S->dsegs, prm, st);
+            launch_rev(true, T, nto, S->dsegs, st);
+            hipLaunchKernelGGL(k_mark_built_fine, dim3(nio), b, 0, st, sid, S->dsegs);
+            launch_assemble<R>(true, T, nto, S->dsegs, ctx->pd, st);
+        }
+        if (nis_many) {
+            launch_build<R>(false, T + nto, nts - nto, S->dsegs, prm, st);
+            launch_rev(false, T + nto, nts - nto, S->dsegs, st);
+            hipLaunchKernelGGL(k_mark_built, dim3((nis_many + 63) / 64), dim3(64), 0, st, sid + nio, S->dsegs,
+                               nis_many);
+            launch_assemble<R>(false, T + nto, nts - nto, S->dsegs, ctx->pd, st);
+        }
         // covalent energy and forces need only the lists: side stream, forked
         // after the assembly so that they run beside the solve
         HIPCHK(hipEventRecord(S->ev_fork, st));
@@ -388,8 +404,11 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
             }
         }
         if (nts) HIPCHK(hipStreamWaitEvent(st, S->ev_join, 0));
-        hipLaunchKernelGGL((k_force_coul<R, LPR>), g, b, 0, st, T, S->dsegs, ctx->pd, 1);
-        hipLaunchKernelGGL(k_fin_energy, gs, b, 0, st, sid, S->dsegs, 1);
+        if (nia_coarse)
+            launch_force_coul<R>(false, T, nta_coarse, sid, nia_coarse, S->dsegs, ctx->pd, 1, st);
+        if (nia > nia_coarse)
+            launch_force_coul<R>(true, T + nta_coarse, nta - nta_coarse, sid + nia_coarse, nia - nia_coarse, S->dsegs,
+                                 ctx->pd, 1, st);
         hipLaunchKernelGGL(k_collect, dim3((nia + 63) / 64), dim3(64), 0, st, sid, S->dsegs, nia, S->dflags);
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(S->hflags, S->dflags, sizeof(int4) * nia, hipMemcpyDeviceToHost, st));
