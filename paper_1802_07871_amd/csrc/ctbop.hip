@@ -596,6 +596,21 @@ void launch_assemble(bool fine, const Tile *tiles, int nt, Seg *segs, const Para
     if (fine) hipLaunchKernelGGL((k_assemble<R, LPR, FINE>), dim3(nt * (TILE / FINE)), b, 0, st, tiles, segs, pd);
     else hipLaunchKernelGGL((k_assemble<R, LPR, TILE>), dim3(nt), b, 0, st, tiles, segs, pd);
 }
+template <typename R>
+void launch_bond(bool fine, const Tile *tiles, int nt, Seg *segs, const Params<double> &pd, hipStream_t st)
+{
+    const dim3 b(TILE);
+    if (fine) hipLaunchKernelGGL((k_bond<R, COV_FINE>), dim3(nt * (TILE / COV_FINE)), b, 0, st, tiles, segs, pd);
+    else hipLaunchKernelGGL((k_bond<R, COV_ROWS>), dim3(nt * (TILE / COV_ROWS)), b, 0, st, tiles, segs, pd);
+}
+template <typename R>
+void launch_force_cov(bool fine, const Tile *tiles, int nt, Seg *segs, const Params<R> &prm, hipStream_t st)
+{
+    const dim3 b(TILE);
+    if (fine)
+        hipLaunchKernelGGL((k_force_cov<R, COV_FINE>), dim3(nt * (TILE / COV_FINE)), b, 0, st, tiles, segs, prm, 0);
+    else hipLaunchKernelGGL((k_force_cov<R, COV_ROWS>), dim3(nt * (TILE / COV_ROWS)), b, 0, st, tiles, segs, prm, 0);
+}
 // (the energy's order of summation depends on the choice: fine is n <=
 // FINE_MAX, so that a system gives the same bits alone and in the server)
 template <typename R>
@@ -655,6 +670,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
     hipStream_t st = P.st;
     const int *sid = P.dsegid;
     launch_lists<R>(ctx, P, prm, flags);
+    const bool fine = P.L.seg.n <= FINE_MAX;
     // covalent terms on the side stream: they need only the lists, and run
     // beside the charge solve and its host round trips, forked after the
     // sliced copy (beside the assembly and the copy they slowed both by more
@@ -683,22 +699,19 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         {
             Timed t(ctx, 3, cst);
             for (int t0 = 0; t0 < nt; t0 += chunk)
-                hipLaunchKernelGGL((k_bond<R>), dim3(std::min(chunk, nt - t0)), b, 0, cst, P.dtiles + t0, P.dseg,
-                                   ctx->pd);
+                launch_bond<R>(fine, P.dtiles + t0, std::min(chunk, nt - t0), P.dseg, ctx->pd, cst);
         }
         if (fq) {
             hipLaunchKernelGGL((k_fq_weight<R>), g, b, 0, cst, P.dtiles, P.dseg);
         } else {
             Timed t(ctx, 4, cst);
             for (int t0 = 0; t0 < nt; t0 += chunk)
-                hipLaunchKernelGGL((k_force_cov<R>), dim3(std::min(chunk, nt - t0)), b, 0, cst, P.dtiles + t0,
-                                   P.dseg, prm, 0);
+                launch_force_cov<R>(fine, P.dtiles + t0, std::min(chunk, nt - t0), P.dseg, prm, cst);
         }
         if (P.own) HIPCHK(hipEventRecord(ctx->ev_join, ctx->side));
         return CTBOP_OK;
     };
     const int lpr = solve_lpr(ctx, P.L.seg.n);
-    const bool fine = P.L.seg.n <= FINE_MAX;
     if (fq || lpr) {
         const int rc = side_launch();
         if (rc) return rc;
@@ -815,7 +828,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
     if (fq) {
         hipLaunchKernelGGL((k_fq_scale<R>), g, b, 0, st, P.dtiles, P.dseg);
         Timed t(ctx, 4, st);
-        hipLaunchKernelGGL((k_force_cov<R>), g, b, 0, st, P.dtiles, P.dseg, prm, 0);
+        launch_force_cov<R>(fine, P.dtiles, nt, P.dseg, prm, st);
     }
     {
         Timed t(ctx, 1, st);

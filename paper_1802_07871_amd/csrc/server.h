@@ -354,8 +354,9 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         // after the assembly so that they run beside the solve
         HIPCHK(hipEventRecord(S->ev_fork, st));
         HIPCHK(hipStreamWaitEvent(S->side, S->ev_fork, 0));
-        hipLaunchKernelGGL((k_bond<R>), g, b, 0, S->side, T, S->dsegs, ctx->pd);
-        hipLaunchKernelGGL((k_force_cov<R>), g, b, 0, S->side, T, S->dsegs, prm, 0);
+        const bool fine = nts <= FINE_MAX / TILE;
+        launch_bond<R>(fine, T, nts, S->dsegs, ctx->pd, S->side);
+        launch_force_cov<R>(fine, T, nts, S->dsegs, prm, S->side);
         HIPCHK(hipEventRecord(S->ev_join, S->side));
         for (int c = 0, t0 = 0; c < 2; t0 += cls_tiles[c++])
             if (cls_tiles[c]) {
