@@ -638,26 +638,29 @@ void launch_lists(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags)
     const int force = (flags & CTBOP_FLAG_FORCE_REBUILD) || P.fresh;
     const int warm = start_mode(P, flags);
     const int *sid = P.dsegid;
-    hipLaunchKernelGGL(k_call_init, g1, dim3(64), 0, st, sid, P.dseg, 1, force);
-    hipLaunchKernelGGL(k_check_disp, g, b, 0, st, P.dtiles, P.dseg);
-    hipLaunchKernelGGL(k_bin_clear, g, b, 0, st, P.dtiles, P.dseg);
-    hipLaunchKernelGGL(k_bin, g, b, 0, st, P.dtiles, P.dseg);
-    hipLaunchKernelGGL(k_scan_part, g, b, 0, st, P.dtiles, P.dseg);
-    hipLaunchKernelGGL(k_scan_mid, g1, b, 0, st, sid, P.dseg);
-    hipLaunchKernelGGL(k_scan_fin, g, b, 0, st, P.dtiles, P.dseg);
-    hipLaunchKernelGGL(k_scatter, g, b, 0, st, P.dtiles, P.dseg);
-    hipLaunchKernelGGL(k_cell_sort, g, b, 0, st, P.dtiles, P.dseg);
-    hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, P.dtiles, P.dseg, warm);
-    hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
-    hipLaunchKernelGGL(k_qfix, g, b, 0, st, P.dtiles, P.dseg);
+    if (P.L.seg.n <= L1_ATOMS && P.L.seg.ncell <= L1_CELLS) {
+        hipLaunchKernelGGL(k_frame_small<R>, g1, dim3(L1_T), 0, st, P.dseg, force, warm);
+    } else {
+        hipLaunchKernelGGL(k_call_init, g1, dim3(64), 0, st, sid, P.dseg, 1, force);
+        hipLaunchKernelGGL(k_check_disp, g, b, 0, st, P.dtiles, P.dseg);
+        hipLaunchKernelGGL(k_bin_clear, g, b, 0, st, P.dtiles, P.dseg);
+        hipLaunchKernelGGL(k_bin, g, b, 0, st, P.dtiles, P.dseg);
+        hipLaunchKernelGGL(k_scan_part, g, b, 0, st, P.dtiles, P.dseg);
+        hipLaunchKernelGGL(k_scan_mid, g1, b, 0, st, sid, P.dseg);
+        hipLaunchKernelGGL(k_scan_fin, g, b, 0, st, P.dtiles, P.dseg);
+        hipLaunchKernelGGL(k_scatter, g, b, 0, st, P.dtiles, P.dseg);
+        hipLaunchKernelGGL(k_cell_sort, g, b, 0, st, P.dtiles, P.dseg);
+        hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, P.dtiles, P.dseg, warm);
+        hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
+        hipLaunchKernelGGL(k_qfix, g, b, 0, st, P.dtiles, P.dseg);
+    }
     const bool fine = solve_lpr(ctx, P.L.seg.n) != 0;
     {
         Timed t(ctx, 7, st);
         launch_build<R>(fine, P.dtiles, nt, P.dseg, prm, st);
     }
     launch_rev(fine, P.dtiles, nt, P.dseg, st);
-    if (fine) hipLaunchKernelGGL(k_mark_built_fine, g1, b, 0, st, sid, P.dseg);
-    else hipLaunchKernelGGL(k_mark_built, g1, dim3(64), 0, st, sid, P.dseg, 1);
+    if (!fine) hipLaunchKernelGGL(k_mark_built, g1, dim3(64), 0, st, sid, P.dseg, 1);
 }
 
 // One evaluation: sorted frame and lists, bond pass, Coulomb rows, charge

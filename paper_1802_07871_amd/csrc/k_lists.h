@@ -242,42 +242,49 @@ __device__ __forceinline__ double pred_coef(int m, int k)
     constexpr double C[5][4] = {{0, 0, 0, 0}, {1, 0, 0, 0}, {2, 1, 0, 0}, {3, 3, 1, 0}, {4, 6, 4, 1}};
     return (k & 1) ? -C[m][k] : C[m][k];
 }
+// Row s (atom i): its local coordinates from its offset; returns its starting charge.
+template <typename R>
+__device__ __forceinline__ double gather_row(const Seg &S, int s, int i, double ox, double oy, double oz, int warm)
+{
+    using V4 = typename Vec4<R>::type;
+    double4 w;
+    w.x = S.x[i] + ox;
+    w.y = S.x[S.n + i] + oy;
+    w.z = S.x[2 * S.n + i] + oz;
+    w.w = (double)S.type[i];
+    V4 v;
+    v.x = (R)w.x;
+    v.y = (R)w.y;
+    v.z = (R)w.z;
+    v.w = (R)w.w;
+    reinterpret_cast<V4 *>(S.xs)[s] = v;
+    if ((void *)S.xs64 != S.xs) S.xs64[s] = w;
+    const int wm = warm < 0 ? S.sst->warm : warm;
+    double q0 = 0.0;
+    if (wm) {
+        int m = 1;
+        if (wm == 2) m = min(S.sst->nhist, (S.q_ring ? NHIST : 0) + 1);
+        m = min(m, PRED_ORDER);
+        if (m >= 1) {
+            q0 = pred_coef(m, 0) * S.q_state[i];
+            const int head = S.sst->qhead;
+            for (int k = 1; k < m; k++) {
+                const int slot = (head - (k - 1) + NHIST) % NHIST;
+                q0 += pred_coef(m, k) * S.q_ring[(size_t)slot * S.n + i];
+            }
+        }
+    }
+    return q0;
+}
 template <typename R>
 __global__ void k_gather(const Tile *tiles, Seg *segs, int warm)
 {
-    using V4 = typename Vec4<R>::type;
     const Tile T = my_tile(tiles);
     const Seg &S = segs[T.seg];
     const int s = T.row0 + threadIdx.x;
     double q0 = 0.0;
     if (s < S.n) {
-        const int i = S.perm[s];
-        double4 w;
-        w.x = S.x[i] + S.off[s];
-        w.y = S.x[S.n + i] + S.off[S.npad + s];
-        w.z = S.x[2 * S.n + i] + S.off[2 * S.npad + s];
-        w.w = (double)S.type[i];
-        V4 v;
-        v.x = (R)w.x;
-        v.y = (R)w.y;
-        v.z = (R)w.z;
-        v.w = (R)w.w;
-        reinterpret_cast<V4 *>(S.xs)[s] = v;
-        if ((void *)S.xs64 != S.xs) S.xs64[s] = w;
-        const int wm = warm < 0 ? S.sst->warm : warm;
-        if (wm) {
-            int m = 1;
-            if (wm == 2) m = min(S.sst->nhist, (S.q_ring ? NHIST : 0) + 1);
-            m = min(m, PRED_ORDER);
-            if (m >= 1) {
-                q0 = pred_coef(m, 0) * S.q_state[i];
-                const int head = S.sst->qhead;
-                for (int k = 1; k < m; k++) {
-                    const int slot = (head - (k - 1) + NHIST) % NHIST;
-                    q0 += pred_coef(m, k) * S.q_ring[(size_t)slot * S.n + i];
-                }
-            }
-        }
+        q0 = gather_row<R>(S, s, S.perm[s], S.off[s], S.off[S.npad + s], S.off[2 * S.npad + s], warm);
         S.q[s] = q0;
     } else if (s < S.npad) {
         S.q[s] = 0.0;
@@ -303,6 +310,153 @@ __global__ void k_fin_qshift(const int *seg_ids, Seg *segs)
     double tot[1];
     seg_total<1>(S, lds, tot);
     if (threadIdx.x == 0) S.sst->qshift = (S.Q - tot[0]) / S.n;
+}
+
+// The offset of an atom in cell c (fold w minus cell origin), component a
+__device__ __forceinline__ double cell_offset(const Seg &S, const double w[3], int c, int a)
+{
+    const int c0 = c / (S.nb[1] * S.nb[2]), c1 = (c / S.nb[2]) % S.nb[1], c2 = c % S.nb[2];
+    return w[0] * S.h[0][a] + w[1] * S.h[1][a] + w[2] * S.h[2][a] -
+           (c0 * S.cw[0][a] + c1 * S.cw[1][a] + c2 * S.cw[2][a]);
+}
+
+// k_call_init to k_qfix for a small system, in one block: twelve launches,
+// each a few microseconds for next to no work, become one (512 atoms without a
+// rebuild: about 45 us with the launch gaps -> 8 us; 1,999 atoms with one 25 us).  At most L1_ATOMS atoms (a few per thread) and L1_CELLS cells (counted
+// and scanned in LDS).  The same frame, bit for bit: the cell order is that
+// of the user indices, and the starting charges are summed by tiles, as
+// k_gather and k_fin_qshift do.
+constexpr int L1_T = 1024, L1_ATOMS = 4096, L1_CELLS = 16384;
+template <typename R>
+__global__ void __launch_bounds__(L1_T) k_frame_small(Seg *segs, int force_rebuild, int warm)
+{
+    constexpr int PER = L1_ATOMS / L1_T;
+    const Seg &S = segs[0];
+    SegState *st = S.sst;
+    __shared__ int cell[L1_CELLS];            // counts, then starts, then ends (fill counters)
+    __shared__ int tmp[L1_ATOMS];             // the scatter's order
+    __shared__ uint16_t at[L1_ATOMS];         // an atom's cell
+    __shared__ int scan[L1_T / 64];
+    __shared__ double part[L1_T / 64 * PER];
+    __shared__ double shift;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, n = S.n;
+    const bool built = st->built != 0;
+    int move = 0;
+    if (!force_rebuild && built) {
+        const double lim = 0.5 * S.skin;
+        for (int i = tid; i < n; i += L1_T) {
+            const double dx = S.x[i] - S.ref_x[i], dy = S.x[n + i] - S.ref_x[n + i],
+                         dz = S.x[2 * n + i] - S.ref_x[2 * n + i];
+            if (dx * dx + dy * dy + dz * dz > lim * lim || (int)S.xs64[i].w != S.type[S.perm[i]]) move = 1;
+        }
+    }
+    const bool rebuild = __syncthreads_or(move) != 0 || force_rebuild || !built;
+    if (tid == 0) {
+        st->rebuild = rebuild ? 1 : 0;
+        st->ticket = 0;
+        st->done = 0;
+        st->iters = 0;
+        st->pabort = 0;
+        st->status = 0;
+        st->forces_done = 0;
+        if (rebuild) {
+            st->maxl = 0;
+            st->maxs = 0;
+            st->nnz_long = 0;
+            st->nnz_short = 0;
+        }
+    }
+    for (int s = n + tid; s < S.npad; s += L1_T) {
+        S.q[s] = 0.0;
+        if (rebuild) {
+            S.perm[s] = -1;
+            S.csort[s] = 0;
+            S.lcnt[s] = 0;
+            S.scnt[s] = 0;
+        }
+    }
+    if (rebuild) {
+        const int nc = S.ncell;
+        for (int c = tid; c < nc; c += L1_T) cell[c] = 0;
+        __syncthreads();
+        for (int i = tid; i < n; i += L1_T) {
+            double f[3], w[3];
+            int cc[3];
+            frac_wrap(S, S.x[i], S.x[n + i], S.x[2 * n + i], f, w);
+            const int c = cell_index(S, f, cc);
+            at[i] = (uint16_t)c;
+            atomicAdd(&cell[c], 1);
+        }
+        __syncthreads();
+        // exclusive scan: each thread a run of cells
+        const int per = (nc + L1_T - 1) / L1_T, c0 = min(nc, tid * per), c1 = min(nc, c0 + per);
+        int sum = 0;
+        for (int c = c0; c < c1; c++) sum += cell[c];
+        int inc = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += t;
+        }
+        if (lane == 63) scan[wv] = inc;
+        __syncthreads();
+        int run = inc - sum;
+        for (int w = 0; w < wv; w++) run += scan[w];
+        for (int c = c0; c < c1; c++) {
+            const int v = cell[c];
+            S.cell_start[c] = run;
+            cell[c] = run;
+            run += v;
+        }
+        if (tid == 0) S.cell_start[nc] = n;
+        __syncthreads();
+        for (int i = tid; i < n; i += L1_T) tmp[atomicAdd(&cell[at[i]], 1)] = i;
+        __syncthreads();
+        // a cell's atoms in user order (cell[c] is now the cell's end)
+        for (int k = tid; k < n; k += L1_T) {
+            const int i = tmp[k], c = at[i], a = c > 0 ? cell[c - 1] : 0, b = cell[c];
+            int row = a;
+            for (int m = a; m < b; m++) row += (tmp[m] < i) ? 1 : 0;
+            const double x = S.x[i], y = S.x[n + i], z = S.x[2 * n + i];
+            double f[3], w[3];
+            frac_wrap(S, x, y, z, f, w);
+            S.perm[row] = i;
+            S.csort[row] = c;
+#pragma unroll
+            for (int d = 0; d < 3; d++) S.off[(size_t)d * S.npad + row] = cell_offset(S, w, c, d);
+            S.ref_x[i] = x;
+            S.ref_x[n + i] = y;
+            S.ref_x[2 * n + i] = z;
+        }
+        __syncthreads();
+    }
+    // local coordinates and starting charges; their sum tile by tile
+    double q0[PER];
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+        const int s = u * L1_T + tid;
+        q0[u] = 0.0;
+        if (s < n)
+            q0[u] = gather_row<R>(S, s, S.perm[s], S.off[s], S.off[S.npad + s], S.off[2 * S.npad + s], warm);
+        const double t = wave_sum(q0[u]);
+        if (lane == 0) part[u * (L1_T / 64) + wv] = t;
+    }
+    __syncthreads();
+    if (wv == 0) {
+        const double *p = part + 4 * lane;
+        const double t = lane < S.ntile ? ((p[0] + p[1]) + p[2]) + p[3] : 0.0;
+        const double total = wave_sum(t);
+        if (lane == 0) {
+            shift = (S.Q - total) / n;
+            st->qshift = shift;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+        const int s = u * L1_T + tid;
+        if (s < n) S.q[s] = q0[u] + shift;
+    }
 }
 
 // table of D(code) for the block's segment, in LDS
@@ -562,57 +716,11 @@ __global__ void __launch_bounds__(TILE) k_build(const Tile *tiles, Seg *segs, Pa
     if constexpr (HALO) write_halo(S, T, hbm, wsum);
 }
 
-// For every covalent entry (i -> j, d) the slot of (j -> i, -d) in row j:
-// 16 lanes per row, one entry each, every lane searching its partner's row.
-template <int ROWS>
-__global__ void __launch_bounds__(TILE) k_rev(const Tile *tiles, Seg *segs)
+// k_mark_built for a system built in FINE-row blocks: one block adds up their
+// rows' statistics.
+__device__ __forceinline__ void mark_built_fine(const Seg &S)
 {
-    constexpr int LR = 16;
-    const Tile T = my_rows<ROWS>(tiles);
-    const Seg &S = segs[T.seg];
-    if (!S.sst->rebuild) return;
-    const int lane = threadIdx.x % LR;
-    const int Ws = S.Ws;
-    const auto sidx = gbl(S.sidx);
-    const auto scnt = gbl(S.scnt);
-    bool bad = false;
-    for (int k = threadIdx.x / LR; k < ROWS; k += TILE / LR) {
-        const int s = T.row0 + k;
-        if (s >= S.n) break;                     // rows past n come last: the group is done
-        const int ns = scnt[s];
-        for (int e = lane; e < ns; e += LR) {
-            const uint32_t ent = sidx[(size_t)s * Ws + e];
-            const int j = (int)(ent & J_MASK), want = code_neg((int)(ent >> CODE_SHIFT));
-            const uint32_t target = (uint32_t)s | ((uint32_t)want << CODE_SHIFT);
-            const int nj = scnt[j];
-            int f = -1;
-            for (int m = 0; m < nj; m++)
-                if (sidx[(size_t)j * Ws + m] == target) { f = m; break; }
-            if (f < 0) { bad = true; f = 0; }
-            S.srev[(size_t)s * Ws + e] = (uint8_t)f;
-        }
-    }
-    if (bad) atomicOr(&S.sst->status, ST_REV);
-}
-
-__global__ void k_mark_built(const int *seg_ids, Seg *segs, int nseg)
-{
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nseg) return;
-    SegState *st = segs[seg_ids[k]].sst;
-    if (st->rebuild) {
-        st->built = 1;
-        st->nrebuild += 1;
-    }
-}
-
-// The same for systems built in FINE-row blocks: one block per segment adds
-// up their rows' statistics.
-__global__ void __launch_bounds__(TILE) k_mark_built_fine(const int *seg_ids, Seg *segs)
-{
-    const Seg &S = segs[seg_ids[blockIdx.x]];
     SegState *st = S.sst;
-    if (!st->rebuild) return;
     __shared__ int red[TILE / 64][5];
     const int *v = reinterpret_cast<const int *>(S.Fcov);
     // (a segment of FINE-row blocks has under 2^31 entries)
@@ -648,6 +756,53 @@ __global__ void __launch_bounds__(TILE) k_mark_built_fine(const int *seg_ids, Se
         st->maxs = r[2];
         st->nnz_long = (unsigned long long)r[3];
         st->nnz_short = (unsigned long long)r[4];
+        st->built = 1;
+        st->nrebuild += 1;
+    }
+}
+
+// For every covalent entry (i -> j, d) the slot of (j -> i, -d) in row j:
+// 16 lanes per row, one entry each, every lane searching its partner's row.
+template <int ROWS>
+__global__ void __launch_bounds__(TILE) k_rev(const Tile *tiles, Seg *segs)
+{
+    constexpr int LR = 16;
+    const Tile T = my_rows<ROWS>(tiles);
+    const Seg &S = segs[T.seg];
+    if (!S.sst->rebuild) return;
+    // (the lists' statistics are complete: the first block of a segment built
+    // in FINE-row blocks adds them up)
+    if (ROWS == FINE && T.row0 == 0) mark_built_fine(S);
+    const int lane = threadIdx.x % LR;
+    const int Ws = S.Ws;
+    const auto sidx = gbl(S.sidx);
+    const auto scnt = gbl(S.scnt);
+    bool bad = false;
+    for (int k = threadIdx.x / LR; k < ROWS; k += TILE / LR) {
+        const int s = T.row0 + k;
+        if (s >= S.n) break;                     // rows past n come last: the group is done
+        const int ns = scnt[s];
+        for (int e = lane; e < ns; e += LR) {
+            const uint32_t ent = sidx[(size_t)s * Ws + e];
+            const int j = (int)(ent & J_MASK), want = code_neg((int)(ent >> CODE_SHIFT));
+            const uint32_t target = (uint32_t)s | ((uint32_t)want << CODE_SHIFT);
+            const int nj = scnt[j];
+            int f = -1;
+            for (int m = 0; m < nj; m++)
+                if (sidx[(size_t)j * Ws + m] == target) { f = m; break; }
+            if (f < 0) { bad = true; f = 0; }
+            S.srev[(size_t)s * Ws + e] = (uint8_t)f;
+        }
+    }
+    if (bad) atomicOr(&S.sst->status, ST_REV);
+}
+
+__global__ void k_mark_built(const int *seg_ids, Seg *segs, int nseg)
+{
+    int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= nseg) return;
+    SegState *st = segs[seg_ids[k]].sst;
+    if (st->rebuild) {
         st->built = 1;
         st->nrebuild += 1;
     }

@@ -181,11 +181,27 @@ __global__ void __launch_bounds__(SV_T) k_solve_prep(const Tile *tiles, Seg *seg
     // Entries of the row's own block are added as 2^-40 fixed point: exact
     // in any order (an atom and several images of a neighbour in a small
     // cell), and finer than the FP32 inversion needs
-    for (int e = lane; e < cnt; e += LPR) {
-        const int j = (int)(ent[e] & J_MASK);
-        atomicOr(&bm[j >> 6], 1ull << (j & 63));
-        if ((j & ~(BK - 1)) == (row & ~(BK - 1)))
-            atomicAdd(&A64[rl * BK + (j & (BK - 1))], (unsigned long long)(long long)((double)val[e] * 1099511627776.0));
+    // (eight entries of a lane in flight)
+    constexpr int U = 8;
+    for (int e0 = lane; e0 < cnt; e0 += U * LPR) {
+        int j[U];
+        R v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int e = min(e0 + u * LPR, cnt - 1);
+            j[u] = (int)(ent[e] & J_MASK);
+            v[u] = val[e];
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            if (e0 + u * LPR >= cnt) continue;
+            // (most neighbours are marked already, and marks of one word wait for each other)
+            const unsigned long long bit = 1ull << (j[u] & 63);
+            if (!(bm[j[u] >> 6] & bit)) atomicOr(&bm[j[u] >> 6], bit);
+            if ((j[u] & ~(BK - 1)) == (row & ~(BK - 1)))
+                atomicAdd(&A64[rl * BK + (j[u] & (BK - 1))],
+                          (unsigned long long)(long long)((double)v[u] * 1099511627776.0));
+        }
     }
     __syncthreads();
     // positions: set bits before each word (threads 0 .. SV_WORDS-1, one word each)
@@ -234,9 +250,15 @@ __global__ void __launch_bounds__(SV_T) k_solve_prep(const Tile *tiles, Seg *seg
     }
     __syncthreads();
     const auto pos = gblw(S.hs16 + (size_t)row * Wl);
-    for (int e = lane; e < cnt; e += LPR) {
-        const int j = (int)(ent[e] & J_MASK);
-        pos[e] = (uint16_t)(pre[j >> 6] + __popcll(bm[j >> 6] & ((1ull << (j & 63)) - 1ull)));
+    for (int e0 = lane; e0 < cnt; e0 += U * LPR) {
+        int j[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) j[u] = (int)(ent[min(e0 + u * LPR, cnt - 1)] & J_MASK);
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (e0 + u * LPR < cnt)
+                pos[e0 + u * LPR] =
+                    (uint16_t)(pre[j[u] >> 6] + __popcll(bm[j[u] >> 6] & ((1ull << (j[u] & 63)) - 1ull)));
     }
     // Gauss-Jordan, in place: a row's lanes hold EPT of its columns
     const int b0 = rl & ~(BK - 1), i = rl & (BK - 1);

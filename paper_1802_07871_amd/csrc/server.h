@@ -340,7 +340,6 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         if (nto) {
             launch_build<R>(true, T, nto, S->dsegs, prm, st);
             launch_rev(true, T, nto, S->dsegs, st);
-            hipLaunchKernelGGL(k_mark_built_fine, dim3(nio), b, 0, st, sid, S->dsegs);
             launch_assemble<R>(true, T, nto, S->dsegs, ctx->pd, st);
         }
         if (nis_many) {

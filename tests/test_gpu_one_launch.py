@@ -4,7 +4,8 @@ neighbours (64 rows of 8 lanes), the change from 8 to 4 lanes per row (16,384
 atoms on 256 CUs), the last size that takes it and the first that takes the
 multi-launch solve, and rows longer than the entries a lane keeps in
 registers (192: dense carbon has ~340 neighbours inside the cutoff), with
-both numbers of lanes; and at 65,536 atoms, the last size whose row kernels
+both numbers of lanes; at 4,096 atoms, the last size whose sorted frame is made
+by one block; and at 65,536 atoms, the last size whose row kernels
 run in blocks of 16 rows.  Tolerances as in the other parity tests: mixed 1e-5
 relative RMS forces, 1e-6 eV/atom, 1e-6 e; FP64 1e-10 (charges solved to
 1e-13 there).
@@ -20,6 +21,7 @@ TOL = {"mixed": dict(F=1e-5, E=1e-6, q=1e-6), "fp64": dict(F=1e-10, E=1e-10, q=1
 
 # (atoms, periodic, carbon fraction, density g/cm^3)
 CASES = [(63, False, 0.7, 2.6), (64, False, 0.7, 2.6), (65, True, 0.7, 2.6), (257, True, 0.6, 3.0),
+         (4096, True, 0.7, 2.8), (4097, False, 0.7, 2.8),
          (900, True, 0.9, 3.2), (16384, True, 0.7, 2.8), (16385, False, 0.7, 2.8), (17000, True, 0.9, 3.2),
          (32512, True, 0.7, 2.4), (32513, True, 0.7, 2.4), (65536, True, 0.7, 2.8), (65537, True, 0.7, 2.8)]
 
