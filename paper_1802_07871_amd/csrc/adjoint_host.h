@@ -101,7 +101,7 @@ AdjLayout adj_layout(const Layout &L)
     A.off_slot = take(8 * A.slot_stride * (size_t)A.chunk);
     A.off_pk = take(sizeof(Params<Dual>) * (size_t)A.cap);
     A.off_kidx = take(sizeof(int) * (size_t)A.cap);
-    A.off_ppart = take(8 * (size_t)L.seg.ntile * (size_t)A.cap);
+    A.off_ppart = take(8 * (size_t)L.seg.ntile * (TILE / FINE) * (size_t)A.cap);
     A.off_scal = take(8 * 8);
     A.off_grad = take(8 * 64);
     A.off_seg = take(sizeof(Seg));
@@ -125,7 +125,7 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
     A.pk = (const Params<Dual> *)(adj + AL.off_pk);
     A.kidx = (const int *)(adj + AL.off_kidx);
     A.ppart = (double *)(adj + AL.off_ppart);
-    A.ptile = P.L.ntile;
+    A.ptile = P.L.ntile * (TILE / FINE);
     A.scal = (double *)(adj + AL.off_scal);
     A.grad = (double *)(adj + AL.off_grad);
     A.w = dLdE;
@@ -135,7 +135,7 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
     const int *sid = P.dsegid;
     hipLaunchKernelGGL(k_zero, g1, dim3(64), 0, st, A.grad, 64);
     hipLaunchKernelGGL(k_adj_seed, g, b, 0, st, P.dtiles, P.dseg, A, dLdF, dLdq);
-    hipLaunchKernelGGL((k_adj_source<R, LPR>), g, b, 0, st, P.dtiles, P.dseg, ctx->pd, A);
+    hipLaunchKernelGGL((k_adj_source<R, LPR>), dim3(P.L.ntile * (TILE / FINE)), b, 0, st, P.dtiles, P.dseg, ctx->pd, A);
     // adjoint view: the solver's charge array is lambda, total charge 0, and
     // its own solver state (the forward state and charges stay untouched)
     SegState *asst = (SegState *)(adj + AL.off_sst);
@@ -223,18 +223,19 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
         const int m = (int)std::min<size_t>(AL.chunk, cov.size() - c0);
         HIPCHK(hipMemcpyAsync(dpk, &hpk[c0], sizeof(Params<Dual>) * m, hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(dk, &hk[c0], sizeof(int) * m, hipMemcpyHostToDevice, st));
-        const dim3 gm(P.L.ntile, m);
-        hipLaunchKernelGGL(k_bond_dual, gm, b, 0, st, P.dtiles, P.dseg, A);
-        hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, P.L.ntile);
-        hipLaunchKernelGGL(k_force_cov_dual, gm, b, 0, st, P.dtiles, P.dseg, A);
-        hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, P.L.ntile);
+        const int nb = P.L.ntile * (TILE / DUAL_ROWS);
+        hipLaunchKernelGGL(k_bond_dual, dim3(nb, m), b, 0, st, P.dtiles, P.dseg, A);
+        hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, nb);
+        hipLaunchKernelGGL(k_force_cov_dual, dim3(nb, m, 2), b, 0, st, P.dtiles, P.dseg, A);
+        hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, 2 * nb);
     }
     {
         const int m = (int)coul.size();
         HIPCHK(hipMemcpyAsync(dpk, &hpk[cov.size()], sizeof(Params<Dual>) * m, hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(dk, &hk[cov.size()], sizeof(int) * m, hipMemcpyHostToDevice, st));
-        hipLaunchKernelGGL((k_coul_dual<R, LPR>), dim3(P.L.ntile, m), b, 0, st, P.dtiles, P.dseg, A);
-        hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, P.L.ntile);
+        const int nb = P.L.ntile * (TILE / FINE);
+        hipLaunchKernelGGL((k_coul_dual<R, LPR>), dim3(nb, m), b, 0, st, P.dtiles, P.dseg, A);
+        hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, nb);
     }
     HIPCHK(hipGetLastError());
     int status = 0;

@@ -37,7 +37,7 @@ struct AdjWs {
     double *slotd;            // dual bond coefficients (b, P1, P2 as value/derivative),
                               // [member][npad * Wb * 6]
     size_t slot_stride;       // doubles per member
-    double *ppart;            // per-member tile partial sums [member][ptile]
+    double *ppart;            // per-member block partial sums [member][ptile]
     int ptile;
 };
 
@@ -52,12 +52,12 @@ __device__ __forceinline__ const Params<Dual> &load_member_params(const AdjWs &A
     return *reinterpret_cast<const Params<Dual> *>(buf);
 }
 
-// Block sum of one value per thread into the member's partial for this tile
-__device__ __forceinline__ void member_partial(const AdjWs &A, int tile_local, double v, double *lds)
+// Block sum of one value per thread into the member's partial k
+__device__ __forceinline__ void member_partial(const AdjWs &A, int k, double v, double *lds)
 {
     double in[1] = {v}, out[1];
     block_sum<1>(in, lds, out);
-    if (threadIdx.x == 0) A.ppart[(size_t)blockIdx.y * A.ptile + tile_local] = out[0];
+    if (threadIdx.x == 0) A.ppart[(size_t)blockIdx.y * A.ptile + k] = out[0];
 }
 
 // seeds into the sorted frame; keep the forward charges' re-projection
@@ -81,11 +81,12 @@ __global__ void __launch_bounds__(TILE) k_adj_seed(const Tile *tiles, Seg *segs,
 }
 
 // a_s = u_s + sum_j q_j C'(r_sj) (v_s - v_j) . r_hat_sj   (self images: v_s - v_s = 0)
+// (FINE rows per block: the systems of a fit are small; 64 to 1,728 atoms 120 -> 14 us)
 template <typename R, int LPR>
 __global__ void __launch_bounds__(TILE) k_adj_source(const Tile *tiles, Seg *segs, Params<double> PD, AdjWs A)
 {
     using V4 = typename Vec4<R>::type;
-    const Tile T = my_tile(tiles);
+    const Tile T = my_rows<FINE>(tiles);
     const Seg &S = segs[T.seg];
     __shared__ V4 dtab[NCODE];
     load_dtab2<R>(S, dtab);
@@ -93,7 +94,7 @@ __global__ void __launch_bounds__(TILE) k_adj_source(const Tile *tiles, Seg *seg
     const double qsh = A.scal[0];
     constexpr int G = TILE / LPR;
     const int lane = threadIdx.x % LPR;
-    for (int k = threadIdx.x / LPR; k < TILE; k += G) {
+    for (int k = threadIdx.x / LPR; k < FINE; k += G) {
         const int s = T.row0 + k;
         if (s >= S.n) continue;
         const V4 li = xs[s];
@@ -153,18 +154,28 @@ __global__ void k_adj_keep_lam_shift(const int *seg_ids, Seg *segs, AdjWs A)
 // dual passes (a chunk of parameters per launch, one per blockIdx.y)
 // ---------------------------------------------------------------------------
 
-// Covalent bond pass in dual numbers: per-bond b, P1, P2 and the tile's
-// w dEcov/dtheta, for the chunk member blockIdx.y.
+// The covalent passes give a lane a bond: DUAL_L lanes per atom take its
+// bonds in turn (an atom per lane walked its bond pairs in dual FP64 numbers
+// one after another, in a handful of blocks for the systems of a fit).
+constexpr int DUAL_L = 4, DUAL_ROWS = TILE / DUAL_L;
+
+__device__ __forceinline__ R3<double> bond_vec64(const Seg &S, const double4 &a, const double4 &b, uint32_t ent)
+{
+    const R3<double> D = code_offset(S, (int)(ent >> CODE_SHIFT));
+    return {(b.x - a.x) + D.x, (b.y - a.y) + D.y, (b.z - a.z) + D.z};
+}
+
+// Covalent bond pass in dual numbers: per-bond b, P1, P2 and the block's
+// w dEcov/dtheta, for the chunk member blockIdx.y (64 to 1,728 atoms, 44
+// members: 111 -> 52 us).
 __global__ void __launch_bounds__(TILE) k_bond_dual(const Tile *tiles, Seg *segs, AdjWs A)
 {
-    const Tile T = my_tile(tiles);
+    const Tile T = my_rows<DUAL_ROWS>(tiles);
     const Seg &S = segs[T.seg];
-    __shared__ double4 dtab[NCODE];
     __shared__ double lds[4];
     __shared__ __align__(16) unsigned char pbuf[sizeof(Params<Dual>)];
     const Params<Dual> &P = load_member_params(A, pbuf);
-    load_dtab2<double>(S, dtab);
-    const int s = T.row0 + threadIdx.x;
+    const int s = T.row0 + threadIdx.x / DUAL_L;
     double ew = 0.0;
     if (s < S.n) {
         const double4 *xs = S.xs64;
@@ -173,12 +184,11 @@ __global__ void __launch_bounds__(TILE) k_bond_dual(const Tile *tiles, Seg *segs
         const double4 li = xs[s];
         const int ti = (int)li.w;
         const int ns = S.bcnt[s];
-        Dual ecov(0.0);
-        for (int e = 0; e < ns; e++) {
+        for (int e = threadIdx.x % DUAL_L; e < ns; e += DUAL_L) {
             const uint32_t ent = row[e];
             const double4 lj = xs[ent & J_MASK];
             const int pp = ti * 2 + (int)lj.w;
-            const R3<double> d = pair_vec<double>(li, lj, dtab[ent >> CODE_SHIFT]);
+            const R3<double> d = bond_vec64(S, li, lj, ent);
             const double r2 = d.x * d.x + d.y * d.y + d.z * d.z;
             Dual b(0.0), P1(0.0), P2(0.0);
             if (r2 < P.Sc[pp].v * P.Sc[pp].v) {
@@ -189,7 +199,7 @@ __global__ void __launch_bounds__(TILE) k_bond_dual(const Tile *tiles, Seg *segs
                     const uint32_t ent2 = row[e2];
                     const double4 lk = xs[ent2 & J_MASK];
                     const int pk = ti * 2 + (int)lk.w;
-                    const R3<double> dk = pair_vec<double>(li, lk, dtab[ent2 >> CODE_SHIFT]);
+                    const R3<double> dk = bond_vec64(S, li, lk, ent2);
                     const double rk2 = dk.x * dk.x + dk.y * dk.y + dk.z * dk.z;
                     if (rk2 >= P.Sc[pk].v * P.Sc[pk].v) continue;
                     const double rk = ::sqrt(rk2);
@@ -208,7 +218,8 @@ __global__ void __launch_bounds__(TILE) k_bond_dual(const Tile *tiles, Seg *segs
                 b = bond_order<Dual>(P, ti, z1, z2, db1, db2);
                 const Dual fc = cutoff<Dual>(Dual(r), P.Rc[pp], P.Sc[pp], P.piSR[pp], dfc);
                 const Dual fR = P.A[pp] * exp(-P.lam1[pp] * r), fA = P.B[pp] * exp(-P.lam2[pp] * r);
-                ecov += 0.5 * fc * (fR - b * fA);
+                const Dual en = 0.5 * fc * (fR - b * fA);
+                ew += en.d;
                 P1 = -0.5 * fc * fA * db1;
                 P2 = -0.5 * fc * fA * db2;
             }
@@ -219,25 +230,26 @@ __global__ void __launch_bounds__(TILE) k_bond_dual(const Tile *tiles, Seg *segs
             slot[6 * e + 4] = P2.v;
             slot[6 * e + 5] = P2.d;
         }
-        ew = A.w * ecov.d;
+        ew *= A.w;
     }
-    member_partial(A, T.row0 / TILE, ew, lds);
+    member_partial(A, T.row0 / DUAL_ROWS, ew, lds);
 }
 
 __device__ __forceinline__ Dual slotd_get(const double *p) { return Dual(p[0], p[1]); }
 
-// Covalent force gather in dual numbers; the tile's sum of v_m . dF_m/dtheta.
+// Covalent force gather in dual numbers; the block's sum of v_m . dF_m/dtheta
+// over its atoms' bonds: with the atom as their centre (blockIdx.z = 0), or
+// as the partner and environment of its neighbours' bonds (1).  64 to 1,728
+// atoms, 44 members: 249 -> 94 us.
 __global__ void __launch_bounds__(TILE) k_force_cov_dual(const Tile *tiles, Seg *segs, AdjWs A)
 {
-    const Tile T = my_tile(tiles);
+    const Tile T = my_rows<DUAL_ROWS>(tiles);
     const Seg &S = segs[T.seg];
-    __shared__ double4 dtab[NCODE];
     __shared__ double lds[4];
     __shared__ __align__(16) unsigned char pbuf[sizeof(Params<Dual>)];
     const Params<Dual> &P = load_member_params(A, pbuf);
-    load_dtab2<double>(S, dtab);
     const double *slotd = A.slotd + blockIdx.y * A.slot_stride;
-    const int m = T.row0 + threadIdx.x;
+    const int m = T.row0 + threadIdx.x / DUAL_L;
     double vf = 0.0;
     if (m < S.n) {
         const double4 *xs = S.xs64;
@@ -245,86 +257,88 @@ __global__ void __launch_bounds__(TILE) k_force_cov_dual(const Tile *tiles, Seg 
         const int tm = (int)lm.w;
         const int ns = S.bcnt[m];
         const SRow<const uint32_t> row = srow<const uint32_t>(S.bidx, m, S.Wb);
-        Dual fx(0.0), fy(0.0), fz(0.0);
-        for (int e = 0; e < ns; e++) {
-            const uint32_t ent = row[e];
-            const double4 lj = xs[ent & J_MASK];
-            const int pp = tm * 2 + (int)lj.w;
-            const R3<double> d = pair_vec<double>(lm, lj, dtab[ent >> CODE_SHIFT]);
-            const double r2 = d.x * d.x + d.y * d.y + d.z * d.z;
-            if (r2 >= P.Sc[pp].v * P.Sc[pp].v) continue;
-            const double r = ::sqrt(r2), ir = 1.0 / r;
-            const double *sv = slotd + ((size_t)m * S.Wb + e) * 6;
-            const Dual b = slotd_get(sv), P1 = slotd_get(sv + 2), P2 = slotd_get(sv + 4);
-            const Dual dv = pair_dvdr<Dual>(P, pp, Dual(r), b) * ir;
-            Dual ax = dv * d.x, ay = dv * d.y, az = dv * d.z;
-            for (int e2 = 0; e2 < ns; e2++) {
-                if (e2 == e) continue;
-                const uint32_t ent2 = row[e2];
-                const double4 lk = xs[ent2 & J_MASK];
-                const int pk = tm * 2 + (int)lk.w;
-                const R3<double> dk = pair_vec<double>(lm, lk, dtab[ent2 >> CODE_SHIFT]);
-                const double rk2 = dk.x * dk.x + dk.y * dk.y + dk.z * dk.z;
-                if (rk2 >= P.Sc[pk].v * P.Sc[pk].v) continue;
-                R3<Dual> gj[2], gk[2];
-                const R3<Dual> dd = {Dual(d.x), Dual(d.y), Dual(d.z)}, ddk = {Dual(dk.x), Dual(dk.y), Dual(dk.z)};
-                trip_grad<Dual>(P, tm, pk, dd, Dual(r), ddk, Dual(::sqrt(rk2)), gj, gk);
-                ax += P1 * (gj[0].x + gk[0].x) + P2 * (gj[1].x + gk[1].x);
-                ay += P1 * (gj[0].y + gk[0].y) + P2 * (gj[1].y + gk[1].y);
-                az += P1 * (gj[0].z + gk[0].z) + P2 * (gj[1].z + gk[1].z);
+        double fx = 0.0, fy = 0.0, fz = 0.0;
+        if (blockIdx.z == 0)
+            for (int e = threadIdx.x % DUAL_L; e < ns; e += DUAL_L) {
+                const uint32_t ent = row[e];
+                const double4 lj = xs[ent & J_MASK];
+                const int pp = tm * 2 + (int)lj.w;
+                const R3<double> d = bond_vec64(S, lm, lj, ent);
+                const double r2 = d.x * d.x + d.y * d.y + d.z * d.z;
+                if (r2 >= P.Sc[pp].v * P.Sc[pp].v) continue;
+                const double r = ::sqrt(r2), ir = 1.0 / r;
+                const double *sv = slotd + ((size_t)m * S.Wb + e) * 6;
+                const Dual b = slotd_get(sv), P1 = slotd_get(sv + 2), P2 = slotd_get(sv + 4);
+                const Dual dv = pair_dvdr<Dual>(P, pp, Dual(r), b) * ir;
+                Dual ax = dv * d.x, ay = dv * d.y, az = dv * d.z;
+                for (int e2 = 0; e2 < ns; e2++) {
+                    if (e2 == e) continue;
+                    const uint32_t ent2 = row[e2];
+                    const double4 lk = xs[ent2 & J_MASK];
+                    const int pk = tm * 2 + (int)lk.w;
+                    const R3<double> dk = bond_vec64(S, lm, lk, ent2);
+                    const double rk2 = dk.x * dk.x + dk.y * dk.y + dk.z * dk.z;
+                    if (rk2 >= P.Sc[pk].v * P.Sc[pk].v) continue;
+                    R3<Dual> gj[2], gk[2];
+                    const R3<Dual> dd = {Dual(d.x), Dual(d.y), Dual(d.z)}, ddk = {Dual(dk.x), Dual(dk.y), Dual(dk.z)};
+                    trip_grad<Dual>(P, tm, pk, dd, Dual(r), ddk, Dual(::sqrt(rk2)), gj, gk);
+                    ax += P1 * (gj[0].x + gk[0].x) + P2 * (gj[1].x + gk[1].x);
+                    ay += P1 * (gj[0].y + gk[0].y) + P2 * (gj[1].y + gk[1].y);
+                    az += P1 * (gj[0].z + gk[0].z) + P2 * (gj[1].z + gk[1].z);
+                }
+                fx += ax.d;
+                fy += ay.d;
+                fz += az.d;
             }
-            fx += ax;
-            fy += ay;
-            fz += az;
-        }
-        for (int e = 0; e < ns; e++) {
-            const uint32_t ent = row[e];
-            const int i = (int)(ent & J_MASK);
-            const double4 li = xs[i];
-            const int ti = (int)li.w, pp = ti * 2 + tm;
-            const R3<double> dmi = pair_vec<double>(lm, li, dtab[ent >> CODE_SHIFT]);
-            const double r2 = dmi.x * dmi.x + dmi.y * dmi.y + dmi.z * dmi.z;
-            if (r2 >= P.Sc[pp].v * P.Sc[pp].v) continue;
-            const double r = ::sqrt(r2), ir = 1.0 / r;
-            const R3<double> d = {-dmi.x, -dmi.y, -dmi.z};
-            const int srev = reverse_bond(S, m, e, i);
-            if (srev >= S.bcnt[i]) continue;                 // (a reverse always exists)
-            const double *sv = slotd + ((size_t)i * S.Wb + srev) * 6;
-            const Dual b = slotd_get(sv), P1 = slotd_get(sv + 2), P2 = slotd_get(sv + 4);
-            const Dual dv = pair_dvdr<Dual>(P, pp, Dual(r), b) * ir;
-            Dual ax = -dv * d.x, ay = -dv * d.y, az = -dv * d.z;
-            const int ni = S.bcnt[i];
-            const SRow<const uint32_t> rowi = srow<const uint32_t>(S.bidx, i, S.Wb);
-            const R3<Dual> dd = {Dual(d.x), Dual(d.y), Dual(d.z)};
-            for (int t = 0; t < ni; t++) {
-                if (t == srev) continue;
-                const uint32_t ent2 = rowi[t];
-                const double4 lk = xs[ent2 & J_MASK];
-                const int pk = ti * 2 + (int)lk.w;
-                const R3<double> dk = pair_vec<double>(li, lk, dtab[ent2 >> CODE_SHIFT]);
-                const double rk2 = dk.x * dk.x + dk.y * dk.y + dk.z * dk.z;
-                if (rk2 >= P.Sc[pk].v * P.Sc[pk].v) continue;
-                const double rk = ::sqrt(rk2);
-                const R3<Dual> ddk = {Dual(dk.x), Dual(dk.y), Dual(dk.z)};
-                R3<Dual> gj[2], gk[2];
-                trip_grad<Dual>(P, ti, pk, dd, Dual(r), ddk, Dual(rk), gj, gk);
-                ax -= P1 * gj[0].x + P2 * gj[1].x;
-                ay -= P1 * gj[0].y + P2 * gj[1].y;
-                az -= P1 * gj[0].z + P2 * gj[1].z;
-                const double *sk = slotd + ((size_t)i * S.Wb + t) * 6;
-                const Dual K1 = slotd_get(sk + 2), K2 = slotd_get(sk + 4);
-                trip_grad<Dual>(P, ti, pp, ddk, Dual(rk), dd, Dual(r), gj, gk);
-                ax -= K1 * gk[0].x + K2 * gk[1].x;
-                ay -= K1 * gk[0].y + K2 * gk[1].y;
-                az -= K1 * gk[0].z + K2 * gk[1].z;
+        else
+            for (int e = threadIdx.x % DUAL_L; e < ns; e += DUAL_L) {
+                const uint32_t ent = row[e];
+                const int i = (int)(ent & J_MASK);
+                const double4 li = xs[i];
+                const int ti = (int)li.w, pp = ti * 2 + tm;
+                const R3<double> dmi = bond_vec64(S, lm, li, ent);
+                const double r2 = dmi.x * dmi.x + dmi.y * dmi.y + dmi.z * dmi.z;
+                if (r2 >= P.Sc[pp].v * P.Sc[pp].v) continue;
+                const double r = ::sqrt(r2), ir = 1.0 / r;
+                const R3<double> d = {-dmi.x, -dmi.y, -dmi.z};
+                const int srev = reverse_bond(S, m, e, i);
+                if (srev >= S.bcnt[i]) continue;                 // (a reverse always exists)
+                const double *sv = slotd + ((size_t)i * S.Wb + srev) * 6;
+                const Dual b = slotd_get(sv), P1 = slotd_get(sv + 2), P2 = slotd_get(sv + 4);
+                const Dual dv = pair_dvdr<Dual>(P, pp, Dual(r), b) * ir;
+                Dual ax = -dv * d.x, ay = -dv * d.y, az = -dv * d.z;
+                const int ni = S.bcnt[i];
+                const SRow<const uint32_t> rowi = srow<const uint32_t>(S.bidx, i, S.Wb);
+                const R3<Dual> dd = {Dual(d.x), Dual(d.y), Dual(d.z)};
+                for (int t = 0; t < ni; t++) {
+                    if (t == srev) continue;
+                    const uint32_t ent2 = rowi[t];
+                    const double4 lk = xs[ent2 & J_MASK];
+                    const int pk = ti * 2 + (int)lk.w;
+                    const R3<double> dk = bond_vec64(S, li, lk, ent2);
+                    const double rk2 = dk.x * dk.x + dk.y * dk.y + dk.z * dk.z;
+                    if (rk2 >= P.Sc[pk].v * P.Sc[pk].v) continue;
+                    const double rk = ::sqrt(rk2);
+                    const R3<Dual> ddk = {Dual(dk.x), Dual(dk.y), Dual(dk.z)};
+                    R3<Dual> gj[2], gk[2];
+                    trip_grad<Dual>(P, ti, pk, dd, Dual(r), ddk, Dual(rk), gj, gk);
+                    ax -= P1 * gj[0].x + P2 * gj[1].x;
+                    ay -= P1 * gj[0].y + P2 * gj[1].y;
+                    az -= P1 * gj[0].z + P2 * gj[1].z;
+                    const double *sk = slotd + ((size_t)i * S.Wb + t) * 6;
+                    const Dual K1 = slotd_get(sk + 2), K2 = slotd_get(sk + 4);
+                    trip_grad<Dual>(P, ti, pp, ddk, Dual(rk), dd, Dual(r), gj, gk);
+                    ax -= K1 * gk[0].x + K2 * gk[1].x;
+                    ay -= K1 * gk[0].y + K2 * gk[1].y;
+                    az -= K1 * gk[0].z + K2 * gk[1].z;
+                }
+                fx += ax.d;
+                fy += ay.d;
+                fz += az.d;
             }
-            fx += ax;
-            fy += ay;
-            fz += az;
-        }
-        vf = A.v[m] * fx.d + A.v[S.npad + m] * fy.d + A.v[2 * S.npad + m] * fz.d;
+        vf = A.v[m] * fx + A.v[S.npad + m] * fy + A.v[2 * S.npad + m] * fz;
     }
-    member_partial(A, T.row0 / TILE, vf, lds);
+    member_partial(A, blockIdx.z * gridDim.x + T.row0 / DUAL_ROWS, vf, lds);
 }
 
 // Coulomb kernel in dual numbers (parameters gamma, ke, rc may carry the
@@ -343,11 +357,12 @@ __device__ __forceinline__ Dual coul_dual(const Params<Dual> &P, int pp, double 
 }
 
 // Per row: w/2 q_s q_j dC/dtheta + q_s q_j d(C')/dtheta (v_s . r_hat) - lambda_s q_j dC/dtheta
+// (FINE rows per block; 64 to 1,728 atoms, 4 members: 182 -> 18 us)
 template <typename R, int LPR>
 __global__ void __launch_bounds__(TILE) k_coul_dual(const Tile *tiles, Seg *segs, AdjWs A)
 {
     using V4 = typename Vec4<R>::type;
-    const Tile T = my_tile(tiles);
+    const Tile T = my_rows<FINE>(tiles);
     const Seg &S = segs[T.seg];
     __shared__ V4 dtab[NCODE];
     __shared__ double lds[4];
@@ -359,7 +374,7 @@ __global__ void __launch_bounds__(TILE) k_coul_dual(const Tile *tiles, Seg *segs
     constexpr int G = TILE / LPR;
     const int lane = threadIdx.x % LPR;
     double tot = 0.0;
-    for (int k = threadIdx.x / LPR; k < TILE; k += G) {
+    for (int k = threadIdx.x / LPR; k < FINE; k += G) {
         const int s = T.row0 + k;
         if (s >= S.n) continue;
         const V4 li = xs[s];
@@ -385,7 +400,7 @@ __global__ void __launch_bounds__(TILE) k_coul_dual(const Tile *tiles, Seg *segs
         acc = group_sum<LPR>(acc);
         if (lane == 0) tot += acc;
     }
-    member_partial(A, T.row0 / TILE, tot, lds);
+    member_partial(A, T.row0 / FINE, tot, lds);
 }
 
 // Closed-form self-energy and diagonal terms, per species t:
@@ -423,14 +438,14 @@ __global__ void k_fin_grad(const int *seg_ids, Seg *segs, AdjWs A, int i0, int i
     }
 }
 
-// Add each chunk member's total (its ptile partials, summed in a fixed order)
+// Add each chunk member's total (its count partials, summed in a fixed order)
 // to grad[kidx[member]]; one block per member.
-__global__ void k_fin_grad_members(AdjWs A, int ntile)
+__global__ void k_fin_grad_members(AdjWs A, int count)
 {
     __shared__ double lds[4];
     double v[1] = {0.0}, tot[1];
     const double *pp = A.ppart + (size_t)blockIdx.x * A.ptile;
-    for (int t = threadIdx.x; t < ntile; t += blockDim.x) v[0] += pp[t];
+    for (int t = threadIdx.x; t < count; t += blockDim.x) v[0] += pp[t];
     block_sum<1>(v, lds, tot);
     if (threadIdx.x == 0) A.grad[A.kidx[blockIdx.x]] += tot[0];
 }
