@@ -4,9 +4,9 @@
 
 namespace {
 
-// workspace: counters, histogram, then the per-row C adjacency
+// workspace: counters, histogram, then the atoms' records and bond marks
 struct RingLayout {
-    size_t off_cnt, off_hist, off_adj, off_deg, off_mark, bytes;
+    size_t off_cnt, off_hist, off_rec, off_mark, bytes;
 };
 
 RingLayout ring_layout(int npad, int nbins)
@@ -20,9 +20,8 @@ RingLayout ring_layout(int npad, int nbins)
     };
     R.off_cnt = take(sizeof(unsigned long long) * RC_N);
     R.off_hist = take(sizeof(unsigned long long) * (size_t)nbins);
-    R.off_adj = take(sizeof(uint32_t) * RING_DEG * (size_t)npad);
-    R.off_deg = take(sizeof(int) * (size_t)npad);
-    R.off_mark = take(sizeof(uint32_t) * RING_DEG * (size_t)npad);
+    R.off_rec = take(sizeof(uint32_t) * REC * (size_t)npad);
+    R.off_mark = take(sizeof(uint32_t) * (size_t)npad);
     R.bytes = o;
     return R;
 }
@@ -114,19 +113,18 @@ int ctbop_rings(ctbop_ctx *ctx, int n, const double *x, const int32_t *types, co
     lists_any(ctx, P, 0);
     char *w = (char *)ws;
     RingWs W;
-    W.adj = (uint32_t *)(w + RL.off_adj);
-    W.deg = (int *)(w + RL.off_deg);
+    W.rec = (uint32_t *)(w + RL.off_rec);
     W.mark = (uint32_t *)(w + RL.off_mark);
     W.cnt = (unsigned long long *)(w + RL.off_cnt);
     W.hist = (unsigned long long *)(w + RL.off_hist);
     W.list = ring_cap > 0 ? ring_list : nullptr;
     W.orient = ring_cap > 0 ? ring_orient : nullptr;
     W.cap = ring_cap;
-    HIPCHK(hipMemsetAsync(w, 0, RL.off_adj, P.st));
+    HIPCHK(hipMemsetAsync(w, 0, RL.off_rec, P.st));
     const dim3 g(P.L.ntile), b(TILE);
     {
         Timed t(ctx, 9, P.st);
-        hipLaunchKernelGGL(k_ring_adj, g, b, 0, P.st, P.dtiles, P.dseg, W, c);
+        hipLaunchKernelGGL(k_ring_adj, dim3(P.L.ntile * (TILE / ADJ_ROWS)), b, 0, P.st, P.dtiles, P.dseg, W, c);
     }
     {
         Timed t(ctx, 10, P.st);

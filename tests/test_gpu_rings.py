@@ -130,3 +130,18 @@ def test_errors(ct, pot, theta):
     with pytest.raises(ct.CtbopError) as e:
         pot.rings(pos, np.ones(15, dtype=np.int32), np.eye(3) * 30.0, [False] * 3)
     assert e.value.code == ct.E_NEIGH_OVERFLOW
+
+
+@pytest.mark.parametrize("n,density,dmin", [(512, 4.2, 1.3), (520, 5.0, 1.35)])
+def test_dense_network(pot, n, density, dmin):
+    """More neighbour pairs than a block takes at once, and more cycles than
+    wait in its buffer (a mean of 6 and 7.6 neighbours, up to 12)."""
+    s = G.random_system(n, 1.0, density, True, seed=77, dmin=dmin)
+    ref = R.ring_statistics(s.pos, s.types, s.box, s.pbc, max_size=6)
+    print(f"[rings] dense network n={n} counts {ref['counts'][3:].tolist()}", flush=True)
+    for cap in (0, 20000):
+        got = pot.rings(s.pos, s.types, s.box, s.pbc, max_size=6, list_cap=cap)
+        assert np.array_equal(got["counts"], ref["counts"]) and got["n_rings"] == len(ref["rings"])
+        assert got["bonds"] == ref["bonds"] and got["chain_bonds"] == ref["chain_bonds"]
+        assert np.array_equal(got["hist"], ref["hist"])
+    assert sorted(got["rings"]) == ref["rings"]
