@@ -133,10 +133,11 @@ def test_errors(ct, pot, theta):
 
 
 @pytest.mark.parametrize("n,density,dmin", [(512, 4.2, 1.3), (520, 5.0, 1.35)])
-def test_dense_network(pot, n, density, dmin):
+def test_dense_network(ct, theta, n, density, dmin):
     """More neighbour pairs than a block takes at once, and more cycles than
     wait in its buffer (a mean of 6 and 7.6 neighbours, up to 12)."""
     s = G.random_system(n, 1.0, density, True, seed=77, dmin=dmin)
+    pot = ct.Potential(theta, long_cap=1024)         # (~600 atoms within the Coulomb list's radius)
     ref = R.ring_statistics(s.pos, s.types, s.box, s.pbc, max_size=6)
     print(f"[rings] dense network n={n} counts {ref['counts'][3:].tolist()}", flush=True)
     for cap in (0, 20000):
