@@ -583,10 +583,10 @@ def main():
     ms, cnt = prof["spmv"]
     iters = int(info["cg_iters_total"]) - int(info_w["cg_iters_total"])
     avg_s = ms / 1e3 / max(iters, 1)
-    # entry: FP32 value + 16-bit halo position or offset (32-bit index in wide
-    # slices); row: count, y_i, J_i, the result (H y)_i, and m1_i, r_i, s_i for
-    # the single-reduction solve's sums
-    spmv_bytes = 6.0 * nnz + 2.0 * nnz_wide + 52.0 * n
+    # entry: FP32 value + 12-bit halo position (16-bit offset in slices whose halo does not fit,
+    # 32-bit index in wide slices); 52 bytes per row
+    nnz_halo = int(info["nnz_coul_halo"])
+    spmv_bytes = 4.0 * nnz + 1.5 * nnz_halo + 4.0 * nnz_wide + 2.0 * (nnz - nnz_halo - nnz_wide) + 52.0 * n
     achieved = spmv_bytes / avg_s / 1e9
     fms, fcnt = prof["force_coul"]
     f_avg = fms / 1e3 / max(fcnt, 1)

@@ -34,7 +34,9 @@ constexpr int HALO_WORDS = HALO_WIN / 64;
 #endif
 constexpr int HALO_MAX = CTBOP_HALO_MAX; // staged rows per tile in the charge-solve product (LDS doubles)
 // forms of a slice of the solver's sliced copy (swide)
-constexpr uint8_t SL_HALO = 0, SL_FULL = 1, SL_OFF16 = 2;
+constexpr uint8_t SL_HALO = 0, SL_FULL = 1, SL_OFF16 = 2, SL_HALO16 = 3;
+constexpr int GRP = 8;                 // entries per group of a 12-bit halo slice
+static_assert(HALO_MAX <= 4096, "halo positions of a group are 12 bits each");
 
 // status bits (mapped to CTBOP_E_* codes on the host)
 constexpr int ST_TOO_CLOSE = 1, ST_NOCONV = 2, ST_NOT_PD = 4, ST_OVERFLOW = 8, ST_REV = 16;
@@ -163,10 +165,12 @@ struct Seg {
     // them.  The charge-solve product stages p of the halo in LDS once per
     // tile, so that each entry gathers from LDS.  In the sliced copy the
     // neighbours of a slice's entries are stored in one of three forms
-    // (swide): their 16-bit positions in the tile's halo (hs16, SL_HALO)
-    // when the halo holds at most HALO_MAX rows, else 16-bit offsets from
-    // the slice's first slot (hs16, offset + 32768, SL_OFF16), and the full
-    // entries (hsidx, SL_FULL) when a row of the slice has an entry beyond a
+    // (swide): their positions in the tile's halo when it holds at most
+    // HALO_MAX rows, 12 bits each in groups of GRP entries (SL_HALO; the
+    // layout is at hs_group), or 16 bits each where the longest row would not
+    // fit its stride rounded up to a group (SL_HALO16); else 16-bit offsets
+    // from the slice's first slot (hs16, offset + 32768, SL_OFF16); and the
+    // full entries (hsidx, SL_FULL) when a row of the slice has an entry beyond a
     // 16-bit offset from some slice of its tile (hwide flags those rows;
     // the entries of the other rows lie in the halo window).  Within each
     // tile the rows take the slice slots in order of decreasing length (ties
@@ -273,6 +277,22 @@ __device__ __forceinline__ size_t slice_base(int s, int W)
 
 // Entry e of row s in a sliced array of row width W
 __device__ __forceinline__ size_t sliced(int s, int e, int W) { return slice_base(s, W) + (size_t)e * SLICE; }
+
+// Group g of slot s of a 12-bit halo slice (SL_HALO), in the slice's own
+// stretch of hs16 and H: a lane's 96 bits of positions are three 32-bit words
+// at hs_group, and its values go in planes of 16 bytes per lane (plane k of
+// the GRP * sizeof(R) / 16 of a group at hs_plane), so that a wave loads a
+// group of its 64 slots with one 12-byte and GRP * sizeof(R) / 16 16-byte
+// loads per lane, each one contiguous segment.
+__device__ __forceinline__ size_t hs_group(int s, int g, int W)    // in 16-bit units
+{
+    return (size_t)(s & ~(SLICE - 1)) * (size_t)W + ((size_t)g * SLICE + (size_t)(s & (SLICE - 1))) * (GRP * 12 / 16);
+}
+template <typename R> __device__ __forceinline__ size_t hs_plane(int s, int g, int k, int W)   // in R
+{
+    constexpr int V = 16 / sizeof(R), NP = GRP / V;
+    return (size_t)(s & ~(SLICE - 1)) * (size_t)W + (((size_t)g * NP + k) * SLICE + (size_t)(s & (SLICE - 1))) * V;
+}
 
 // A row of a sliced array, indexed by entry
 template <typename T> struct SRow {

@@ -317,7 +317,8 @@ __global__ void __launch_bounds__(TILE) k_hslice(const Tile *tiles, Seg *segs)
     const int rk = slot_row[tid];
     const int rrow = T.row0 + rk;
     S.hperm[own] = (uint8_t)rk;
-    const uint8_t smode = __ballot(wide_row[rk] != 0) != 0ull ? SL_FULL : (hfit ? SL_HALO : SL_OFF16);
+    const uint8_t smode = __ballot(wide_row[rk] != 0) != 0ull ? SL_FULL : !hfit ? SL_OFF16
+                          : slot_cnt[tid & ~(SLICE - 1)] <= (S.Wl & ~(GRP - 1)) ? SL_HALO : SL_HALO16;
     if ((tid & (SLICE - 1)) == 0) {
         S.swide[own / SLICE] = smode;
         sw[tid / SLICE] = smode;
@@ -375,16 +376,50 @@ __global__ void __launch_bounds__(TILE) k_hslice(const Tile *tiles, Seg *segs)
                 }
             }
             __syncthreads();
+            // an entry's place in the halo
+            auto place = [&](uint32_t ent) {
+                const int hw = (int)(ent & J_MASK) - T.row0 + HALO_WIN / 2;
+                const unsigned long long below = (1ull << (hw & 63)) - 1ull;
+                return (unsigned)(hpre[hw >> 6] + __popcll(hbm[hw >> 6] & below));
+            };
+            if (mode == SL_HALO) {
+                // wave w takes entries 4w .. 4w+3 of the chunk, half a group
+                // (past the row's end, up to a whole group, zeros)
+                static_assert(HS_CH == 16 && GRP == 8, "four waves, half a group each");
+                const int e = E0 + 4 * wq, g = e / GRP, h = (e / 4) & 1;
+                if (g * GRP < wcnt) {
+                    typedef R rv4 __attribute__((ext_vector_type(4)));
+                    rv4 v;
+                    unsigned long long w = 0ull;
+#pragma unroll
+                    for (int k = 0; k < 4; k++) {
+                        const bool in = e + k < wcnt;
+                        v[k] = in ? cv[wl][4 * wq + k] : (R)0;
+                        w |= (unsigned long long)(in ? place(ci[wl][4 * wq + k]) : 0u) << (12 * k);
+                    }
+                    const size_t at = hs_group(sbase + wl, g, S.Wl) + 3 * h;
+#pragma unroll
+                    for (int k = 0; k < 3; k++) hs16[at + k] = (uint16_t)(w >> (16 * k));
+                    constexpr int V = 16 / sizeof(R);
+                    typedef R rv __attribute__((ext_vector_type(V)));
+#pragma unroll
+                    for (int k = 0; k < 4 / V; k++) {
+                        rv o;
+#pragma unroll
+                        for (int t = 0; t < V; t++) o[t] = v[k * V + t];
+                        *(__attribute__((address_space(1))) rv *)(H + hs_plane<R>(sbase + wl, g, h * (4 / V) + k,
+                                                                                 S.Wl)) = o;
+                    }
+                }
+            } else
 #pragma unroll
             for (int k = 0; k < HS_CH / 4; k++) {
                 const int c = wq + 4 * k;
                 const int e = E0 + c;
                 if (e < wcnt) {
                     const uint32_t ent = ci[wl][c];
-                    if (mode == SL_HALO) {
-                        const int hw = (int)(ent & J_MASK) - T.row0 + HALO_WIN / 2;
-                        const unsigned long long below = (1ull << (hw & 63)) - 1ull;
-                        hs16[b0 + (size_t)e * SLICE] = (uint16_t)(hpre[hw >> 6] + __popcll(hbm[hw >> 6] & below));
+                    if (mode == SL_HALO16) {
+                        hs16[b0 + (size_t)e * SLICE] = (uint16_t)place(ent);
                     } else if (mode == SL_OFF16) {
                         hs16[b0 + (size_t)e * SLICE] = (uint16_t)((int)(ent & J_MASK) - sbase + 32768);
                     } else {
@@ -447,7 +482,7 @@ __global__ void __launch_bounds__(TILE) k_hslice(const Tile *tiles, Seg *segs)
         v[1] = (double)own_cnt;
         v[2] = sw[rank / SLICE] == SL_FULL ? (double)own_cnt : 0.0;
         v[4] = m1;
-        v[5] = sw[rank / SLICE] == SL_HALO ? (double)own_cnt : 0.0;
+        v[5] = sw[rank / SLICE] == SL_HALO || sw[rank / SLICE] == SL_HALO16 ? (double)own_cnt : 0.0;
     } else if (own < S.npad) {
         S.m1[own] = 0.0;
     }
@@ -615,6 +650,53 @@ __device__ __forceinline__ double spmv_row(const double *p_, const IDX *row_, co
     return a;
 }
 
+// A slot of a 12-bit halo slice: 8 entries per group, 5.5 bytes each (FP32),
+// three loads per group and the next group's in flight meanwhile.  Bound by
+// HBM: 1,008,640 atoms 202 us with 16-bit positions and sixteen loads per 8
+// entries, 192 now (beside the covalent kernels in part).
+template <typename R>
+__device__ __forceinline__ double spmv_row_group(const double *hp, const uint16_t *hs16, const R *H, int slot, int cnt,
+                                                 int W)
+{
+    constexpr int V = 16 / sizeof(R), NP = GRP / V;
+    typedef R rv __attribute__((ext_vector_type(V)));
+    const auto pos = gbl(reinterpret_cast<const unsigned *>(hs16 + hs_group(slot, 0, W)));
+    const auto val = (const __attribute__((address_space(1))) rv *)gbl(H + hs_plane<R>(slot, 0, 0, W));
+    const int ng = (cnt + GRP - 1) / GRP;
+    double acc[GRP];
+#pragma unroll
+    for (int u = 0; u < GRP; u++) acc[u] = 0.0;
+    unsigned w[2][3];
+    rv v[2][NP];
+    auto load = [&](int b, int g) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) w[b][k] = __builtin_nontemporal_load(pos + (size_t)g * (SLICE * 3) + k);
+#pragma unroll
+        for (int k = 0; k < NP; k++) v[b][k] = __builtin_nontemporal_load(val + ((size_t)g * NP + k) * SLICE);
+    };
+    auto use = [&](int b) {
+        const unsigned long long lo = ((unsigned long long)w[b][1] << 32) | w[b][0],
+                                 hi = ((unsigned long long)w[b][2] << 32) | w[b][1];
+        const unsigned p[GRP] = {(unsigned)lo & 4095u,         (unsigned)(lo >> 12) & 4095u,
+                                 (unsigned)(lo >> 24) & 4095u, (unsigned)(lo >> 36) & 4095u,
+                                 (unsigned)(hi >> 16) & 4095u, (unsigned)(hi >> 28) & 4095u,
+                                 (unsigned)(hi >> 40) & 4095u, (unsigned)(hi >> 52) & 4095u};
+#pragma unroll
+        for (int u = 0; u < GRP; u++) acc[u] += (double)v[b][u / V][u % V] * hp[p[u]];
+    };
+    if (ng > 0) load(0, 0);
+    for (int g = 0; g < ng; g += 2) {
+        if (g + 1 < ng) load(1, g + 1);
+        use(0);
+        if (g + 2 < ng) load(0, g + 2);
+        if (g + 1 < ng) use(1);
+    }
+    double a = 0.0;
+#pragma unroll
+    for (int u = 0; u < GRP; u++) a += acc[u];
+    return a;
+}
+
 // The same with p of the tile's halo staged in LDS (hp) and the row's
 // entries as 16-bit halo positions; products and sums in the same order.
 template <typename R, int U>
@@ -658,7 +740,7 @@ constexpr int P_CG1 = 14;   // partials the finalize adds up
 // sliced copy; U entries of the row are loaded before their products are
 // summed (U accumulators, combined in a fixed order at the end).  The block
 // first stages p of its tile's halo in LDS; a slice of halo positions then
-// reads 6 bytes per entry from memory and p from LDS.  Slices of 16-bit
+// reads 5.5 bytes per entry from memory and p from LDS.  Slices of 16-bit
 // offsets (the halo did not fit) or full entries gather p from memory.
 template <typename R, int U, int MODE>
 __global__ void __launch_bounds__(TILE) k_spmv(const Tile *tiles, Seg *segs)
@@ -704,7 +786,8 @@ __global__ void __launch_bounds__(TILE) k_spmv(const Tile *tiles, Seg *segs)
         const R *hrow = reinterpret_cast<const R *>(S.H) + b0;
         const int cnt = S.hcnt[s];
         const int mode = S.swide[slot / SLICE];
-        a = mode == SL_HALO   ? spmv_row_halo<R, U>(hp, S.hs16 + b0, hrow, cnt)
+        a = mode == SL_HALO ? spmv_row_group<R>(hp, S.hs16, reinterpret_cast<const R *>(S.H), slot, cnt, S.Wl)
+            : mode == SL_HALO16 ? spmv_row_halo<R, U>(hp, S.hs16 + b0, hrow, cnt)
             : mode == SL_FULL ? spmv_row<R, U, uint32_t>(x, S.hsidx + b0, hrow, cnt, 0)
                               : spmv_row<R, U, uint16_t>(x, S.hs16 + b0, hrow, cnt, (slot & ~(SLICE - 1)) - 32768);
     }

@@ -86,3 +86,28 @@ def test_repeat_is_bitwise(ct, theta, systems):
     b = ct.Potential(theta).compute(s.pos, s.types, s.box, s.pbc, warm=False)
     assert a[0] == b[0]
     assert bool((a[1] == b[1]).all()) and bool((a[2] == b[2]).all())
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+def test_rows_that_fill_their_stride(ct, theta, orc, prec):
+    """Halo positions go in groups of eight 12-bit numbers, unless a slice's
+    longest row would not fit its stride rounded up to a group: with no skin
+    the Coulomb list holds the entries inside rc only, and a stride of the
+    longest row, and of the next multiple of eight, takes each form (a system
+    too large for the one-launch solve)."""
+    s = G.slab_4h(40, 40, 6, seed=175)
+    s.pos = s.pos + np.random.Generator(np.random.PCG64(176)).normal(0.0, 0.05, s.pos.shape)
+    tol = 1e-9 if prec == "mixed" else 1e-13
+    Eo, Fo, qo, _ = orc.evaluate(s.pos, s.types, s.box, s.pbc, theta, tol=1e-13)
+    t = TOL[prec]
+    cap = 512
+    for k in range(3):
+        print(f"[halo] stride {cap} n={s.n} {prec}", flush=True)
+        pot = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=tol, skin=0.0, long_cap=cap)
+        E, F, q, info = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)
+        assert info["status"] == 0 and info["nnz_coul_halo"] > 0
+        assert abs(E - Eo) / s.n <= t["E"]
+        assert np.linalg.norm(F.cpu().numpy() - Fo) / np.linalg.norm(Fo) <= t["F"]
+        assert np.abs(q.cpu().numpy() - qo).max() <= t["q"]
+        longest = info["max_long"]
+        cap = longest if k == 0 else (longest + 7) // 8 * 8
