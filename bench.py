@@ -584,7 +584,8 @@ def main():
     iters = int(info["cg_iters_total"]) - int(info_w["cg_iters_total"])
     avg_s = ms / 1e3 / max(iters, 1)
     # entry: FP32 value + 12-bit halo position (16-bit offset in slices whose halo does not fit,
-    # 32-bit index in wide slices); 52 bytes per row
+    # 32-bit index in wide slices); row: count, y_i, J_i, the result (H y)_i, and m1_i, r_i, s_i
+    # for the single-reduction solve's sums
     nnz_halo = int(info["nnz_coul_halo"])
     spmv_bytes = 4.0 * nnz + 1.5 * nnz_halo + 4.0 * nnz_wide + 2.0 * (nnz - nnz_halo - nnz_wide) + 52.0 * n
     achieved = spmv_bytes / avg_s / 1e9

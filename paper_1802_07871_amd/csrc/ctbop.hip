@@ -20,6 +20,7 @@
 #include "k_tersoff.h"
 #include "k_qeq.h"
 #include "k_solve.h"
+#include "k_solve_fq.h"
 #include "k_md.h"
 #include "k_fq.h"
 
@@ -533,11 +534,10 @@ int start_mode(const Prep &P, int flags)
 // device), so a system is solved alike alone and in the server: the blocks of
 // one system have to be on the device together, one per CU.  Up to 64 rows a
 // CU take 8 lanes per row, up to SV_MAX_ATOMS (16-bit halo positions, a
-// bitmap of all rows in LDS) 4 lanes; the charge coupling's nonlinear solve
-// has its own kernels.
+// bitmap of all rows in LDS) 4 lanes.
 int solve_lpr(ctbop_ctx *ctx, int n)
 {
-    if (ctx->opts.fq_kappa > 0.0 || n > SV_MAX_ATOMS) return 0;
+    if (n > SV_MAX_ATOMS) return 0;
     if (ctx->ncu == 0) {
         int dev = 0, ncu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
@@ -571,6 +571,20 @@ void launch_solve(int lpr, int ncu, const Tile *tiles, int nt, Seg *segs, SolveC
     else if (lpr == 8) hipLaunchKernelGGL((k_solve<8, R, 2>), g, b, 0, st, tiles, segs, ctl);
     else if (two) hipLaunchKernelGGL((k_solve<4, R, OCC2>), g, b, 0, st, tiles, segs, ctl);
     else hipLaunchKernelGGL((k_solve<4, R, 2>), g, b, 0, st, tiles, segs, ctl);
+}
+
+// The coupling's (one system per launch).
+template <typename R>
+void launch_solve_fq(int lpr, const Tile *tiles, int nt, Seg *segs, CgCtl ctl, hipStream_t st)
+{
+    const dim3 g(nt * (TILE / sv_rows(lpr))), b(SV_T), gt(nt), bt(TILE);
+    if (lpr == 8) {
+        hipLaunchKernelGGL(k_solve_fq_bonds<8>, gt, bt, 0, st, tiles, segs);
+        hipLaunchKernelGGL((k_solve_fq<8, R>), g, b, 0, st, tiles, segs, ctl);
+    } else {
+        hipLaunchKernelGGL(k_solve_fq_bonds<4>, gt, bt, 0, st, tiles, segs);
+        hipLaunchKernelGGL((k_solve_fq<4, R>), g, b, 0, st, tiles, segs, ctl);
+    }
 }
 
 // The row kernels over nt tiles, a tile or FINE rows per block.  The list
@@ -714,7 +728,8 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         if (P.own) HIPCHK(hipEventRecord(ctx->ev_join, ctx->side));
         return CTBOP_OK;
     };
-    const int lpr = solve_lpr(ctx, P.L.seg.n);
+    // (the coupling's one-launch solve keeps its bonds' halo positions beside the halo list)
+    const int lpr = fq && P.L.seg.Wl <= P.L.seg.Wb ? 0 : solve_lpr(ctx, P.L.seg.n);
     if (fq || lpr) {
         const int rc = side_launch();
         if (rc) return rc;
@@ -731,7 +746,12 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
             Timed t(ctx, 8, st);
             launch_solve_prep<R>(lpr, P.dtiles, nt, P.dseg, st);
         }
-        {
+        if (fq) {
+            // the bonds and their weights
+            if (P.own) HIPCHK(hipStreamWaitEvent(st, ctx->ev_join, 0));
+            Timed t(ctx, 0, st);
+            launch_solve_fq<R>(lpr, P.dtiles, nt, P.dseg, ctl, st);
+        } else {
             Timed t(ctx, 0, st);
             launch_solve<R>(lpr, ctx->ncu, P.dtiles, nt, P.dseg, SolveCtl{ctl.tol, ctl.maxit, 0}, st);
         }

@@ -60,3 +60,32 @@ def test_matches_oracle(ct, theta, reference, case, prec):
     again = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=1e-9 if prec == "mixed" else 1e-13).compute(
         s.pos, s.types, s.box, s.pbc, warm=False)
     assert again[0] == E and np.array_equal(again[1].cpu().numpy(), F) and np.array_equal(again[2].cpu().numpy(), q)
+
+
+# The charge coupling's solve, at its own edges: a block of 64 rows and one
+# more, the change of lanes per row, rows and bonds past what a lane keeps in
+# registers, the last size that takes it.  Its tolerances are the same (both
+# sides solve the nonlinear charges to the tolerances above).
+FQ_CASES = [(64, False, 0.7, 2.6), (65, True, 0.7, 2.6), (900, True, 0.9, 3.2), (16385, False, 0.7, 2.8),
+            (32512, True, 0.7, 2.4)]
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("case", FQ_CASES, ids=[str(c[0]) for c in FQ_CASES])
+def test_coupling_matches_oracle(ct, orc, theta, case, prec):
+    n, periodic, c_frac, density = case
+    s = G.random_system(n, c_frac, density, periodic, seed=3000 + n)
+    print(f"[one launch, coupling] n={s.n} {prec}", flush=True)
+    Eo, Fo, qo, _ = orc.evaluate_fq(s.pos, s.types, s.box, s.pbc, theta, 1.0, tol=1e-13)
+    runs = []
+    for _ in range(2):
+        pot = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=1e-9 if prec == "mixed" else 1e-13, fq_kappa=1.0)
+        E, F, q, info = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)
+        assert info["status"] == 0
+        runs.append((E, F.cpu().numpy(), q.cpu().numpy()))
+    E, F, q = runs[0]
+    t = TOL[prec]
+    assert abs(E - Eo) / s.n <= t["E"]
+    assert np.linalg.norm(F - Fo) / np.linalg.norm(Fo) <= t["F"]
+    assert np.abs(q - qo).max() <= t["q"]
+    assert runs[1][0] == E and np.array_equal(runs[1][1], F) and np.array_equal(runs[1][2], q)
