@@ -182,12 +182,8 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
         hipLaunchKernelGGL((k_cg1_update<true>), g, b, 0, st, P.dtiles, dadj);
         int done_it = 0;
         for (;;) {
-            for (int c = 0; c < ctx->opts.cg_check; c++) {
-                hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), g, b, 0, st, P.dtiles, dadj);
-                hipLaunchKernelGGL(k_cg1_sum, dim3(FIN_SPLIT), b, 0, st, sid, dadj);
-                hipLaunchKernelGGL(k_cg1_fin, g1, b, 0, st, sid, dadj, ctl);
-                hipLaunchKernelGGL((k_cg1_update<false>), g, b, 0, st, P.dtiles, dadj);
-            }
+            for (int c = 0; c < ctx->opts.cg_check; c++)
+                launch_cg1<R>(nullptr, P.L.ntile <= SPLIT_TILES, P.dtiles, P.L.ntile, sid, 1, dadj, ctl, st);
             done_it += ctx->opts.cg_check;
             HIPCHK(hipGetLastError());
             HIPCHK(hipMemcpyAsync(ctx->host_flag, &asst->done, 2 * sizeof(int), hipMemcpyDeviceToHost, st));

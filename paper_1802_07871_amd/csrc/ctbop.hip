@@ -396,7 +396,7 @@ struct Timed {
     hipEvent_t a = nullptr;
     Timed(ctbop_ctx *c, int kk, hipStream_t s) : ctx(c), k(kk), st(s)
     {
-        if (ctx->profile && ((ctx->profile_mask >> k) & 1u)) {
+        if (ctx && ctx->profile && ((ctx->profile_mask >> k) & 1u)) {
             a = ev_get(ctx);
             if (a) (void)hipEventRecord(a, st);
         }
@@ -585,6 +585,34 @@ void launch_solve_fq(int lpr, const Tile *tiles, int nt, Seg *segs, CgCtl ctl, h
         hipLaunchKernelGGL(k_solve_fq_bonds<4>, gt, bt, 0, st, tiles, segs);
         hipLaunchKernelGGL((k_solve_fq<4, R>), g, b, 0, st, tiles, segs, ctl);
     }
+}
+
+// One iteration of the multi-launch solve over nt tiles of nid systems: in
+// two launches where every system has at most SPLIT_TILES tiles (the rule is
+// on n alone, as a system's sums depend on it), in four otherwise.  ctx (the
+// profile's events, of the caller's thread alone) may be null.
+template <typename R>
+void launch_cg1(ctbop_ctx *ctx, bool split, const Tile *tiles, int nt, const int *ids, int nid, Seg *segs, CgCtl ctl,
+                hipStream_t st)
+{
+    const dim3 g(nt), b(TILE);
+    if (split) {
+        {
+            Timed t(ctx, 0, st);
+            hipLaunchKernelGGL(k_spmv_split<R>, dim3(nt * SPLIT), dim3(SPLIT_T), 0, st, tiles, segs);
+        }
+        Timed t(ctx, 5, st);
+        hipLaunchKernelGGL(k_cg1_step, g, b, 0, st, tiles, segs, ctl);
+        return;
+    }
+    {
+        Timed t(ctx, 0, st);
+        hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), g, b, 0, st, tiles, segs);
+    }
+    hipLaunchKernelGGL(k_cg1_sum, dim3(nid * FIN_SPLIT), b, 0, st, ids, segs);
+    hipLaunchKernelGGL(k_cg1_fin, dim3(nid), b, 0, st, ids, segs, ctl);
+    Timed t(ctx, 5, st);
+    hipLaunchKernelGGL((k_cg1_update<false>), g, b, 0, st, tiles, segs);
 }
 
 // The row kernels over nt tiles, a tile or FINE rows per block.  The list
@@ -805,14 +833,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         for (;;) {
             for (int c = 0; c < chunk; c++) {
                 if (!fq) {
-                    {
-                        Timed t(ctx, 0, st);
-                        hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), g, b, 0, st, P.dtiles, P.dseg);
-                    }
-                    hipLaunchKernelGGL(k_cg1_sum, dim3(FIN_SPLIT), b, 0, st, sid, P.dseg);
-                    hipLaunchKernelGGL(k_cg1_fin, g1, b, 0, st, sid, P.dseg, ctl);
-                    Timed t(ctx, 5, st);
-                    hipLaunchKernelGGL((k_cg1_update<false>), g, b, 0, st, P.dtiles, P.dseg);
+                    launch_cg1<R>(ctx, nt <= SPLIT_TILES, P.dtiles, nt, sid, 1, P.dseg, ctl, st);
                     continue;
                 }
                 {

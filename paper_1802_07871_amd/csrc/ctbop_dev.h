@@ -68,7 +68,7 @@ struct Params {
 // ---------------------------------------------------------------------------
 struct SegState {
     int rebuild;       // lists rebuilt in this call
-    int ticket;        // last-block detection counter (returns to 0)
+    int par;           // split iteration: which set of the update's partials is current
     int done;          // charge solve finished
     int iters;
     int pabort;        // one-launch solve: given up (the host takes the multi-launch path)
@@ -135,7 +135,7 @@ struct Seg {
     double *E_out;     // 1
     // persistent arrays
     int *perm;         // sorted row -> user index        [npad]
-    int *perm_tmp;     // the scatter's order of each cell's atoms (list build only) [npad]
+    int *perm_tmp;     // the scatter's order of each cell's atoms (list build only; then scratch of the split product) [npad]
     int *cell_of;      // user index -> cell              [n]
     int *csort;        // sorted row -> cell              [npad]
     int *cell_start;   // [ncell + 1]

@@ -25,7 +25,6 @@ __global__ void k_call_init(const int *seg_ids, Seg *segs, int nseg, int force_r
     if (k >= nseg) return;
     SegState *st = segs[seg_ids[k]].sst;
     st->rebuild = (force_rebuild || !st->built) ? 1 : 0;
-    st->ticket = 0;
     st->done = 0;
     st->iters = 0;
     st->status = 0;
@@ -353,7 +352,6 @@ __global__ void __launch_bounds__(L1_T) k_frame_small(Seg *segs, int force_rebui
     const bool rebuild = __syncthreads_or(move) != 0 || force_rebuild || !built;
     if (tid == 0) {
         st->rebuild = rebuild ? 1 : 0;
-        st->ticket = 0;
         st->done = 0;
         st->iters = 0;
         st->pabort = 0;

@@ -535,6 +535,7 @@ __global__ void k_fin_w0(const int *seg_ids, Seg *segs)
         st->qshift = 0.0;
         st->cg_first = 1;
         st->cg_last = 0;
+        st->par = 0;
     }
 }
 
@@ -820,6 +821,198 @@ __global__ void __launch_bounds__(TILE) k_spmv(const Tile *tiles, Seg *segs)
 }
 
 // ---------------------------------------------------------------------------
+// Systems of up to SPLIT_TILES tiles: the product with eight waves per row
+// slice, and the finalize in the update (two launches per iteration instead
+// of four).  There a lane per row leaves most of the card idle and an
+// iteration is a chain of launches that each wait for memory once or twice:
+// 36,864 atoms 50 us (product 29.5, its sums 8.8, update 4.5, gaps), now 31
+// (18, 7.3, gaps); ten MD steps 19.4 -> 12.9 ms.
+// ---------------------------------------------------------------------------
+constexpr int SPLIT_TILES = 256;
+static_assert(sizeof(SegState) <= 16 * FIN_SPLIT * sizeof(double) && sizeof(SegState) / 4 <= TILE, "scratch, a word per thread");
+constexpr int SPLIT = TILE / SLICE;         // blocks per tile: one per slice
+
+// scratch of the split iteration: the product's partials (k of block b at k
+// * blocks + b) where the list build keeps an order, the solver's state at
+// the product in the group sums' place
+__device__ __forceinline__ double *split_part(const Seg &S) { return reinterpret_cast<double *>(S.perm_tmp); }
+__device__ __forceinline__ SegState *split_state(const Seg &S)
+{
+    return reinterpret_cast<SegState *>(S.part + (size_t)NPART * S.ntile);
+}
+
+constexpr int SPLIT_T = 512, SPLIT_W = SPLIT_T / 64;
+
+// One wave's share of a row: entries in groups of GRP, every SPLIT_W-th
+// group (the first is loaded before y is staged).
+template <typename R>
+struct SplitRow {
+    static constexpr int V = 16 / sizeof(R), NP = GRP / V;
+    typedef R rv __attribute__((ext_vector_type(V)));
+    const __attribute__((address_space(1))) unsigned *pos;
+    const __attribute__((address_space(1))) rv *val;
+    int ng, g;
+    unsigned w[3];
+    rv v[NP];
+    __device__ __forceinline__ void load()
+    {
+        if (g >= ng) return;
+#pragma unroll
+        for (int k = 0; k < 3; k++) w[k] = pos[(size_t)g * (SLICE * 3) + k];
+#pragma unroll
+        for (int k = 0; k < NP; k++) v[k] = val[((size_t)g * NP + k) * SLICE];
+    }
+    __device__ __forceinline__ double sum(const double *hp)
+    {
+        double acc[GRP];
+#pragma unroll
+        for (int u = 0; u < GRP; u++) acc[u] = 0.0;
+        while (g < ng) {
+            const unsigned long long lo = ((unsigned long long)w[1] << 32) | w[0],
+                                     hi = ((unsigned long long)w[2] << 32) | w[1];
+            const unsigned p[GRP] = {(unsigned)lo & 4095u,         (unsigned)(lo >> 12) & 4095u,
+                                     (unsigned)(lo >> 24) & 4095u, (unsigned)(lo >> 36) & 4095u,
+                                     (unsigned)(hi >> 16) & 4095u, (unsigned)(hi >> 28) & 4095u,
+                                     (unsigned)(hi >> 40) & 4095u, (unsigned)(hi >> 52) & 4095u};
+#pragma unroll
+            for (int u = 0; u < GRP; u++) acc[u] += (double)v[u / V][u % V] * hp[p[u]];
+            g += SPLIT_W;
+            load();
+        }
+        double a = 0.0;
+#pragma unroll
+        for (int u = 0; u < GRP; u++) a += acc[u];
+        return a;
+    }
+};
+
+// The same of entries that are not grouped: positions idx(e) into x.
+template <typename R, typename X, typename I>
+__device__ __forceinline__ double spmv_part(X x, const R *hrow_, int cnt, int wv, I idx)
+{
+    const auto hrow = gbl(hrow_);
+    double acc[GRP];
+#pragma unroll
+    for (int u = 0; u < GRP; u++) acc[u] = 0.0;
+    for (int e0 = wv * GRP; e0 < cnt; e0 += SPLIT_W * GRP) {
+        int j[GRP];
+        R h[GRP];
+#pragma unroll
+        for (int u = 0; u < GRP; u++) {
+            const int e = min(e0 + u, cnt - 1);
+            j[u] = idx(e);
+            h[u] = hrow[(size_t)e * SLICE];
+        }
+#pragma unroll
+        for (int u = 0; u < GRP; u++)
+            if (e0 + u < cnt) acc[u] += (double)h[u] * x[j[u]];
+    }
+    double a = 0.0;
+#pragma unroll
+    for (int u = 0; u < GRP; u++) a += acc[u];
+    return a;
+}
+
+// H y of one slice (a lane per row, SPLIT_W waves sharing its entries), and
+// the six sums the finalize needs; also copies the solver's state for the
+// update.  Bound by latency (five loads that wait for one another, 38 MB of
+// entries at 2.1 TB/s beside them): what does not wait for y (the halo list,
+// the first entries) is loaded before the test for the end of the solve, and
+// three blocks fit on a CU, so that 65,536 atoms run in two rounds (four
+// waves per slice 22 us, eight with up to four groups in flight 18.4 to 19.3,
+// one group in flight 17.8).
+template <typename R>
+__global__ void __launch_bounds__(SPLIT_T, sizeof(R) == 8 ? 4 : 6) k_spmv_split(const Tile *tiles, Seg *segs)
+{
+    constexpr int NHL = HALO_MAX / SPLIT_T;
+    static_assert(HALO_MAX % SPLIT_T == 0, "whole rounds of the staging");
+    const Tile T = tiles[blockIdx.x / SPLIT];
+    const int sl = blockIdx.x % SPLIT, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / SLICE),
+              wl = threadIdx.x % SLICE;
+    const Seg &S = segs[T.seg];
+    const int tl = T.row0 / TILE;
+    const int slot = T.row0 + sl * SLICE + wl;
+    const int rl = gbl(S.hperm)[slot];
+    const int nh = S.nhalo[tl], mode = S.swide[slot / SLICE], over = S.sst->done | S.sst->cg_last;
+    const auto hl = gbl(S.halo + (size_t)tl * HALO_MAX);
+    int j[NHL];
+#pragma unroll
+    for (int u = 0; u < NHL; u++) j[u] = (int)hl[threadIdx.x + u * SPLIT_T];
+    if (tl == 0 && sl == 0 && threadIdx.x < sizeof(SegState) / 4)
+        reinterpret_cast<int *>(split_state(S))[threadIdx.x] = reinterpret_cast<const int *>(S.sst)[threadIdx.x];
+    if (over) return;
+    __shared__ double hp[HALO_MAX];
+    __shared__ double sum[SPLIT_W][SLICE];
+    const int s = T.row0 + rl;
+    const bool live = s < S.n;
+    const auto x = gbl(S.y);
+    const int cnt = live ? gbl(S.hcnt)[s] : 0;
+    double xs = 0.0, jd = 0.0, m1s = 0.0, rs = 0.0, ss = 0.0;
+    if (wv == 0 && live) {
+        xs = x[s];
+        jd = gbl(S.jd)[s];
+        m1s = gbl(S.m1)[s];
+        rs = gbl(S.r)[s];
+        ss = gbl(S.s)[s];
+    }
+    double v[NHL];
+    const bool staged = nh <= HALO_MAX;
+    if (staged) {
+#pragma unroll
+        for (int u = 0; u < NHL; u++)
+            if ((int)threadIdx.x + u * SPLIT_T < nh) v[u] = x[j[u]];
+    }
+    SplitRow<R> row;
+    row.pos = gbl(reinterpret_cast<const unsigned *>(S.hs16 + hs_group(slot, 0, S.Wl)));
+    row.val = (const __attribute__((address_space(1))) typename SplitRow<R>::rv *)gbl(
+        reinterpret_cast<const R *>(S.H) + hs_plane<R>(slot, 0, 0, S.Wl));
+    row.ng = mode == SL_HALO ? (cnt + GRP - 1) / GRP : 0;
+    row.g = wv;
+    row.load();
+    if (staged) {
+#pragma unroll
+        for (int u = 0; u < NHL; u++)
+            if ((int)threadIdx.x + u * SPLIT_T < nh) hp[threadIdx.x + u * SPLIT_T] = v[u];
+    }
+    __syncthreads();
+    double a = 0.0;
+    if (mode == SL_HALO) {
+        a = row.sum(hp);
+    } else if (live) {
+        const size_t b0 = slice_base(slot, S.Wl);
+        const R *hrow = reinterpret_cast<const R *>(S.H) + b0;
+        const auto h16 = gbl(S.hs16 + b0);
+        const auto h32 = gbl(S.hsidx + b0);
+        const int jb = (slot & ~(SLICE - 1)) - 32768;
+        if (mode == SL_HALO16)
+            a = spmv_part<R>((const double *)hp, hrow, cnt, wv, [&](int e) { return (int)h16[(size_t)e * SLICE]; });
+        else if (mode == SL_FULL)
+            a = spmv_part<R>(x, hrow, cnt, wv, [&](int e) { return (int)(h32[(size_t)e * SLICE] & J_MASK); });
+        else
+            a = spmv_part<R>(x, hrow, cnt, wv, [&](int e) { return jb + (int)h16[(size_t)e * SLICE]; });
+    }
+    sum[wv][wl] = a;
+    __syncthreads();
+    if (wv != 0) return;
+    double y = 0.0;
+    if (live) {
+        double t = sum[0][wl];
+#pragma unroll
+        for (int k = 1; k < SPLIT_W; k++) t += sum[k][wl];
+        y = jd * xs + t;
+        S.hz[s] = y;
+    }
+    const double p[6] = {xs * y, m1s * y, rs * y, y * y, ss * y, y};
+    const auto out = gblw(split_part(S));
+    const int nb = S.ntile * SPLIT, blk = tl * SPLIT + sl;
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        const double t = wave_sum(p[k]);
+        if (wl == 0) out[(size_t)k * nb + blk] = t;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // The same projected PCG with one reduction per iteration (Chronopoulos and
 // Gear's rearrangement of conjugate gradients): the product is taken of
 // y = M r, the unprojected preconditioned residual, and the direction's
@@ -831,7 +1024,8 @@ __global__ void __launch_bounds__(TILE) k_spmv(const Tile *tiles, Seg *segs)
 // (each minus its mean part), from sums of the two kernels, so the solve
 // stops after the update that meets the tolerance without a further product.
 // An iteration is four launches: product (k_spmv, SP_CG1), the finalize's two
-// stages (k_cg1_sum, k_cg1_fin), update.
+// stages (k_cg1_sum, k_cg1_fin), update; of up to SPLIT_TILES tiles it is two,
+// k_spmv_split and k_cg1_step.
 // ---------------------------------------------------------------------------
 
 // p <- y + beta p, s <- H y + beta s, q <- q + alpha p, r <- r - alpha s - c,
@@ -965,6 +1159,139 @@ __global__ void __launch_bounds__(TILE) k_cg1_fin(const int *seg_ids, Seg *segs,
     if (threadIdx.x == 0) {
         const int bad = cg1_step(*S.sst, 1.0 / S.n, 1.0 / S.sst->sdinv, S.Q, t, ctl.tol, ctl.maxit);
         if (bad) atomicOr(&S.sst->status, bad);
+    }
+}
+
+// The split iteration's second launch: every block adds up the partials of
+// all blocks and takes the scalar step itself, then updates its tile's rows
+// as k_cg1_update does.  The state it reads is the product's copy and the
+// first block stores the new one, and the update's partials have two sets
+// (SegState::par), so no block reads what another writes.  36,864 atoms: 7.3 us
+// against 13.3 and two launch gaps in three launches.
+__global__ void __launch_bounds__(TILE) k_cg1_step(const Tile *tiles, Seg *segs, CgCtl ctl)
+{
+    const Tile T = my_tile(tiles);
+    const Seg &S = segs[T.seg];
+    const SegState *const old = split_state(S);
+    __shared__ double lds[4 * 8];
+    __shared__ double tot[16];
+    __shared__ SegState st;
+    constexpr int NW = TILE / 64;
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid / 64), wl = tid % 64;
+    if (tid < (int)(sizeof(SegState) / 4)) reinterpret_cast<int *>(&st)[tid] = reinterpret_cast<const int *>(old)[tid];
+    // the row, in flight beside the sums
+    const int s = T.row0 + tid, nt = S.ntile, par = old->par;
+    const bool live = s < S.n;
+    const auto qv = gblw(S.q);
+    const auto rv = gblw(S.r);
+    const auto yv = gblw(S.y);
+    const auto pv = gblw(S.p);
+    const auto sv = gblw(S.s);
+    const auto hz = gbl(S.hz);
+    const auto part = gblw(S.part);
+    const _Float16 *binv = S.binv;
+    double q = 0.0, r = 0.0, y = 0.0, p = 0.0, sn = 0.0, h = 0.0;
+    if (live) {
+        q = qv[s];
+        r = rv[s];
+        y = yv[s];
+        p = pv[s];
+        sn = sv[s];
+        h = hz[s];
+    }
+    // sums wv, wv + NW, ...: 0..7 of the update (a partial per tile), 8..13
+    // of the product (SPLIT per tile)
+    const auto prd = gbl(split_part(S));
+    constexpr int NU = SPLIT_TILES / 64, NP = SPLIT_TILES * SPLIT / 64;
+    const int nb = nt * SPLIT, kp = 2 - wv / 2;      // the wave's sums of the product: 2, 2, 1, 1
+    double xu[2][NU], xp[2][NP];
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int i = 0; i < NP; i++)
+            if (i * 64 < nb) xp[h][i] = prd[(size_t)min(wv + h * NW, 5) * nb + min(i * 64 + wl, nb - 1)];
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int i = 0; i < NU; i++) xu[h][i] = part[(size_t)(8 * par + wv + h * NW) * nt + min(i * 64 + wl, nt - 1)];
+    if (old->done) return;
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        double t = 0.0, u = 0.0;
+#pragma unroll
+        for (int i = 0; i < NU; i++) t += i * 64 + wl < nt ? xu[h][i] : 0.0;
+#pragma unroll
+        for (int i = 0; i < NP; i++)
+            if (i * 64 < nb) u += i * 64 + wl < nb ? xp[h][i] : 0.0;
+        t = wave_sum(t);
+        u = wave_sum(u);
+        if (wl == 0) {
+            tot[P_UPD + wv + h * NW] = t;
+            if (h < kp) tot[P_PRD + wv + h * NW] = u;
+        }
+    }
+    __syncthreads();
+    if (wv == 0) {
+        const double mine = tot[wl & 15];
+        double t[P_CG1];
+#pragma unroll
+        for (int k = 0; k < P_CG1; k++)
+            t[k] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(mine), k),
+                                    __builtin_amdgcn_readlane(__double2loint(mine), k));
+        if (wl == 0) {
+            const int bad = cg1_step(st, 1.0 / S.n, 1.0 / st.sdinv, S.Q, t, ctl.tol, ctl.maxit);
+            if (T.row0 == 0) {
+                SegState *o = S.sst;
+                o->par = par ^ 1;
+                o->iters = st.iters;
+                o->iters_total = st.iters_total;
+                o->cg_first = st.cg_first;
+                o->cg_last = st.cg_last;
+                o->w = st.w;
+                o->rho = st.rho;
+                o->alpha = st.alpha;
+                o->beta = st.beta;
+                o->res = st.res;
+                o->res0 = st.res0;
+                o->mshift = st.mshift;
+                o->qshift = st.qshift;
+                o->m1s = st.m1s;
+                o->den = st.den;
+                if (bad) atomicOr(&o->status, bad);
+                o->done = st.done;
+            }
+        }
+    }
+    __syncthreads();
+    if (st.done) return;
+    if (live) {
+        p = y + st.beta * p;
+        sn = h + st.beta * sn;
+        q = q + st.alpha * p;
+        r = (r - st.alpha * sn) - st.w;
+        pv[s] = p;
+        sv[s] = sn;
+        qv[s] = q;
+        rv[s] = r;
+    }
+    y = block_apply(binv, s, r);
+    double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (live) {
+        yv[s] = y;
+        v[0] = y;
+        v[1] = r * y;
+        v[2] = r;
+        v[3] = r * r;
+        v[4] = q;
+        v[5] = r * sn;
+        v[6] = sn * sn;
+        v[7] = sn;
+    }
+    double u[8];
+    block_sum<8>(v, lds, u);
+    if (tid == 0) {
+#pragma unroll
+        for (int k = 0; k < 8; k++) part[(size_t)(8 * (par ^ 1) + k) * nt + T.row0 / TILE] = u[k];
     }
 }
 

@@ -378,16 +378,15 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         CgCtl ctl{ctx->opts.cg_tol, ctx->opts.cg_maxit};
         // single-reduction solve: a solve of n iterations takes n + 1 rounds
         // (its first finalize counts none)
-        const dim3 gm(nta_many), gsm(nia_many);
         const int limit = nia_many == 0 ? 0 : poll ? ctx->opts.cg_maxit + 2 : cg_iters;
         for (int c = 0; c < limit;) {
             const int first = std::max(ctx->opts.cg_check, std::min(S->iters_hint, ctx->opts.cg_maxit) + 1);
             const int chunk = poll ? std::min(limit - c, c == 0 ? first : ctx->opts.cg_check) : cg_iters;
             for (int k = 0; k < chunk; k++) {
-                hipLaunchKernelGGL((k_spmv<R, SPMV_U, SP_CG1>), gm, b, 0, st, T, S->dsegs);
-                hipLaunchKernelGGL(k_cg1_sum, dim3(nia_many * FIN_SPLIT), b, 0, st, sid, S->dsegs);
-                hipLaunchKernelGGL(k_cg1_fin, gsm, b, 0, st, sid, S->dsegs, ctl);
-                hipLaunchKernelGGL((k_cg1_update<false>), gm, b, 0, st, T, S->dsegs);
+                if (nia_coarse) launch_cg1<R>(nullptr, false, T, nta_coarse, sid, nia_coarse, S->dsegs, ctl, st);
+                if (nia_many > nia_coarse)
+                    launch_cg1<R>(nullptr, true, T + nta_coarse, nta_many - nta_coarse, sid + nia_coarse,
+                                  nia_many - nia_coarse, S->dsegs, ctl, st);
             }
             c += chunk;
             if (!poll || c >= limit) break;

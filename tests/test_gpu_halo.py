@@ -111,3 +111,33 @@ def test_rows_that_fill_their_stride(ct, theta, orc, prec):
         assert np.abs(q.cpu().numpy() - qo).max() <= t["q"]
         longest = info["max_long"]
         cap = longest if k == 0 else (longest + 7) // 8 * 8
+
+
+# The same forms above 65,536 atoms, where the product has a lane per row (the
+# systems above run it with eight waves per row slice).
+LARGE = {
+    "stepped slab": (lambda: G.slab_4h(50, 50, 8, step=True, deplete=0.3, seed=177), ("halo", "full")),
+    "3C-SiC 74088": (lambda: G.zincblende(21, sigma=0.05, seed=178), ("off16",)),
+    "full rows": (lambda: G.slab_4h(54, 54, 6, seed=179), ("halo",)),
+}
+
+
+@pytest.mark.parametrize("name", list(LARGE))
+def test_forms_of_a_large_system(ct, theta, orc, name):
+    s = LARGE[name][0]()
+    s.pos = s.pos + np.random.Generator(np.random.PCG64(180)).normal(0.0, 0.05, s.pos.shape)
+    assert s.n > 65536
+    Eo, Fo, qo, _ = orc.evaluate(s.pos, s.types, s.box, s.pbc, theta, tol=1e-13)
+    t, opts = TOL["mixed"], {}
+    if name == "full rows":
+        # a stride of the longest row: its slice keeps 16-bit positions
+        opts = dict(skin=0.0, long_cap=ct.Potential(theta, skin=0.0).compute(s.pos, s.types, s.box, s.pbc)[3]["max_long"])
+    print(f"[halo] {name} n={s.n} {opts}", flush=True)
+    E, F, q, info = ct.Potential(theta, **opts).compute(s.pos, s.types, s.box, s.pbc, warm=False)
+    nnz, wide, halo = info["nnz_coul"], info["nnz_coul_wide"], info["nnz_coul_halo"]
+    forms = {"halo": halo, "full": wide, "off16": nnz - wide - halo}
+    assert all(forms[f] > 0 for f in LARGE[name][1]), forms
+    assert info["status"] == 0
+    assert abs(E - Eo) / s.n <= t["E"]
+    assert np.linalg.norm(F.cpu().numpy() - Fo) / np.linalg.norm(Fo) <= t["F"]
+    assert np.abs(q.cpu().numpy() - qo).max() <= t["q"]
