@@ -537,7 +537,7 @@ int start_mode(const Prep &P, int flags)
 // bitmap of all rows in LDS) 4 lanes.
 int solve_lpr(ctbop_ctx *ctx, int n)
 {
-    if (n > SV_MAX_ATOMS) return 0;
+    if (n > SV_MAX_ATOMS || ctx->opts.long_cap < SV_MIN_WL) return 0;
     if (ctx->ncu == 0) {
         int dev = 0, ncu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||

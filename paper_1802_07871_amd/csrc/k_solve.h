@@ -42,6 +42,10 @@ constexpr unsigned long long SV_NAN = 0x7ff8000000000000ull;
 constexpr long long SV_WAIT = CTBOP_SOLVE_WAIT;   // ticks of the 100 MHz clock: 50 ms per wait (< 0: none waits, a check of the way out)
 constexpr int SV_NSUM = 14;
 constexpr int SV_MAX_BLOCKS = 256;          // blocks of one system
+constexpr int SV_LINE = 16;                 // a block's sums: one 128-byte line,
+constexpr int SV_REP = 4;                   // in as many copies, a quarter of the blocks reading each
+constexpr int SV_NW = SV_T / 64;
+constexpr int SV_MIN_WL = 8;                // list strides whose copy of the rows holds the lines
 
 // rows of a block, LPR lanes each
 constexpr int sv_rows(int lpr) { return SV_T / lpr; }
@@ -122,9 +126,9 @@ __device__ __forceinline__ int sv_row0(const Tile *tiles, const Seg *segs, int &
 }
 
 // scratch of the solve in arrays that only the multi-launch path uses: the
-// y buffers are S.y and S.hz, the sums S.p (three buffers of SV_NSUM per
-// block), the block's halo list the head of its rows in S.hsidx, with its
-// length in the last word of them
+// y buffers are S.y and S.hz, the sums the head of S.H (three buffers of
+// SV_REP lines per block), the block's halo list the head of its rows in
+// S.hsidx, with its length in the last word of them
 __device__ __forceinline__ __attribute__((address_space(1))) unsigned long long *sv_slots(double *p)
 {
     return (__attribute__((address_space(1))) unsigned long long *)p;
@@ -135,7 +139,59 @@ __device__ __forceinline__ void sv_clear_row(const Seg &S, int s)
 {
     reinterpret_cast<unsigned long long *>(S.y)[s] = SV_EMPTY;
     reinterpret_cast<unsigned long long *>(S.hz)[s] = SV_EMPTY;
-    reinterpret_cast<unsigned long long *>(S.p)[s] = SV_EMPTY;
+}
+
+// The sums of a block, loc[0 .. 15], into its line of a buffer, by one wave:
+// one 128-byte store per copy.  (A slot per sum and block, [sum][block],
+// made 14 narrow stores into lines that 16 blocks share and all blocks read:
+// 20,000 atoms, 8000 cycles from the first store to the last sum.)
+__device__ __forceinline__ __attribute__((address_space(1))) unsigned long long *
+sv_line(__attribute__((address_space(1))) unsigned long long *slots, int buf, int nblk, int blk, int wl)
+{
+    static_assert(SV_REP * SV_LINE == 64, "a lane per word");
+    return slots + (unsigned)(((buf * SV_REP + (wl >> 4)) * nblk + blk) * SV_LINE + (wl & 15));
+}
+
+// The waves' shares of every block's sums into red (wave w takes blocks 4 w
+// .. 4 w + 3 of every 32); false when a wait ran out.
+__device__ __forceinline__ bool sv_collect(__attribute__((address_space(1))) unsigned long long *slots, int buf, int nblk,
+                                           int blk, double (*red)[SV_LINE], int wv, int wl, const int *pabort)
+{
+    constexpr int PB = SV_MAX_BLOCKS / (4 * SV_NW);
+    const auto line = slots + (unsigned)((buf * SV_REP + (blk & (SV_REP - 1))) * nblk * SV_LINE + (wl & 15));
+    unsigned long long x[PB];
+#pragma unroll
+    for (int i = 0; i < PB; i++)
+        if ((i * SV_NW + wv) * 4 < nblk)
+            x[i] = sv_get(line + (unsigned)(min((i * SV_NW + wv) * 4 + (wl >> 4), nblk - 1) * SV_LINE));
+    bool ok = true;
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < PB; i++)
+        if ((i * SV_NW + wv) * 4 < nblk) {
+            const int b = (i * SV_NW + wv) * 4 + (wl >> 4);
+            ok = ok && sv_wait(line + (unsigned)(min(b, nblk - 1) * SV_LINE), x[i], pabort);
+            t += b < nblk ? __longlong_as_double((long long)x[i]) : 0.0;
+        }
+    t += __shfl_xor(t, 16, 64);
+    t += __shfl_xor(t, 32, 64);
+    if (wl < SV_LINE) red[wv][wl] = t;
+    return ok;
+}
+
+// sum wl & 15 of the system, from the waves' shares (one block: its own)
+__device__ __forceinline__ double sv_total(const double *loc, const double (*red)[SV_LINE], int nblk, int wl)
+{
+    if (nblk == 1) return loc[wl & 15];
+    double t = red[0][wl & 15];
+#pragma unroll
+    for (int w = 1; w < SV_NW; w++) t += red[w][wl & 15];
+    return t;
+}
+__device__ __forceinline__ double sv_lane(double v, int k)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
+                            __builtin_amdgcn_readlane(__double2loint(v), k));
 }
 
 // before the multi-launch solve of a system whose one-launch solve gave up
@@ -291,6 +347,7 @@ __global__ void __launch_bounds__(SV_T) k_solve_prep(const Tile *tiles, Seg *seg
         S.m1[row] = live ? m1 : 0.0;
         sv_clear_row(S, row);
     }
+    if (tid < 3 * 64) *sv_line(sv_slots((double *)S.H), tid / 64, (n + RB - 1) / RB, row0 / RB, tid % 64) = SV_EMPTY;
     // partial sums of the block: r m1, m1 and the entries
     double v[3] = {0.0, 0.0, 0.0};
     if (live && lane == 0) {
@@ -347,7 +404,7 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
     __shared__ double va[9][RB];
     double *const vr = va[0], *const vy = va[1], *const vs = va[2], *const vq = va[3], *const vh = va[5],
            *const vp = va[7], *const vj = va[8];
-    __shared__ double tot[16];
+    __shared__ double tot[SV_LINE], red[SV_NW][SV_LINE];   // the block's sums, the waves' shares of all blocks'
     __shared__ SegState st;
     __shared__ int sab;
     const int tid = threadIdx.x, rl = tid / LPR, lane = tid % LPR, row = row0 + rl, wv = uni(tid >> 6), wl = tid & 63;
@@ -356,7 +413,7 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
     const double Q = S.Q;
     SegState *const sst = uni(S.sst);
     int *const pabort = &sst->pabort;
-    const auto slots_y0 = sv_slots(uni(S.y)), slots_y1 = sv_slots(uni(S.hz)), slots_p = sv_slots(uni(S.p));
+    const auto slots_y0 = sv_slots(uni(S.y)), slots_y1 = sv_slots(uni(S.hz)), slots_p = sv_slots(uni((double *)S.H));
     // the block's halo rows
     const uint32_t *region = S.hsidx + (size_t)row0 * Wl;
     const int nh = uni((int)region[(size_t)RB * Wl - 1]);
@@ -399,6 +456,7 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
     static_assert(sizeof(SegState) % 4 == 0 && sizeof(SegState) / 4 <= SV_T, "a word per thread");
     if (tid < (int)(sizeof(SegState) / 4)) reinterpret_cast<int *>(&st)[tid] = reinterpret_cast<const int *>(sst)[tid];
     if (tid == 0) sab = 0;
+    if (tid < SV_LINE) tot[tid] = 0.0;
     if (lane == 0) {
         vr[rl] = live ? S.r[row] : 0.0;
         vq[rl] = live ? S.q[row] : 0.0;
@@ -516,7 +574,6 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         // sums wv and wv + NW: the block's share, then every block's
-        const auto slots = slots_p + (size_t)(it % 3) * SV_NSUM * nblk;
         double v[2];
 #pragma unroll
         for (int h = 0; h < 2; h++) {
@@ -529,49 +586,21 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
 #pragma unroll
         for (int h = 0; h < 2; h++) {
             v[h] = wave_sum(v[h]);
-            const int w = wv + h * NW;
-            if (wl == 0 && w < SV_NSUM) {
-                if (nblk > 1) sv_put(slots + w * nblk + blk, v[h]);
-                else tot[w] = v[h];
-            }
+            if (wl == 0 && wv + h * NW < SV_NSUM) tot[wv + h * NW] = v[h];
         }
         if (nblk > 1) {
-            constexpr int PB = SV_MAX_BLOCKS / 64;
-            bool ok = true;
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const auto slot = slots + (unsigned)(min(wv + h * NW, SV_NSUM - 1) * nblk);
-                unsigned long long x[PB];
-#pragma unroll
-                for (int u = 0; u < PB; u++)
-                    if (u * 64 < nblk) x[u] = sv_get(slot + (unsigned)min(u * 64 + wl, nblk - 1));
-                double t = 0.0;
-#pragma unroll
-                for (int u = 0; u < PB; u++)
-                    if (u * 64 < nblk) {
-                        const int b = u * 64 + wl;
-                        ok = ok && sv_wait(slot + (unsigned)min(b, nblk - 1), x[u], pabort);
-                        t += b < nblk ? __longlong_as_double((long long)x[u]) : 0.0;
-                    }
-                v[h] = t;
-            }
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                v[h] = wave_sum(v[h]);
-                if (wl == 0 && wv + h * NW < SV_NSUM) tot[wv + h * NW] = v[h];
-            }
-            if (!ok) sab = 1;
+            __syncthreads();
+            if (wv == 0) sv_put(sv_line(slots_p, it % 3, nblk, blk, wl), tot[wl & 15]);
+            if (!sv_collect(slots_p, it % 3, nblk, blk, red, wv, wl, pabort)) sab = 1;
         }
         __syncthreads();
         if (sab) break;
         if (wv == 0) {
             // the scalar step, on the sums in scalar registers
-            const double mine = tot[wl & 15];
+            const double mine = sv_total(tot, red, nblk, wl);
             double t[P_CG1];
 #pragma unroll
-            for (int k = 0; k < P_CG1; k++)
-                t[k] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(mine), k),
-                                        __builtin_amdgcn_readlane(__double2loint(mine), k));
+            for (int k = 0; k < P_CG1; k++) t[k] = sv_lane(mine, k);
             if (wl == 0 && st.cg_first == 2) {
                 st.w = t[P_UPD + 0] * inv_sd;
                 st.mshift -= st.w;
@@ -586,9 +615,7 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
         }
         // empty this iteration's y and the previous one's sums
         if (!last && lane == 0) sv_clear(((it & 1) ? slots_y1 : slots_y0) + row);
-        if (nblk > 1 && wl == 0)
-            for (int w = wv; w < SV_NSUM; w += NW)
-                sv_clear(slots_p + ((size_t)((it + 2) % 3) * SV_NSUM + w) * nblk + blk);
+        if (nblk > 1 && wv == 1) sv_clear(sv_line(slots_p, (it + 2) % 3, nblk, blk, wl));
         __syncthreads();
         if (st.done) break;
         if (lane == 0 && live) {

@@ -17,7 +17,6 @@
 
 namespace ctbop {
 
-constexpr int SVF_NSUM = 7;
 constexpr int SVF_REG_BONDS = 2;            // bonds a lane keeps in registers
 
 // Each bond's position in the block's halo, 16 bits, row-major (Wb per row):
@@ -29,58 +28,41 @@ __device__ __forceinline__ uint16_t *svf_bonds(const Seg &S, int row0, int rb)
     return reinterpret_cast<uint16_t *>(S.hsidx + (size_t)row0 * S.Wl) + (size_t)rb * S.Wl;
 }
 
-// Sums 0 .. K-1 of the products of two row arrays (or an array and ones), as
-// in k_solve: K <= the block's waves, one each; results in tot.  Round `ex`
-// of the exchange.  false: a wait ran out.
+// Sums 0 .. K-1 of the products of two row arrays, a wave each, as in
+// k_solve: the block's into tot, every block's into red.  Round `ex` of the
+// exchange.  false: a wait ran out.
 template <int K, int RB>
 __device__ __forceinline__ bool svf_sum(const double (*va)[RB], unsigned long long fa, unsigned long long fb, int wv,
                                         int wl, int nblk, int blk, int ex,
                                         __attribute__((address_space(1))) unsigned long long *slots_p, double *tot,
-                                        const int *pabort)
+                                        double (*red)[SV_LINE], const int *pabort)
 {
-    bool ok = true;
+    static_assert(K <= SV_NW, "a sum per wave");
     if (wv < K) {
         const double *a = va[(fa >> (4 * wv)) & 15], *b = va[(fb >> (4 * wv)) & 15];
         double v = 0.0;
 #pragma unroll
         for (int k = 0; k < RB; k += 64) v += a[k + wl] * b[k + wl];
         v = wave_sum(v);
-        if (nblk > 1) {
-            const auto slot = slots_p + ((size_t)(ex % 3) * SVF_NSUM + wv) * nblk;
-            if (wl == 0) sv_put(slot + blk, v);
-            constexpr int PB = SV_MAX_BLOCKS / 64;
-            unsigned long long x[PB];
-#pragma unroll
-            for (int u = 0; u < PB; u++)
-                if (u * 64 < nblk) x[u] = sv_get(slot + (unsigned)min(u * 64 + wl, nblk - 1));
-            double t = 0.0;
-#pragma unroll
-            for (int u = 0; u < PB; u++)
-                if (u * 64 < nblk) {
-                    const int b2 = u * 64 + wl;
-                    ok = ok && sv_wait(slot + (unsigned)min(b2, nblk - 1), x[u], pabort);
-                    t += b2 < nblk ? __longlong_as_double((long long)x[u]) : 0.0;
-                }
-            v = wave_sum(t);
-        }
         if (wl == 0) tot[wv] = v;
     }
-    return ok;
+    if (nblk == 1) return true;
+    __syncthreads();
+    if (wv == 0) sv_put(sv_line(slots_p, ex % 3, nblk, blk, wl), tot[wl & 15]);
+    return sv_collect(slots_p, ex % 3, nblk, blk, red, wv, wl, pabort);
 }
 
 // empty this block's sums of the round before (every block has read them)
 __device__ __forceinline__ void svf_clear(int wv, int wl, int nblk, int blk, int ex,
                                           __attribute__((address_space(1))) unsigned long long *slots_p)
 {
-    if (nblk > 1 && wl == 0 && wv < SVF_NSUM) sv_clear(slots_p + ((size_t)((ex + 2) % 3) * SVF_NSUM + wv) * nblk + blk);
+    if (nblk > 1 && wv == 1) sv_clear(sv_line(slots_p, (ex + 2) % 3, nblk, blk, wl));
 }
 
 template <int LPR, typename R>
 __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *segs, CgCtl ctl)
 {
     constexpr int RB = sv_rows(LPR), EPT = BK / LPR, E = sv_regs<R, LPR, 2>(), NB = SVF_REG_BONDS;
-    constexpr int NW = SV_T / 64;
-    static_assert(NW >= SVF_NSUM, "a sum per wave");
     int seg;
     const int row0 = sv_row0<RB>(tiles, segs, seg);
     if (row0 < 0) return;
@@ -92,7 +74,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     // quadratic residual, ones, the line search's A and B, J
     enum { R_ = 0, Y_, S_, Q_, M_, RO_, P_, RL_, ONE_, A_, B_, J_, NV_ };
     __shared__ double va[NV_][RB];
-    __shared__ double tot[8];
+    __shared__ double tot[SV_LINE], red[SV_NW][SV_LINE];
     __shared__ SegState st;
     __shared__ int sab;
     const int tid = threadIdx.x, rl = tid / LPR, lane = tid % LPR, row = row0 + rl, wv = uni(tid >> 6), wl = tid & 63;
@@ -101,7 +83,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     const double Q = S.Q, kq = S.fqk;
     SegState *const sst = uni(S.sst);
     int *const pabort = &sst->pabort;
-    const auto slots_y0 = sv_slots(uni(S.y)), slots_y1 = sv_slots(uni(S.hz)), slots_p = sv_slots(uni(S.p));
+    const auto slots_y0 = sv_slots(uni(S.y)), slots_y1 = sv_slots(uni(S.hz)), slots_p = sv_slots(uni((double *)S.H));
     const uint32_t *region = S.hsidx + (size_t)row0 * Wl;
     const int nh = uni((int)region[(size_t)RB * Wl - 1]);
     {
@@ -166,6 +148,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     static_assert(sizeof(SegState) % 4 == 0 && sizeof(SegState) / 4 <= SV_T, "a word per thread");
     if (tid < (int)(sizeof(SegState) / 4)) reinterpret_cast<int *>(&st)[tid] = reinterpret_cast<const int *>(sst)[tid];
     if (tid == 0) sab = 0;
+    if (tid < SV_LINE) tot[tid] = 0.0;
     if (lane == 0) {
         va[Q_][rl] = live ? S.q[row] : 0.0;
         va[RL_][rl] = live ? S.r[row] : 0.0;
@@ -198,20 +181,25 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     residual();
     if (lane == 0) va[A_][rl] = (double)cnt;
     __syncthreads();
-    bool ok = svf_sum<3, RB>(va, 0x940ull, 0x884ull, wv, wl, nblk, blk, ex, slots_p, tot, pabort);
+    bool ok = svf_sum<3, RB>(va, 0x940ull, 0x884ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
     if (!ok) sab = 1;
     __syncthreads();
     if (!sab) {
-        if (tid == 0) {
-            st.sdinv = tot[1];
-            st.w = tot[0] / tot[1];
-            st.nnz_coul = tot[2];
-            st.nnz_wide = 0.0;
-            st.nnz_halo = tot[2];
-            st.nnz_slots = (double)nblk * RB * LPR * E;
-            st.mshift = st.mu_prev - st.w;
-            st.iters = 0;
-            st.qshift = 0.0;
+        if (wv == 0) {
+            const double mine = sv_total(tot, red, nblk, wl);
+            double t[3];
+            for (int k = 0; k < 3; k++) t[k] = sv_lane(mine, k);
+            if (wl == 0) {
+                st.sdinv = t[1];
+                st.w = t[0] / t[1];
+                st.nnz_coul = t[2];
+                st.nnz_wide = 0.0;
+                st.nnz_halo = t[2];
+                st.nnz_slots = (double)nblk * RB * LPR * E;
+                st.mshift = st.mu_prev - st.w;
+                st.iters = 0;
+                st.qshift = 0.0;
+            }
         }
         svf_clear(wv, wl, nblk, blk, ex, slots_p);
         ex++;
@@ -225,20 +213,25 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         precond();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        ok = svf_sum<4, RB>(va, 0x0000ull, 0x0814ull, wv, wl, nblk, blk, ex, slots_p, tot, pabort);
+        ok = svf_sum<4, RB>(va, 0x0000ull, 0x0814ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
         if (!ok) sab = 1;
         __syncthreads();
     }
     if (!sab) {
-        if (tid == 0) {
-            const double w = tot[0] / st.sdinv, res2 = (tot[3] - tot[2] * tot[2] / n) / n;
-            st.w = w;
-            st.rho = tot[1] - w * tot[0];
-            st.beta = 0.0;
-            st.res = sqrt(fmax(res2, 0.0));
-            st.res0 = st.res;
-            st.mshift -= w;
-            st.done = st.res < ctl.tol ? 1 : 0;
+        if (wv == 0) {
+            const double mine = sv_total(tot, red, nblk, wl);
+            double t[4];
+            for (int k = 0; k < 4; k++) t[k] = sv_lane(mine, k);
+            if (wl == 0) {
+                const double w = t[0] / st.sdinv, res2 = (t[3] - t[2] * t[2] / n) / n;
+                st.w = w;
+                st.rho = t[1] - w * t[0];
+                st.beta = 0.0;
+                st.res = sqrt(fmax(res2, 0.0));
+                st.res0 = st.res;
+                st.mshift -= w;
+                st.done = st.res < ctl.tol ? 1 : 0;
+            }
         }
         svf_clear(wv, wl, nblk, blk, ex, slots_p);
         ex++;
@@ -320,21 +313,26 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         // p H p, p r, A, B
-        ok = svf_sum<4, RB>(va, 0xa966ull, 0x8802ull, wv, wl, nblk, blk, ex, slots_p, tot, pabort);
+        ok = svf_sum<4, RB>(va, 0xa966ull, 0x8802ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
         if (!ok) sab = 1;
         __syncthreads();
         if (sab) break;
-        if (tid == 0) {
-            st.ps = tot[0];
-            st.pr = tot[1];
-            st.A0 = tot[2];
-            st.alpha = 0.0;
-            const double d2 = tot[0] + tot[3];
-            if (!(d2 > 0.0) || !(st.ps > 0.0)) {
-                st.status |= ST_NOT_PD;
-                st.done = 1;
-            } else {
-                st.alpha = tot[1] / d2;
+        if (wv == 0) {
+            const double mine = sv_total(tot, red, nblk, wl);
+            double t[4];
+            for (int k = 0; k < 4; k++) t[k] = sv_lane(mine, k);
+            if (wl == 0) {
+                st.ps = t[0];
+                st.pr = t[1];
+                st.A0 = t[2];
+                st.alpha = 0.0;
+                const double d2 = t[0] + t[3];
+                if (!(d2 > 0.0) || !(st.ps > 0.0)) {
+                    st.status |= ST_NOT_PD;
+                    st.done = 1;
+                } else {
+                    st.alpha = t[1] / d2;
+                }
             }
         }
         // (every block has staged p)
@@ -346,18 +344,23 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         line(st.alpha);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        ok = svf_sum<2, RB>(va, 0xa9ull, 0x88ull, wv, wl, nblk, blk, ex, slots_p, tot, pabort);
+        ok = svf_sum<2, RB>(va, 0xa9ull, 0x88ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
         if (!ok) sab = 1;
         __syncthreads();
         if (sab) break;
-        if (tid == 0) {
-            const double d1 = -st.pr + st.alpha * st.ps + (tot[0] - st.A0), d2 = st.ps + tot[1];
-            if (!(d2 > 0.0)) {
-                st.status |= ST_NOT_PD;
-                st.done = 1;
-                st.alpha = 0.0;
-            } else {
-                st.alpha -= d1 / d2;
+        if (wv == 0) {
+            const double mine = sv_total(tot, red, nblk, wl);
+            double t[2];
+            for (int k = 0; k < 2; k++) t[k] = sv_lane(mine, k);
+            if (wl == 0) {
+                const double d1 = -st.pr + st.alpha * st.ps + (t[0] - st.A0), d2 = st.ps + t[1];
+                if (!(d2 > 0.0)) {
+                    st.status |= ST_NOT_PD;
+                    st.done = 1;
+                    st.alpha = 0.0;
+                } else {
+                    st.alpha -= d1 / d2;
+                }
             }
         }
         svf_clear(wv, wl, nblk, blk, ex, slots_p);
@@ -379,28 +382,33 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         // r m1, r y, r, r r, q, y r_old, m1 r_old
-        ok = svf_sum<7, RB>(va, 0x4130000ull, 0x5580814ull, wv, wl, nblk, blk, ex, slots_p, tot, pabort);
+        ok = svf_sum<7, RB>(va, 0x4130000ull, 0x5580814ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
         if (!ok) sab = 1;
         __syncthreads();
         if (sab) break;
-        if (tid == 0) {
-            const double w = tot[0] / st.sdinv;
-            const double rho = tot[1] - w * tot[0], cross = tot[5] - w * tot[6];
-            const double res2 = (tot[3] - tot[2] * tot[2] / n) / n;
-            const double beta = (rho - cross) / st.rho;
-            st.beta = beta > 0.0 ? beta : 0.0;
-            st.rho = rho;
-            st.w = w;
-            st.mshift -= w;
-            st.res = sqrt(fmax(res2, 0.0));
-            st.iters += 1;
-            st.iters_total += 1;
-            st.qshift = (Q - tot[4]) / n;
-            if (st.res < ctl.tol) {
-                st.done = 1;
-            } else if (st.iters >= ctl.maxit) {
-                st.done = 1;
-                st.status |= ST_NOCONV;
+        if (wv == 0) {
+            const double mine = sv_total(tot, red, nblk, wl);
+            double t[7];
+            for (int k = 0; k < 7; k++) t[k] = sv_lane(mine, k);
+            if (wl == 0) {
+                const double w = t[0] / st.sdinv;
+                const double rho = t[1] - w * t[0], cross = t[5] - w * t[6];
+                const double res2 = (t[3] - t[2] * t[2] / n) / n;
+                const double beta = (rho - cross) / st.rho;
+                st.beta = beta > 0.0 ? beta : 0.0;
+                st.rho = rho;
+                st.w = w;
+                st.mshift -= w;
+                st.res = sqrt(fmax(res2, 0.0));
+                st.iters += 1;
+                st.iters_total += 1;
+                st.qshift = (Q - t[4]) / n;
+                if (st.res < ctl.tol) {
+                    st.done = 1;
+                } else if (st.iters >= ctl.maxit) {
+                    st.done = 1;
+                    st.status |= ST_NOCONV;
+                }
             }
         }
         svf_clear(wv, wl, nblk, blk, ex, slots_p);
