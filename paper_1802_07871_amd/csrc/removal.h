@@ -73,50 +73,44 @@ int ctbop_removal_energies(ctbop_ctx *ctx, int n, const double *pos_host, const 
     ctx->last_iters.erase(sys);
     ctx->eval_gen.erase(sys);
     if (rc) return rc;
-    std::vector<double> qh(n);
-    HIPCHK(hipMemcpyAsync(qh.data(), q, 8 * (size_t)n, hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(E_host, E, sizeof(double), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (m == 0) return CTBOP_OK;
-    // leave-one-out systems, each starting from the full system's charges
+    // leave-one-out systems, each starting from the full system's charges,
+    // made on the device from the arrays at the head of the arena
+    size_t req_bytes;
+    rc = ctbop_server_request_bytes(ctx, n - 1, box, pbc, &req_bytes);
+    if (rc) return rc;
     ctbop_server *srv = nullptr;
     const int slots = std::max(1, std::min(m, REMOVAL_MAX_SLOTS));
     rc = ctbop_server_create(ctx, a + head, arena_bytes - head, slots, 8, stream, &srv);
     if (rc) return rc;
+    if (req_bytes + ctbop_server_table_bytes(srv->max_slots, srv->max_tiles) > srv->arena_bytes) {
+        ctbop_server_destroy(srv);
+        return fail(CTBOP_E_NOMEM, "request larger than the serving arena");
+    }
     std::vector<double> Ek(m, 0.0);
     std::vector<int> status(m, -1), iters(m, 0);
     std::unordered_map<long, int> which;
-    std::vector<double> xs(3 * (size_t)(n - 1)), q0(n - 1);
-    std::vector<int32_t> ts(n - 1);
     const int window = 4 * slots;              // requests pending in the server at most
     int next = 0, done = 0, err = CTBOP_OK;
     std::vector<ctbop_result> res(slots);
     while (done < m && err == CTBOP_OK) {
         while (next < m && next - done < window) {
-            const int i = cand_host[next];
-            for (int d = 0; d < 3; d++) {
-                const double *src = pos_host + (size_t)d * n;
-                double *dst = xs.data() + (size_t)d * (n - 1);
-                std::copy(src, src + i, dst);
-                std::copy(src + i + 1, src + n, dst + i);
-            }
-            std::copy(types_host, types_host + i, ts.begin());
-            std::copy(types_host + i + 1, types_host + n, ts.begin() + i);
-            std::copy(qh.begin(), qh.begin() + i, q0.begin());
-            std::copy(qh.begin() + i + 1, qh.end(), q0.begin() + i);
-            ctbop_request r;
-            memset(&r, 0, sizeof r);
+            SrvReq r;
             r.n = n - 1;
-            r.pos_host = xs.data();
-            r.types_host = ts.data();
             memcpy(r.box, box, sizeof r.box);
             for (int d = 0; d < 3; d++) r.pbc[d] = pbc[d];
-            r.total_charge = Q;
-            r.system_id = -1;
-            r.E_host = &Ek[next];
-            r.q0_host = q0.data();
+            r.Q = Q;
+            r.sys_id = -1;
+            r.x_dev = x;
+            r.types_dev = ty;
+            r.q_dev = q;
+            r.skip = cand_host[next];
+            r.E_out = &Ek[next];
+            r.F_out = r.q_out = nullptr;
             long t;
-            const int s = ctbop_server_submit(srv, &r, &t);
+            const int s = queue_request(srv, r, &t);
             if (s == CTBOP_E_BUSY) break;
             if (s) {
                 err = s;

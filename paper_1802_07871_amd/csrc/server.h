@@ -46,6 +46,11 @@ struct SrvReq {
     double Q;
     long sys_id;
     std::vector<double> q0;         // starting charges (user order), or empty
+    // or: the atoms of a system in device memory but one, with its charges as
+    // the starting charges (removal energies); read when the request is admitted
+    const double *x_dev = nullptr, *q_dev = nullptr;
+    const int32_t *types_dev = nullptr;
+    int skip = -1;
     double *E_out, *F_out, *q_out;
     double t_submit, t_admit;
 };
@@ -237,16 +242,21 @@ int admit_one(ctbop_server *S, SrvReq &r, bool &placed)
     sd.q_out = q;
     sd.E_out = E;
     sd.Q = sl.req.Q;
-    HIPCHK(hipMemcpyAsync(x, sl.req.pos.data(), 8 * 3 * (size_t)n, hipMemcpyHostToDevice, S->stream));
-    HIPCHK(hipMemcpyAsync(ty, sl.req.types.data(), 4 * (size_t)n, hipMemcpyHostToDevice, S->stream));
+    if (sl.req.x_dev) {
+        hipLaunchKernelGGL(k_leave_out, dim3(sl.L.ntile), dim3(TILE), 0, S->stream, n, sl.req.skip, sl.req.x_dev,
+                           sl.req.types_dev, sl.req.q_dev, x, ty, sd.q_state);
+    } else {
+        HIPCHK(hipMemcpyAsync(x, sl.req.pos.data(), 8 * 3 * (size_t)n, hipMemcpyHostToDevice, S->stream));
+        HIPCHK(hipMemcpyAsync(ty, sl.req.types.data(), 4 * (size_t)n, hipMemcpyHostToDevice, S->stream));
+    }
     hipLaunchKernelGGL(k_set_seg, dim3(1), dim3(1), 0, S->stream, S->dsegs + k, sd);
     if (fresh)
         hipLaunchKernelGGL(k_reset_state, dim3((sl.L.ntile + 255) / 256), dim3(256), 0, S->stream, sd.sst,
                            (Tile *)(base + iob + sl.L.off_tiles), sl.L.ntile, (int *)(base + iob + sl.L.off_segid));
     // starting charges given with the request replace the warm-start state;
     // a retained system otherwise starts from its last charges
-    const bool given = !sl.req.q0.empty();
-    if (given)
+    const bool given = !sl.req.q0.empty() || sl.req.x_dev;
+    if (!sl.req.q0.empty())
         HIPCHK(hipMemcpyAsync(sd.q_state, sl.req.q0.data(), 8 * (size_t)n, hipMemcpyHostToDevice, S->stream));
     hipLaunchKernelGGL(k_set_warm, dim3(1), dim3(1), 0, S->stream, sd.sst, (fresh && !given) ? 0 : 1);
     HIPCHK(hipGetLastError());
@@ -474,6 +484,22 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
     return CTBOP_OK;
 }
 
+// into the queue, for the next tick
+int queue_request(ctbop_server *S, SrvReq &r, long *ticket)
+{
+    r.t_submit = now_s();
+    {
+        std::lock_guard<std::mutex> lk(S->mu);
+        if (S->stop) return fail(S->error ? S->error : CTBOP_E_INVAL, "server stopped: " + S->errmsg);
+        if (S->pending.size() >= S->max_pending) return fail(CTBOP_E_BUSY, "pending queue full");
+        r.ticket = S->next_ticket++;
+        if (ticket) *ticket = r.ticket;
+        S->pending.push_back(std::move(r));
+    }
+    S->cv.notify_all();
+    return CTBOP_OK;
+}
+
 // the server's stream, events and pinned tables (whichever exist)
 void release_handles(ctbop_server *S)
 {
@@ -633,17 +659,7 @@ int ctbop_server_submit(ctbop_server *S, const ctbop_request *rq, long *ticket)
     r.E_out = rq->E_host;
     r.F_out = rq->F_host;
     r.q_out = rq->q_host;
-    r.t_submit = now_s();
-    {
-        std::lock_guard<std::mutex> lk(S->mu);
-        if (S->stop) return fail(S->error ? S->error : CTBOP_E_INVAL, "server stopped: " + S->errmsg);
-        if (S->pending.size() >= S->max_pending) return fail(CTBOP_E_BUSY, "pending queue full");
-        r.ticket = S->next_ticket++;
-        if (ticket) *ticket = r.ticket;
-        S->pending.push_back(std::move(r));
-    }
-    S->cv.notify_all();
-    return CTBOP_OK;
+    return queue_request(S, r, ticket);
 }
 
 int ctbop_server_poll(ctbop_server *S, ctbop_result *out, int max, double wait_s, int *n_done)
