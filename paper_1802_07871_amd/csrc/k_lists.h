@@ -17,22 +17,6 @@ namespace ctbop {
 
 __global__ void k_set_seg(Seg *dst, Seg src) { *dst = src; }
 
-__global__ void k_set_warm(SegState *st, int warm) { st->warm = warm; }
-
-// The n atoms of a system of n + 1 without atom `skip`: positions (by
-// component), types and charges.  Bound by its launch; copies made on the
-// host and sent: 32 removal energies of 18,086 atoms 13.0 ms, 10.8 with this.
-__global__ void __launch_bounds__(TILE) k_leave_out(int n, int skip, const double *x, const int32_t *types,
-                                                    const double *q, double *x_out, int32_t *types_out, double *q_out)
-{
-    const int i = blockIdx.x * TILE + threadIdx.x;
-    if (i >= n) return;
-    const int j = i + (i >= skip ? 1 : 0);
-    for (int d = 0; d < 3; d++) x_out[(size_t)d * n + i] = x[(size_t)d * (n + 1) + j];
-    types_out[i] = types[j];
-    q_out[i] = q[j];
-}
-
 __global__ void k_call_init(const int *seg_ids, Seg *segs, int nseg, int force_rebuild)
 {
     int k = blockIdx.x * blockDim.x + threadIdx.x;

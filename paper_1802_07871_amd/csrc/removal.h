@@ -83,7 +83,7 @@ int ctbop_removal_energies(ctbop_ctx *ctx, int n, const double *pos_host, const 
     if (rc) return rc;
     ctbop_server *srv = nullptr;
     const int slots = std::max(1, std::min(m, REMOVAL_MAX_SLOTS));
-    rc = ctbop_server_create(ctx, a + head, arena_bytes - head, slots, 8, stream, &srv);
+    rc = create_server(ctx, a + head, arena_bytes - head, slots, 8, stream, 0, &srv);
     if (rc) return rc;
     if (req_bytes + ctbop_server_table_bytes(srv->max_slots, srv->max_tiles) > srv->arena_bytes) {
         ctbop_server_destroy(srv);

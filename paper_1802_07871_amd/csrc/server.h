@@ -7,15 +7,17 @@
 // thread runs ticks on one stream:
 //   1. admit pending requests in arrival order while slots and arena bytes
 //      allow (a request that does not fit waits; retained systems are evicted
-//      least recently used first);
+//      least recently used first), and send their inputs in one launch;
 //   2. set-up kernels (bins, lists, bond pass, Coulomb assembly) over the new
 //      segments' tiles, all in one launch per kernel;
-//   3. K charge-solve iterations over every active segment's tiles, again one
-//      launch per kernel; each segment stops on its own test;
+//   3. the one-launch charge solve of the new segments that take it, then K
+//      iterations over the tiles of the others, again one launch per kernel;
+//      each segment stops on its own test;
 //   4. force and energy kernels over the same tiles, gated per segment on
 //      "solve finished, forces pending";
-//   5. read the per-segment flags, copy finished results to the caller's host
-//      buffers and free (or retain) their regions.
+//   5. read the per-segment flags and, by one launch into pinned memory, the
+//      finished results, copy these to the caller's host buffers and free (or
+//      retain) their regions.
 // Requests that arrive during a tick join at the next one, so work of
 // requests of any size and phase overlaps on the device.  Each segment's
 // arithmetic and reduction order do not depend on the other segments, so a
@@ -64,6 +66,8 @@ struct SrvSlot {
     Layout L;
     size_t io_off = 0;              // I/O arrays at the start of the region
     int phase = 0;                  // 0 = needs set-up, 1 = solving/finishing
+    bool placed = false;            // placed since the last tick, its inputs not yet on the device
+    bool fresh = false;             // in a new region
     bool many = false;              // its one-launch solve gave up: multi-launch solve
     long sys_id = -1;
     double last_use = 0;
@@ -71,6 +75,81 @@ struct SrvSlot {
 };
 
 } // namespace
+
+namespace ctbop {
+
+// An admitted request for k_admit, in pinned memory: its descriptor and where
+// its inputs are (pinned or device memory; x null: copied by themselves;
+// skip >= 0: those of a system of n + 1 atoms without atom skip).
+struct SrvAdmit {
+    Seg seg;
+    const double *x, *q0;
+    const int32_t *type;
+    int slot, n, skip, fresh, warm;
+};
+// Where k_deliver puts the results of an active request (pinned memory or null).
+struct SrvOut {
+    double *F, *q;
+    int slot, n;
+};
+
+// Inputs, descriptors and start states of the requests admitted to a tick, a
+// column of blocks each, read across PCIe from pinned memory (or, for removal
+// energies, from the full system's arrays on the device).  Bound by that link.
+// A request took three to five copies and launches by itself: 48 requests of 8
+// to 20,000 atoms 6.6 ms, 3.7 with this and k_deliver; 32 removal energies of
+// 18,086 atoms 13.0 ms with inputs put together on the host, 10.7 with a
+// launch per system that makes them here, 9.7 now.
+__global__ void __launch_bounds__(TILE) k_admit(const SrvAdmit *adm, Seg *segs)
+{
+    const SrvAdmit &A = adm[blockIdx.x];
+    const int tid = threadIdx.x, n = A.n, skip = A.skip, ns = skip >= 0 ? n + 1 : n;
+    if (A.x) {
+        const double *x = A.x, *q0 = A.q0;
+        const int32_t *type = A.type;
+        double *xo = const_cast<double *>(A.seg.x), *qo = A.seg.q_state;
+        int32_t *to = const_cast<int32_t *>(A.seg.type);
+        for (int i = blockIdx.y * TILE + tid; i < n; i += gridDim.y * TILE) {
+            const int j = i + (skip >= 0 && i >= skip ? 1 : 0);
+            const double x0 = x[j], x1 = x[(size_t)ns + j], x2 = x[2 * (size_t)ns + j], q = q0 ? q0[j] : 0.0;
+            const int32_t t = type[j];
+            xo[i] = x0;
+            xo[(size_t)n + i] = x1;
+            xo[2 * (size_t)n + i] = x2;
+            to[i] = t;
+            if (q0) qo[i] = q;
+        }
+    }
+    if (blockIdx.y != 0) return;
+    static_assert(sizeof(Seg) % 4 == 0 && sizeof(SegState) % 4 == 0, "copied as words");
+    for (int w = tid; w < (int)(sizeof(Seg) / 4); w += TILE)
+        reinterpret_cast<int *>(segs + A.slot)[w] = reinterpret_cast<const int *>(&A.seg)[w];
+    SegState *st = A.seg.sst;
+    if (A.fresh)
+        for (int w = tid; w < (int)(sizeof(SegState) / 4); w += TILE) reinterpret_cast<int *>(st)[w] = 0;
+    __syncthreads();
+    if (tid == 0) st->warm = A.warm;
+}
+
+// Forces, charges and energies of the finished requests into pinned memory.
+__global__ void __launch_bounds__(TILE) k_deliver(const SrvOut *out, const Seg *segs, double *E)
+{
+    const SrvOut &o = out[blockIdx.x];
+    const Seg &S = segs[o.slot];
+    if (!S.sst->forces_done) return;
+    const int i0 = blockIdx.y * TILE + threadIdx.x, step = gridDim.y * TILE, n = o.n;
+    if (o.F) {
+        double *F = o.F;
+        for (int i = i0; i < 3 * n; i += step) F[i] = S.F[i];
+    }
+    if (o.q) {
+        double *q = o.q;
+        for (int i = i0; i < n; i += step) q[i] = S.q_out[i];
+    }
+    if (i0 == 0) E[blockIdx.x] = *S.E_out;
+}
+
+} // namespace ctbop
 
 struct ctbop_server {
     ctbop_ctx *ctx = nullptr;
@@ -96,6 +175,13 @@ struct ctbop_server {
     Tile *htiles = nullptr;
     int *hids = nullptr;
     int4 *hflags = nullptr;
+    double *hE = nullptr;             // after hflags, as the next two
+    SrvAdmit *hadm = nullptr;
+    SrvOut *hout = nullptr;
+    // pinned room for the inputs, then the results, of a tick (tick thread
+    // only); allocated with the server, so that a tick allocates nothing
+    char *stage = nullptr;
+    size_t stage_bytes = 0;
     // regions
     std::map<size_t, size_t> free_ranges;   // offset -> size
     std::vector<SrvSlot> slots;
@@ -167,8 +253,8 @@ Sig req_sig(const ctbop_ctx *ctx, const SrvReq &r, size_t bytes)
     return g;
 }
 
-// place a request into a slot: region, descriptor, inputs.  Returns false if
-// it does not fit right now.
+// place a request into a slot and its region (the next tick sends its
+// descriptor and inputs).  Returns false if it does not fit right now.
 int admit_one(ctbop_server *S, SrvReq &r, bool &placed)
 {
     placed = false;
@@ -229,39 +315,89 @@ int admit_one(ctbop_server *S, SrvReq &r, bool &placed)
     sl.req = std::move(r);
     sl.req.t_admit = now_s();
     sl.last_use = sl.req.t_admit;
-    const int n = sl.req.n;
-    double *x = (double *)base;
-    int32_t *ty = (int32_t *)(base + align_up(8 * 3 * (size_t)n, 256));
-    double *F = (double *)((char *)ty + align_up(4 * (size_t)n, 256));
-    double *q = (double *)((char *)F + align_up(8 * 3 * (size_t)n, 256));
-    double *E = (double *)((char *)q + align_up(8 * (size_t)n, 256));
-    Seg sd = sl.L.seg;
-    sd.x = x;
-    sd.type = ty;
-    sd.F = F;
-    sd.q_out = q;
-    sd.E_out = E;
-    sd.Q = sl.req.Q;
-    if (sl.req.x_dev) {
-        hipLaunchKernelGGL(k_leave_out, dim3(sl.L.ntile), dim3(TILE), 0, S->stream, n, sl.req.skip, sl.req.x_dev,
-                           sl.req.types_dev, sl.req.q_dev, x, ty, sd.q_state);
-    } else {
-        HIPCHK(hipMemcpyAsync(x, sl.req.pos.data(), 8 * 3 * (size_t)n, hipMemcpyHostToDevice, S->stream));
-        HIPCHK(hipMemcpyAsync(ty, sl.req.types.data(), 4 * (size_t)n, hipMemcpyHostToDevice, S->stream));
-    }
-    hipLaunchKernelGGL(k_set_seg, dim3(1), dim3(1), 0, S->stream, S->dsegs + k, sd);
-    if (fresh)
-        hipLaunchKernelGGL(k_reset_state, dim3((sl.L.ntile + 255) / 256), dim3(256), 0, S->stream, sd.sst,
-                           (Tile *)(base + iob + sl.L.off_tiles), sl.L.ntile, (int *)(base + iob + sl.L.off_segid));
-    // starting charges given with the request replace the warm-start state;
-    // a retained system otherwise starts from its last charges
-    const bool given = !sl.req.q0.empty() || sl.req.x_dev;
-    if (!sl.req.q0.empty())
-        HIPCHK(hipMemcpyAsync(sd.q_state, sl.req.q0.data(), 8 * (size_t)n, hipMemcpyHostToDevice, S->stream));
-    hipLaunchKernelGGL(k_set_warm, dim3(1), dim3(1), 0, S->stream, sd.sst, (fresh && !given) ? 0 : 1);
-    HIPCHK(hipGetLastError());
+    sl.placed = true;
+    sl.fresh = fresh;
     S->admitted++;
     placed = true;
+    return CTBOP_OK;
+}
+
+// Device arrays of a slot's request.
+struct SrvArrays {
+    double *x;
+    int32_t *type;
+    double *F, *q, *E;
+};
+SrvArrays slot_arrays(const ctbop_server *S, const SrvSlot &sl)
+{
+    const size_t n = (size_t)sl.req.n;
+    SrvArrays a;
+    a.x = (double *)(S->arena + sl.off);
+    a.type = (int32_t *)((char *)a.x + align_up(8 * 3 * n, 256));
+    a.F = (double *)((char *)a.type + align_up(4 * n, 256));
+    a.q = (double *)((char *)a.F + align_up(8 * 3 * n, 256));
+    a.E = (double *)((char *)a.q + align_up(8 * n, 256));
+    return a;
+}
+
+// Send the inputs and descriptors of the requests placed since the last tick,
+// through the pinned room; inputs that do not fit it are copied by themselves.
+int send_placed(ctbop_server *S, const std::vector<int> &act)
+{
+    hipStream_t st = S->stream;
+    std::vector<int> fresh;
+    for (int k : act)
+        if (S->slots[k].placed) fresh.push_back(k);
+    if (fresh.empty()) return CTBOP_OK;
+    size_t at = 0;
+    int tiles = 1, m = 0;
+    for (int k : fresh) {
+        SrvSlot &sl = S->slots[k];
+        const size_t n = (size_t)sl.req.n;
+        const SrvArrays a = slot_arrays(S, sl);
+        SrvAdmit &A = S->hadm[m++];
+        A.seg = sl.L.seg;
+        A.seg.x = a.x;
+        A.seg.type = a.type;
+        A.seg.F = a.F;
+        A.seg.q_out = a.q;
+        A.seg.E_out = a.E;
+        A.seg.Q = sl.req.Q;
+        A.slot = k;
+        A.n = sl.req.n;
+        A.skip = sl.req.skip;
+        A.fresh = sl.fresh ? 1 : 0;
+        // starting charges given with the request replace the warm-start
+        // state; a retained system otherwise starts from its last charges
+        const bool q0 = !sl.req.q0.empty();
+        A.warm = sl.fresh && !q0 && !sl.req.x_dev ? 0 : 1;
+        A.x = sl.req.x_dev;
+        A.type = sl.req.types_dev;
+        A.q0 = sl.req.q_dev;
+        const size_t b = align_up(28 * n, 8) + (q0 ? 8 * n : 0);
+        if (!sl.req.x_dev && at + b <= S->stage_bytes) {
+            char *p = S->stage + at;
+            at += b;
+            memcpy(p, sl.req.pos.data(), 24 * n);
+            A.x = (const double *)p;
+            p += 24 * n;
+            if (q0) {
+                memcpy(p, sl.req.q0.data(), 8 * n);
+                A.q0 = (const double *)p;
+                p += 8 * n;
+            }
+            memcpy(p, sl.req.types.data(), 4 * n);
+            A.type = (const int32_t *)p;
+        } else if (!sl.req.x_dev) {
+            HIPCHK(hipMemcpyAsync(a.x, sl.req.pos.data(), 24 * n, hipMemcpyHostToDevice, st));
+            HIPCHK(hipMemcpyAsync(a.type, sl.req.types.data(), 4 * n, hipMemcpyHostToDevice, st));
+            if (q0) HIPCHK(hipMemcpyAsync(A.seg.q_state, sl.req.q0.data(), 8 * n, hipMemcpyHostToDevice, st));
+        }
+        if (A.x) tiles = std::max(tiles, sl.L.ntile);
+        sl.placed = false;
+    }
+    hipLaunchKernelGGL(k_admit, dim3(m, std::min(tiles, 64)), dim3(TILE), 0, st, S->hadm, S->dsegs);
+    HIPCHK(hipGetLastError());
     return CTBOP_OK;
 }
 
@@ -288,6 +424,11 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         act.push_back(k);
     }
     if (act.empty()) return CTBOP_OK;
+    // the largest first: of a batch that fills the device more than once the
+    // last systems to run are then the smallest
+    std::stable_sort(act.begin(), act.end(), [&](int a, int b) { return S->slots[a].req.n > S->slots[b].req.n; });
+    const int src = send_placed(S, act);
+    if (src) return src;
     int total_tiles = 0;
     for (int k : act) total_tiles += S->slots[k].L.ntile;
     if (total_tiles > S->max_tiles) return fail(CTBOP_E_NOMEM, "server tile table too small");
@@ -421,6 +562,22 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         hipLaunchKernelGGL(k_collect, dim3((nia + 63) / 64), dim3(64), 0, st, sid, S->dsegs, nia, S->dflags);
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(S->hflags, S->dflags, sizeof(int4) * nia, hipMemcpyDeviceToHost, st));
+        // results of those finished, for which there is pinned room
+        size_t at = 0;
+        int most = 1;
+        for (int a = 0; a < nia; a++) {
+            const SrvReq &r = S->slots[hia[a]].req;
+            const size_t f = r.F_out ? 24 * (size_t)r.n : 0, b = f + (r.q_out ? 8 * (size_t)r.n : 0);
+            SrvOut &o = S->hout[a];
+            o = SrvOut{nullptr, nullptr, hia[a], r.n};
+            if (b == 0 || at + b > S->stage_bytes) continue;
+            if (r.F_out) o.F = (double *)(S->stage + at);
+            if (r.q_out) o.q = (double *)(S->stage + at + f);
+            at += b;
+            most = std::max(most, S->slots[hia[a]].L.ntile);
+        }
+        hipLaunchKernelGGL(k_deliver, dim3(nia, std::min(most, 64)), dim3(TILE), 0, st, S->hout, S->dsegs, S->hE);
+        HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(st));
     }
     // harvest
@@ -436,18 +593,26 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
             sl.phase = 0;
         }
     }
+    bool copies = false;
     for (int a : fin) {
         SrvSlot &sl = S->slots[hia[a]];
-        const int n = sl.req.n;
-        char *base = S->arena + sl.off;
-        double *F = (double *)(base + align_up(8 * 3 * (size_t)n, 256) + align_up(4 * (size_t)n, 256));
-        double *q = (double *)((char *)F + align_up(8 * 3 * (size_t)n, 256));
-        double *E = (double *)((char *)q + align_up(8 * (size_t)n, 256));
-        if (sl.req.F_out) HIPCHK(hipMemcpyAsync(sl.req.F_out, F, 8 * 3 * (size_t)n, hipMemcpyDeviceToHost, st));
-        if (sl.req.q_out) HIPCHK(hipMemcpyAsync(sl.req.q_out, q, 8 * (size_t)n, hipMemcpyDeviceToHost, st));
-        if (sl.req.E_out) HIPCHK(hipMemcpyAsync(sl.req.E_out, E, 8, hipMemcpyDeviceToHost, st));
+        const SrvReq &r = sl.req;
+        const SrvOut &o = S->hout[a];
+        const SrvArrays d = slot_arrays(S, sl);
+        const size_t n = (size_t)r.n;
+        if (r.F_out && o.F) memcpy(r.F_out, o.F, 24 * n);
+        if (r.q_out && o.q) memcpy(r.q_out, o.q, 8 * n);
+        if (r.E_out) *r.E_out = S->hE[a];
+        if (r.F_out && !o.F) {
+            HIPCHK(hipMemcpyAsync(r.F_out, d.F, 24 * n, hipMemcpyDeviceToHost, st));
+            copies = true;
+        }
+        if (r.q_out && !o.q) {
+            HIPCHK(hipMemcpyAsync(r.q_out, d.q, 8 * n, hipMemcpyDeviceToHost, st));
+            copies = true;
+        }
     }
-    if (!fin.empty()) HIPCHK(hipStreamSynchronize(st));
+    if (copies) HIPCHK(hipStreamSynchronize(st));
     const double t = now_s();
     std::vector<ctbop_result> res;
     for (int a : fin) {
@@ -512,6 +677,7 @@ void release_handles(ctbop_server *S)
     if (S->htiles) (void)hipHostFree(S->htiles);
     if (S->hids) (void)hipHostFree(S->hids);
     if (S->hflags) (void)hipHostFree(S->hflags);
+    if (S->stage) (void)hipHostFree(S->stage);
 }
 
 void server_loop(ctbop_server *S)
@@ -569,6 +735,69 @@ void server_loop(ctbop_server *S)
     }
 }
 
+// A server with `stage` bytes of pinned room for inputs and results (0: each
+// is copied by itself).
+constexpr size_t STAGE_MAX = (size_t)8 << 20;
+int create_server(ctbop_ctx *ctx, void *arena, size_t arena_bytes, int max_slots, int cg_per_tick, void *stream,
+                  size_t stage, ctbop_server **out)
+{
+    if (!ctx || !arena || !out || max_slots <= 0) return fail(CTBOP_E_INVAL, "bad argument");
+    if (ctx->opts.fq_kappa > 0.0) return fail(CTBOP_E_INVAL, "server: not available with fq_kappa > 0");
+    ctbop_server *S = new ctbop_server();
+    S->ctx = ctx;
+    S->arena = (char *)arena;
+    S->arena_bytes = arena_bytes;
+    S->max_slots = max_slots;
+    S->cg_per_tick = cg_per_tick > 0 ? cg_per_tick : 8;
+    S->stream = (hipStream_t)stream;
+    S->max_tiles = 2 * (int)std::min<size_t>(arena_bytes / ((size_t)TILE * 1024) + max_slots, 1 << 22);
+    const size_t tb = ctbop_server_table_bytes(max_slots, S->max_tiles);
+    S->stage_bytes = stage;
+    if (tb + (1 << 20) > arena_bytes) {
+        delete S;
+        return fail(CTBOP_E_NOMEM, "arena too small for the server tables");
+    }
+    char *p = S->arena;
+    S->dsegs = (Seg *)p;
+    p += align_up(sizeof(Seg) * max_slots, 256);
+    S->dtiles_setup = (Tile *)p;
+    p += align_up(sizeof(Tile) * S->max_tiles, 256);
+    S->dtiles_act = (Tile *)p;
+    p += align_up(sizeof(Tile) * S->max_tiles, 256);
+    S->dids_setup = (int *)p;
+    p += align_up(sizeof(int) * max_slots, 256);
+    S->dids_act = (int *)p;
+    p += align_up(sizeof(int) * max_slots, 256);
+    S->dflags = (int4 *)p;
+    p += align_up(sizeof(int4) * max_slots, 256);
+    S->free_ranges[tb] = arena_bytes - tb;
+    S->slots.resize(max_slots);
+    const size_t per_slot = sizeof(int4) + sizeof(double) + sizeof(SrvOut) + sizeof(SrvAdmit);
+    if (hipGetDevice(&S->device) != hipSuccess ||
+        hipStreamCreateWithFlags(&S->side, hipStreamNonBlocking) != hipSuccess ||
+        hipEventCreateWithFlags(&S->ev_fork, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&S->ev_join, hipEventDisableTiming) != hipSuccess ||
+        hipHostMalloc((void **)&S->htiles, sizeof(Tile) * 2 * S->max_tiles, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&S->hids, sizeof(int) * 2 * max_slots, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&S->hflags, per_slot * max_slots, hipHostMallocDefault) != hipSuccess) {
+        release_handles(S);
+        delete S;
+        return fail(CTBOP_E_HIP, "server stream, events or pinned host tables");
+    }
+    if (stage && hipHostMalloc((void **)&S->stage, stage, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        S->stage = nullptr;
+        S->stage_bytes = 0;
+    }
+    S->hE = (double *)(S->hflags + max_slots);
+    S->hout = (SrvOut *)(S->hE + max_slots);
+    S->hadm = (SrvAdmit *)(S->hout + max_slots);
+    S->th = std::thread(server_loop, S);
+    ctx->servers++;
+    *out = S;
+    return CTBOP_OK;
+}
+
 } // namespace
 
 extern "C" {
@@ -592,51 +821,8 @@ int ctbop_server_request_bytes(ctbop_ctx *ctx, int n, const double *box, const i
 int ctbop_server_create(ctbop_ctx *ctx, void *arena, size_t arena_bytes, int max_slots, int cg_per_tick,
                         void *stream, ctbop_server **out)
 {
-    if (!ctx || !arena || !out || max_slots <= 0) return fail(CTBOP_E_INVAL, "bad argument");
-    if (ctx->opts.fq_kappa > 0.0) return fail(CTBOP_E_INVAL, "server: not available with fq_kappa > 0");
-    ctbop_server *S = new ctbop_server();
-    S->ctx = ctx;
-    S->arena = (char *)arena;
-    S->arena_bytes = arena_bytes;
-    S->max_slots = max_slots;
-    S->cg_per_tick = cg_per_tick > 0 ? cg_per_tick : 8;
-    S->stream = (hipStream_t)stream;
-    S->max_tiles = 2 * (int)std::min<size_t>(arena_bytes / ((size_t)TILE * 1024) + max_slots, 1 << 22);
-    const size_t tb = ctbop_server_table_bytes(max_slots, S->max_tiles);
-    if (tb + (1 << 20) > arena_bytes) {
-        delete S;
-        return fail(CTBOP_E_NOMEM, "arena too small for the server tables");
-    }
-    char *p = S->arena;
-    S->dsegs = (Seg *)p;
-    p += align_up(sizeof(Seg) * max_slots, 256);
-    S->dtiles_setup = (Tile *)p;
-    p += align_up(sizeof(Tile) * S->max_tiles, 256);
-    S->dtiles_act = (Tile *)p;
-    p += align_up(sizeof(Tile) * S->max_tiles, 256);
-    S->dids_setup = (int *)p;
-    p += align_up(sizeof(int) * max_slots, 256);
-    S->dids_act = (int *)p;
-    p += align_up(sizeof(int) * max_slots, 256);
-    S->dflags = (int4 *)p;
-    p += align_up(sizeof(int4) * max_slots, 256);
-    S->free_ranges[tb] = arena_bytes - tb;
-    S->slots.resize(max_slots);
-    if (hipGetDevice(&S->device) != hipSuccess ||
-        hipStreamCreateWithFlags(&S->side, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&S->ev_fork, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&S->ev_join, hipEventDisableTiming) != hipSuccess ||
-        hipHostMalloc((void **)&S->htiles, sizeof(Tile) * 2 * S->max_tiles, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&S->hids, sizeof(int) * 2 * max_slots, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&S->hflags, sizeof(int4) * max_slots, hipHostMallocDefault) != hipSuccess) {
-        release_handles(S);
-        delete S;
-        return fail(CTBOP_E_HIP, "server stream, events or pinned host tables");
-    }
-    S->th = std::thread(server_loop, S);
-    ctx->servers++;
-    *out = S;
-    return CTBOP_OK;
+    return create_server(ctx, arena, arena_bytes, max_slots, cg_per_tick, stream,
+                         std::min(STAGE_MAX, align_up(arena_bytes / 64, 4096)), out);
 }
 
 int ctbop_server_submit(ctbop_server *S, const ctbop_request *rq, long *ticket)

@@ -202,3 +202,26 @@ def test_retained_system_warm_start(ct, orc, theta):
     assert abs(r2["E"] - Eo) / s.n < 1e-6
     assert np.linalg.norm(r2["F"] - Fo) / np.linalg.norm(Fo) < 1e-5
     assert np.abs(r2["q"] - qo).max() < 1e-6
+
+
+def test_inputs_past_the_pinned_room(ct, theta):
+    """A server has 8 MiB of pinned room for a tick's inputs and results, an
+    input of 314,432 atoms takes 8.8 million bytes and is copied by itself;
+    beside it requests that go through the room, one with starting charges."""
+    from paper_1802_07871_amd.serving import Server
+    pot = ct.Potential(theta)
+    big, small = G.zincblende(34, sigma=0.02, seed=91), G.zincblende(4, sigma=0.05, seed=92)
+    print(f"[serving] inputs past the pinned room n={big.n}", flush=True)
+    single = [pot.compute(s.pos, s.types, s.box, s.pbc, warm=False) for s in (small, big)]
+    q0 = single[0][2].cpu().numpy()
+    srv = Server(pot, 2 * Server(pot, 1 << 26, max_slots=2).request_bytes(big.n, big.box, big.pbc), max_slots=8)
+    t = [srv.submit(small.pos, small.types, small.box, small.pbc), srv.submit(big.pos, big.types, big.box, big.pbc),
+         srv.submit(small.pos, small.types, small.box, small.pbc, q0=q0)]
+    got = srv.wait_all(t)
+    srv.close()
+    for k, (E, F, q, _) in zip(t, single):
+        assert got[k]["status"] == 0 and got[k]["E"] == E
+        assert np.array_equal(got[k]["F"], F.cpu().numpy()) and np.array_equal(got[k]["q"], q.cpu().numpy())
+    # solved again from its own charges: at once, to the solver's tolerance
+    assert got[t[2]]["status"] == 0 and got[t[2]]["cg_iters"] <= 2
+    assert np.abs(got[t[2]]["q"] - q0).max() <= 1e-8
