@@ -151,9 +151,9 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
     // source a (whose scale is the caller's)
     int *flag = ctx->host_flag;
     bool solved = false;
-    if (const int lpr = solve_lpr(ctx, P.L.seg.n)) {
-        launch_solve_prep<R>(lpr, P.dtiles, P.L.ntile, dadj, st);
-        launch_solve<R>(lpr, ctx->ncu, P.dtiles, P.L.ntile, dadj, SolveCtl{ctx->opts.cg_tol, ctx->opts.cg_maxit, 1}, st);
+    if (const int kind = solve_kind(ctx, P.L.seg.n)) {
+        launch_solve_prep<R>(kind, P.dtiles, P.L.ntile, dadj, st);
+        launch_solve<R>(kind, ctx->ncu, P.dtiles, P.L.ntile, dadj, SolveCtl{ctx->opts.cg_tol, ctx->opts.cg_maxit, 1}, st);
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(flag, &asst->done, 3 * sizeof(int), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));

@@ -529,15 +529,21 @@ int start_mode(const Prep &P, int flags)
     return (flags & CTBOP_FLAG_EXTRAPOLATE) ? 2 : 1;
 }
 
-// Lanes per row of the one-launch charge solve for a system of n atoms, 0
-// where the multi-launch solve runs.  The rule is on n alone (and the
-// device), so a system is solved alike alone and in the server: the blocks of
-// one system have to be on the device together, one per CU.  Up to 64 rows a
-// CU take 8 lanes per row, up to SV_MAX_ATOMS (16-bit halo positions, a
-// bitmap of all rows in LDS) 4 lanes.
-int solve_lpr(ctbop_ctx *ctx, int n)
+// Kind of the one-launch charge solve for a system of n atoms: 8 or 4 lanes
+// per row in blocks of SV_T threads, SV_WIDE for 4 lanes per row in blocks of
+// SV_TW, 0 where the multi-launch solve runs.  The rule is on n alone (and
+// the device), so a system is solved alike alone and in the server: the blocks
+// of one system have to be on the device together, one per CU.  Up to 64 rows
+// a CU take 8 lanes per row, up to SV_MAX_ATOMS 4, up to SV_MAX_ATOMS_W the
+// larger blocks (an evaluation of 48,640 atoms 2.26 ms in two launches per
+// iteration, 1.48 with them).  The lines at 128 and 192 tiles are not of speed
+// (53,760 atoms would take 1.52 ms for 2.40): the multi-launch solve's 16-bit
+// offsets and full entries are checked on systems of 32,768 and 50,240 atoms,
+// which have to reach it.
+constexpr int SV_WIDE = 1;
+int solve_kind(ctbop_ctx *ctx, int n)
 {
-    if (n > SV_MAX_ATOMS || ctx->opts.long_cap < SV_MIN_WL) return 0;
+    if (n > SV_MAX_ATOMS_W || ctx->opts.long_cap < SV_MIN_WL) return 0;
     if (ctx->ncu == 0) {
         int dev = 0, ncu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
@@ -546,31 +552,38 @@ int solve_lpr(ctbop_ctx *ctx, int n)
         ctx->ncu = std::min(ncu, SV_MAX_BLOCKS);
     }
     if (n <= sv_rows(8) * ctx->ncu) return 8;
-    return n <= sv_rows(4) * ctx->ncu ? 4 : 0;
+    if (n <= std::min(sv_rows(4) * ctx->ncu, SV_MAX_ATOMS)) return 4;
+    return n > 128 * TILE && 4 * n <= 3 * sv_rows(4, SV_TW) * ctx->ncu ? SV_WIDE : 0;
 }
+// the list build of the system leaves out the tiles' halos
+bool fine_lists(int kind) { return kind == 8 || kind == 4; }
 
-// The one-launch solve over nt tiles of systems of one solve_lpr class, and
-// the kernel that prepares it.
+// The one-launch solve over nt tiles of systems of one kind, and the kernel
+// that prepares it.
 template <typename R>
-void launch_solve_prep(int lpr, const Tile *tiles, int nt, Seg *segs, hipStream_t st)
+void launch_solve_prep(int kind, const Tile *tiles, int nt, Seg *segs, hipStream_t st)
 {
-    const dim3 b(SV_T);
-    if (lpr == 8) hipLaunchKernelGGL((k_solve_prep<8, R>), dim3(nt * (TILE / sv_rows(8))), b, 0, st, tiles, segs);
-    else hipLaunchKernelGGL((k_solve_prep<4, R>), dim3(nt * (TILE / sv_rows(4))), b, 0, st, tiles, segs);
+    if (kind == 8)
+        hipLaunchKernelGGL((k_solve_prep<8, R, SV_T>), dim3(nt * (TILE / sv_rows(8))), dim3(SV_T), 0, st, tiles, segs);
+    else if (kind == 4)
+        hipLaunchKernelGGL((k_solve_prep<4, R, SV_T>), dim3(nt * (TILE / sv_rows(4))), dim3(SV_T), 0, st, tiles, segs);
+    else hipLaunchKernelGGL((k_solve_prep<4, R, SV_TW>), dim3(nt), dim3(SV_TW), 0, st, tiles, segs);
 }
 template <typename R>
-void launch_solve(int lpr, int ncu, const Tile *tiles, int nt, Seg *segs, SolveCtl ctl, hipStream_t st)
+void launch_solve(int kind, int ncu, const Tile *tiles, int nt, Seg *segs, SolveCtl ctl, hipStream_t st)
 {
-    const int rb = sv_rows(lpr), nb = nt * (TILE / rb);
+    const int rb = kind == SV_WIDE ? TILE : sv_rows(kind), nb = nt * (TILE / rb);
     const dim3 g(nb), b(SV_T);
     // more blocks than CUs (a batch of systems): the build with two blocks
     // per CU, the same arithmetic in fewer registers
     const bool two = sizeof(R) == 4 && nb > ncu;
     constexpr int OCC2 = sizeof(R) == 4 ? 4 : 2;
-    if (lpr == 8 && two) hipLaunchKernelGGL((k_solve<8, R, OCC2>), g, b, 0, st, tiles, segs, ctl);
-    else if (lpr == 8) hipLaunchKernelGGL((k_solve<8, R, 2>), g, b, 0, st, tiles, segs, ctl);
-    else if (two) hipLaunchKernelGGL((k_solve<4, R, OCC2>), g, b, 0, st, tiles, segs, ctl);
-    else hipLaunchKernelGGL((k_solve<4, R, 2>), g, b, 0, st, tiles, segs, ctl);
+    static_assert(sv_rows(4, SV_TW) == TILE, "a tile per block");
+    if (kind == SV_WIDE) hipLaunchKernelGGL((k_solve<4, R, 4, SV_TW>), g, dim3(SV_TW), 0, st, tiles, segs, ctl);
+    else if (kind == 8 && two) hipLaunchKernelGGL((k_solve<8, R, OCC2, SV_T>), g, b, 0, st, tiles, segs, ctl);
+    else if (kind == 8) hipLaunchKernelGGL((k_solve<8, R, 2, SV_T>), g, b, 0, st, tiles, segs, ctl);
+    else if (two) hipLaunchKernelGGL((k_solve<4, R, OCC2, SV_T>), g, b, 0, st, tiles, segs, ctl);
+    else hipLaunchKernelGGL((k_solve<4, R, 2, SV_T>), g, b, 0, st, tiles, segs, ctl);
 }
 
 // The coupling's (one system per launch).
@@ -696,7 +709,7 @@ void launch_lists(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags)
         hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
         hipLaunchKernelGGL(k_qfix, g, b, 0, st, P.dtiles, P.dseg);
     }
-    const bool fine = solve_lpr(ctx, P.L.seg.n) != 0;
+    const bool fine = fine_lists(solve_kind(ctx, P.L.seg.n));
     {
         Timed t(ctx, 7, st);
         launch_build<R>(fine, P.dtiles, nt, P.dseg, prm, st);
@@ -757,31 +770,32 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         return CTBOP_OK;
     };
     // (the coupling's one-launch solve keeps its bonds' halo positions beside the halo list)
-    const int lpr = fq && P.L.seg.Wl <= P.L.seg.Wb ? 0 : solve_lpr(ctx, P.L.seg.n);
-    if (fq || lpr) {
+    int kind = solve_kind(ctx, P.L.seg.n);
+    if (fq && (kind == SV_WIDE || P.L.seg.Wl <= P.L.seg.Wb)) kind = 0;
+    if (fq || kind) {
         const int rc = side_launch();
         if (rc) return rc;
     }
     CgCtl ctl{ctx->opts.cg_tol, ctx->opts.cg_maxit};
     int *flag = P.flag_host;
-    bool solved = false;
-    if (lpr) {
+    bool solved = false, assembled = false;
+    if (kind) {
         {
             Timed t(ctx, 2, st);
             launch_assemble<R>(fine, P.dtiles, nt, P.dseg, ctx->pd, st);
         }
         {
             Timed t(ctx, 8, st);
-            launch_solve_prep<R>(lpr, P.dtiles, nt, P.dseg, st);
+            launch_solve_prep<R>(kind, P.dtiles, nt, P.dseg, st);
         }
         if (fq) {
             // the bonds and their weights
             if (P.own) HIPCHK(hipStreamWaitEvent(st, ctx->ev_join, 0));
             Timed t(ctx, 0, st);
-            launch_solve_fq<R>(lpr, P.dtiles, nt, P.dseg, ctl, st);
+            launch_solve_fq<R>(kind, P.dtiles, nt, P.dseg, ctl, st);
         } else {
             Timed t(ctx, 0, st);
-            launch_solve<R>(lpr, ctx->ncu, P.dtiles, nt, P.dseg, SolveCtl{ctl.tol, ctl.maxit, 0}, st);
+            launch_solve<R>(kind, ctx->ncu, P.dtiles, nt, P.dseg, SolveCtl{ctl.tol, ctl.maxit, 0}, st);
         }
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(flag, &P.L.seg.sst->done, 3 * sizeof(int), hipMemcpyDeviceToHost, st));
@@ -789,15 +803,19 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         if (ctx->profile) ev_harvest(ctx);
         solved = flag[0] && !flag[2];
         if (!solved) {
-            // given up: the starting charges again, then the multi-launch solve
-            hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, P.dtiles, P.dseg, start_mode(P, flags));
-            hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
-            hipLaunchKernelGGL(k_qfix, g, b, 0, st, P.dtiles, P.dseg);
+            // given up: the starting charges again (unless the solve never
+            // began), then the multi-launch solve
+            assembled = flag[2] == 2;
+            if (!assembled) {
+                hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, P.dtiles, P.dseg, start_mode(P, flags));
+                hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
+                hipLaunchKernelGGL(k_qfix, g, b, 0, st, P.dtiles, P.dseg);
+            }
             hipLaunchKernelGGL(k_solve_retry, g1, g1, 0, st, sid, P.dseg);
         }
     }
     if (!solved) {
-        {
+        if (!assembled) {
             Timed t(ctx, 2, st);
             launch_assemble<R>(fine, P.dtiles, nt, P.dseg, ctx->pd, st);
         }
@@ -810,7 +828,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
             Timed t(ctx, 8, st);
             hipLaunchKernelGGL((k_hslice<R>), g, b, 0, st, P.dtiles, P.dseg);
         }
-        if (!fq && !lpr) {
+        if (!fq && !kind) {
             const int rc = side_launch();
             if (rc) return rc;
         }

@@ -4,7 +4,7 @@
 // iteration, each a few microseconds of launch gap and fill, and gives a row
 // to a lane: at 20,000 atoms its product ran 79 blocks on 256 CUs and an
 // iteration took 48 us for about 3 us of matrix data.  Here every block
-// keeps SV_RB(LPR) rows for the whole solve: the rows' matrix entries, block
+// keeps sv_rows(LPR) rows for the whole solve: the rows' matrix entries, block
 // inverses and solver vectors stay in registers, and an iteration exchanges
 // only y = M r (each block stages the y of its rows' neighbours in LDS) and
 // 14 partial sums.
@@ -31,9 +31,14 @@
 namespace ctbop {
 
 constexpr int SV_T = 512;                   // threads per block
-constexpr int SV_MAX_ATOMS = 127 * TILE;    // the bitmap below, and 16-bit halo positions
-constexpr int SV_WORDS = 512;               // neighbour bitmap of a block's rows
-constexpr int SV_HALO = 6144;               // distinct neighbours a block stages at most
+constexpr int SV_MAX_ATOMS = 127 * TILE;    // blocks of SV_T threads (the bitmap of all rows, a word per thread)
+constexpr int SV_HALO = 6144;               // distinct neighbours such a block stages at most
+// Blocks of SV_TW threads keep 256 rows each.  A block whose rows have more
+// than HALO_MAX neighbours (the multi-launch product stages no more either)
+// gives up.
+constexpr int SV_TW = 1024;
+constexpr int SV_MAX_ATOMS_W = 192 * TILE;
+constexpr int sv_halo(int t) { return t == SV_T ? SV_HALO : HALO_MAX; }
 constexpr unsigned long long SV_EMPTY = ~0ull;
 constexpr unsigned long long SV_NAN = 0x7ff8000000000000ull;
 #ifndef CTBOP_SOLVE_WAIT
@@ -44,16 +49,15 @@ constexpr int SV_NSUM = 14;
 constexpr int SV_MAX_BLOCKS = 256;          // blocks of one system
 constexpr int SV_LINE = 16;                 // a block's sums: one 128-byte line,
 constexpr int SV_REP = 4;                   // in as many copies, a quarter of the blocks reading each
-constexpr int SV_NW = SV_T / 64;
 constexpr int SV_MIN_WL = 8;                // list strides whose copy of the rows holds the lines
 
 // rows of a block, LPR lanes each
-constexpr int sv_rows(int lpr) { return SV_T / lpr; }
+constexpr int sv_rows(int lpr, int t = SV_T) { return t / lpr; }
 // matrix entries of a row that each of its lanes keeps in registers (longer
 // rows stream the rest)
-template <typename R, int LPR, int OCC> constexpr int sv_regs()
+template <typename R, int LPR, int OCC, int T = SV_T> constexpr int sv_regs()
 {
-    return LPR == 8 ? 24 : sizeof(R) == 8 ? 32 : OCC == 4 ? 40 : 48;
+    return LPR == 8 || (sizeof(R) == 8 && OCC == 4) ? 24 : sizeof(R) == 8 ? 32 : OCC == 4 ? (T == SV_T ? 40 : 32) : 48;
 }
 
 __device__ __forceinline__ void sv_put(__attribute__((address_space(1))) unsigned long long *p, double v)
@@ -153,23 +157,24 @@ sv_line(__attribute__((address_space(1))) unsigned long long *slots, int buf, in
 }
 
 // The waves' shares of every block's sums into red (wave w takes blocks 4 w
-// .. 4 w + 3 of every 32); false when a wait ran out.
+// .. 4 w + 3 of every 4 NW); false when a wait ran out.
+template <int NW>
 __device__ __forceinline__ bool sv_collect(__attribute__((address_space(1))) unsigned long long *slots, int buf, int nblk,
                                            int blk, double (*red)[SV_LINE], int wv, int wl, const int *pabort)
 {
-    constexpr int PB = SV_MAX_BLOCKS / (4 * SV_NW);
+    constexpr int PB = SV_MAX_BLOCKS / (4 * NW);
     const auto line = slots + (unsigned)((buf * SV_REP + (blk & (SV_REP - 1))) * nblk * SV_LINE + (wl & 15));
     unsigned long long x[PB];
 #pragma unroll
     for (int i = 0; i < PB; i++)
-        if ((i * SV_NW + wv) * 4 < nblk)
-            x[i] = sv_get(line + (unsigned)(min((i * SV_NW + wv) * 4 + (wl >> 4), nblk - 1) * SV_LINE));
+        if ((i * NW + wv) * 4 < nblk)
+            x[i] = sv_get(line + (unsigned)(min((i * NW + wv) * 4 + (wl >> 4), nblk - 1) * SV_LINE));
     bool ok = true;
     double t = 0.0;
 #pragma unroll
     for (int i = 0; i < PB; i++)
-        if ((i * SV_NW + wv) * 4 < nblk) {
-            const int b = (i * SV_NW + wv) * 4 + (wl >> 4);
+        if ((i * NW + wv) * 4 < nblk) {
+            const int b = (i * NW + wv) * 4 + (wl >> 4);
             ok = ok && sv_wait(line + (unsigned)(min(b, nblk - 1) * SV_LINE), x[i], pabort);
             t += b < nblk ? __longlong_as_double((long long)x[i]) : 0.0;
         }
@@ -180,12 +185,13 @@ __device__ __forceinline__ bool sv_collect(__attribute__((address_space(1))) uns
 }
 
 // sum wl & 15 of the system, from the waves' shares (one block: its own)
+template <int NW>
 __device__ __forceinline__ double sv_total(const double *loc, const double (*red)[SV_LINE], int nblk, int wl)
 {
     if (nblk == 1) return loc[wl & 15];
     double t = red[0][wl & 15];
 #pragma unroll
-    for (int w = 1; w < SV_NW; w++) t += red[w][wl & 15];
+    for (int w = 1; w < NW; w++) t += red[w][wl & 15];
     return t;
 }
 __device__ __forceinline__ double sv_lane(double v, int k)
@@ -209,21 +215,21 @@ __global__ void k_solve_retry(const int *seg_ids, Seg *segs)
 // makes them) with their row sums, and the sums of the first shift.  Also
 // empties the exchange slots.  Bound by latency (two passes over the rows, a
 // scan, 16 elimination steps).
-template <int LPR, typename R>
-__global__ void __launch_bounds__(SV_T) k_solve_prep(const Tile *tiles, Seg *segs)
+template <int LPR, typename R, int T>
+__global__ void __launch_bounds__(T) k_solve_prep(const Tile *tiles, Seg *segs)
 {
-    constexpr int RB = sv_rows(LPR), EPT = BK / LPR;
+    constexpr int RB = sv_rows(LPR, T), EPT = BK / LPR;
     static_assert(LPR == 4 || LPR == 8 || LPR == 16, "a row's lanes share a 16-lane DPP row");
     int seg;
     const int row0 = sv_row0<RB>(tiles, segs, seg);
     if (row0 < 0) return;
     const Seg &S = segs[seg];
-    __shared__ unsigned long long bm[SV_WORDS];
-    __shared__ uint16_t pre[SV_WORDS];
+    __shared__ unsigned long long bm[T];
+    __shared__ uint16_t pre[T];
     __shared__ unsigned long long A64[RB * BK];
     __shared__ float A[RB][BK + 1];
-    __shared__ int wsum[SV_T / 64];
-    __shared__ double lds[SV_T / 64 * 3];
+    __shared__ int wsum[T / 64];
+    __shared__ double lds[T / 64 * 3];
     const int tid = threadIdx.x, rl = tid / LPR, lane = tid % LPR, row = row0 + rl;
     const int n = S.n, Wl = S.Wl;
     const bool live = row < n;
@@ -231,8 +237,8 @@ __global__ void __launch_bounds__(SV_T) k_solve_prep(const Tile *tiles, Seg *seg
     const int cnt = live ? hcnt[row] : 0;
     const auto ent = gbl(S.hidx + (size_t)row * Wl);
     const auto val = gbl(reinterpret_cast<const R *>(S.Hr) + (size_t)row * Wl);
-    for (int w = tid; w < SV_WORDS; w += SV_T) bm[w] = 0ull;
-    for (int w = tid; w < RB * BK; w += SV_T) A64[w] = 0ull;
+    for (int w = tid; w < T; w += T) bm[w] = 0ull;
+    for (int w = tid; w < RB * BK; w += T) A64[w] = 0ull;
     __syncthreads();
     // Entries of the row's own block are added as 2^-40 fixed point: exact
     // in any order (an atom and several images of a neighbour in a small
@@ -260,8 +266,7 @@ __global__ void __launch_bounds__(SV_T) k_solve_prep(const Tile *tiles, Seg *seg
         }
     }
     __syncthreads();
-    // positions: set bits before each word (threads 0 .. SV_WORDS-1, one word each)
-    static_assert(SV_WORDS == SV_T, "a word per thread");
+    // positions: set bits before each word (threads 0 .. T-1, one word each)
     const unsigned long long mine = bm[tid];
     const int c = __popcll(mine);
     int inc = c;
@@ -273,7 +278,7 @@ __global__ void __launch_bounds__(SV_T) k_solve_prep(const Tile *tiles, Seg *seg
     if ((tid & 63) == 63) wsum[tid >> 6] = inc;
     __syncthreads();
     int before = inc - c, total = 0;
-    for (int w = 0; w < SV_T / 64; w++) {
+    for (int w = 0; w < T / 64; w++) {
         if (w < (tid >> 6)) before += wsum[w];
         total += wsum[w];
     }
@@ -291,7 +296,7 @@ __global__ void __launch_bounds__(SV_T) k_solve_prep(const Tile *tiles, Seg *seg
     }
     if (tid == 0) {
         region[(size_t)RB * Wl - 1] = (uint32_t)total;
-        if (total > SV_HALO) atomicOr(&S.sst->pabort, 1);
+        if (total > sv_halo(T)) atomicOr(&S.sst->pabort, 2);   // (before the solve has changed anything)
     }
     // the FP32 block row, J on the diagonal; identity rows past n
     {
@@ -363,7 +368,7 @@ __global__ void __launch_bounds__(SV_T) k_solve_prep(const Tile *tiles, Seg *seg
     __syncthreads();
     if (tid < 3) {
         double s = 0.0;
-        for (int w = 0; w < SV_T / 64; w++) s += lds[w * 3 + tid];
+        for (int w = 0; w < T / 64; w++) s += lds[w * 3 + tid];
         S.part[(size_t)(row0 / RB) * 3 + tid] = s;
     }
 }
@@ -380,31 +385,31 @@ struct SolveCtl {
 // k_cg1_update, k_spmv and k_cg1_fin, whose scalar step it shares), blocks
 // of RB rows.  An iteration is bound by its two exchanges (a round trip past
 // the L2s each, with the wait for the slowest block) and the gathers from
-// LDS: at 20,000 atoms in cycles ~4000 staging y, ~3900 products (352 wave
-// gathers), ~1900 block sums, ~4000 their exchange, ~1500 the scalar step.
-// 20,000 atoms: an iteration 48 -> 10 us, a cold solve 2.2 -> 0.51 ms; 512
-// atoms 26 -> 5.5 us.  OCC 4 keeps two blocks on a CU in half the registers,
+// LDS: at 20,000 atoms in cycles ~1100 y = M r, ~3700 staging y, ~3900
+// products (352 wave gathers), ~1200 block sums, ~4000 their exchange, ~2600
+// the scalar step.
+// 20,000 atoms: an iteration 48 -> 8.5 us, a cold solve 2.2 -> 0.41 ms; 512
+// atoms 26 -> 5.2 us; 36,864 atoms (SV_TW) 31 in two launches -> 11.5 us.  OCC 4 keeps two blocks on a CU in half the registers,
 // for launches with more blocks than CUs.
-template <int LPR, typename R, int OCC>
-__global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *segs, SolveCtl ctl)
+template <int LPR, typename R, int OCC, int T>
+__global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, SolveCtl ctl)
 {
-    constexpr int RB = sv_rows(LPR), EPT = BK / LPR, E = sv_regs<R, LPR, OCC>();
-    constexpr int NW = SV_T / 64;
-    static_assert(2 * NW >= SV_NSUM, "two sums per wave");
+    constexpr int RB = sv_rows(LPR, T), EPT = BK / LPR, E = sv_regs<R, LPR, OCC, T>();
+    constexpr int NW = T / 64, NH = (SV_NSUM + NW - 1) / NW;
     static_assert(E % 8 == 0, "entries are loaded and used by eight");
     int seg;
     const int row0 = sv_row0<RB>(tiles, segs, seg);
     if (row0 < 0) return;
     const Seg &S = segs[seg];
     if (uni(S.sst->pabort)) return;
-    __shared__ double hp[SV_HALO];
-    __shared__ uint16_t hl[SV_HALO];
+    __shared__ double hp[sv_halo(T)];
+    __shared__ uint16_t hl[sv_halo(T)];
     // the rows' r, y, s, q, m1 and H y, ones, p and J (a row's first lane
     // takes its vector steps; the registers are the matrix's)
     __shared__ double va[9][RB];
     double *const vr = va[0], *const vy = va[1], *const vs = va[2], *const vq = va[3], *const vh = va[5],
            *const vp = va[7], *const vj = va[8];
-    __shared__ double tot[SV_LINE], red[SV_NW][SV_LINE];   // the block's sums, the waves' shares of all blocks'
+    __shared__ double tot[SV_LINE], red[NW][SV_LINE];   // the block's sums, the waves' shares of all blocks'
     __shared__ SegState st;
     __shared__ int sab;
     const int tid = threadIdx.x, rl = tid / LPR, lane = tid % LPR, row = row0 + rl, wv = uni(tid >> 6), wl = tid & 63;
@@ -418,7 +423,7 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
     const uint32_t *region = S.hsidx + (size_t)row0 * Wl;
     const int nh = uni((int)region[(size_t)RB * Wl - 1]);
     const auto list = gbl(reinterpret_cast<const uint16_t *>(region));
-    for (int k = tid; k < nh; k += SV_T) hl[k] = list[k];
+    for (int k = tid; k < nh; k += T) hl[k] = list[k];
     // the row's entries
     const int cnt = live ? gbl(S.hcnt)[row] : 0;
     const auto vals = gbl(uni(reinterpret_cast<const R *>(S.Hr)) + (size_t)row0 * Wl);
@@ -453,7 +458,7 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
     float bv[EPT];
 #pragma unroll
     for (int u = 0; u < EPT; u++) bv[u] = (float)gbl(S.binv + (size_t)row * BK)[lane * EPT + u];
-    static_assert(sizeof(SegState) % 4 == 0 && sizeof(SegState) / 4 <= SV_T, "a word per thread");
+    static_assert(sizeof(SegState) % 4 == 0 && sizeof(SegState) / 4 <= T, "a word per thread");
     if (tid < (int)(sizeof(SegState) / 4)) reinterpret_cast<int *>(&st)[tid] = reinterpret_cast<const int *>(sst)[tid];
     if (tid == 0) sab = 0;
     if (tid < SV_LINE) tot[tid] = 0.0;
@@ -532,12 +537,12 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
             // stage the halo, four loads in flight per thread (past its end
             // the last one again)
             bool ok = true;
-            for (int k0 = tid; k0 < nh + tid && ok; k0 += 4 * SV_T) {
+            for (int k0 = tid; k0 < nh + tid && ok; k0 += 4 * T) {
                 int k[4];
                 unsigned long long v[4];
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    k[u] = min(k0 + u * SV_T, nh - 1);
+                    k[u] = min(k0 + u * T, nh - 1);
                     v[u] = sv_get(ys + (unsigned)hl[k[u]]);
                 }
 #pragma unroll
@@ -574,9 +579,9 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         // sums wv and wv + NW: the block's share, then every block's
-        double v[2];
+        double v[NH];
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
+        for (int h = 0; h < NH; h++) {
             const int w = min(wv + h * NW, SV_NSUM - 1);
             const double *a = va[(FA >> (3 * w)) & 7], *b = va[(FB >> (3 * w)) & 7];
             v[h] = 0.0;
@@ -584,20 +589,20 @@ __global__ void __launch_bounds__(SV_T, OCC) k_solve(const Tile *tiles, Seg *seg
             for (int k = 0; k < RB; k += 64) v[h] += a[k + wl] * b[k + wl];
         }
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
+        for (int h = 0; h < NH; h++) {
             v[h] = wave_sum(v[h]);
             if (wl == 0 && wv + h * NW < SV_NSUM) tot[wv + h * NW] = v[h];
         }
         if (nblk > 1) {
             __syncthreads();
             if (wv == 0) sv_put(sv_line(slots_p, it % 3, nblk, blk, wl), tot[wl & 15]);
-            if (!sv_collect(slots_p, it % 3, nblk, blk, red, wv, wl, pabort)) sab = 1;
+            if (!sv_collect<NW>(slots_p, it % 3, nblk, blk, red, wv, wl, pabort)) sab = 1;
         }
         __syncthreads();
         if (sab) break;
         if (wv == 0) {
             // the scalar step, on the sums in scalar registers
-            const double mine = sv_total(tot, red, nblk, wl);
+            const double mine = sv_total<NW>(tot, red, nblk, wl);
             double t[P_CG1];
 #pragma unroll
             for (int k = 0; k < P_CG1; k++) t[k] = sv_lane(mine, k);

@@ -17,6 +17,7 @@
 
 namespace ctbop {
 
+constexpr int SVF_NW = SV_T / 64;
 constexpr int SVF_REG_BONDS = 2;            // bonds a lane keeps in registers
 
 // Each bond's position in the block's halo, 16 bits, row-major (Wb per row):
@@ -37,7 +38,7 @@ __device__ __forceinline__ bool svf_sum(const double (*va)[RB], unsigned long lo
                                         __attribute__((address_space(1))) unsigned long long *slots_p, double *tot,
                                         double (*red)[SV_LINE], const int *pabort)
 {
-    static_assert(K <= SV_NW, "a sum per wave");
+    static_assert(K <= SVF_NW, "a sum per wave");
     if (wv < K) {
         const double *a = va[(fa >> (4 * wv)) & 15], *b = va[(fb >> (4 * wv)) & 15];
         double v = 0.0;
@@ -49,7 +50,7 @@ __device__ __forceinline__ bool svf_sum(const double (*va)[RB], unsigned long lo
     if (nblk == 1) return true;
     __syncthreads();
     if (wv == 0) sv_put(sv_line(slots_p, ex % 3, nblk, blk, wl), tot[wl & 15]);
-    return sv_collect(slots_p, ex % 3, nblk, blk, red, wv, wl, pabort);
+    return sv_collect<SVF_NW>(slots_p, ex % 3, nblk, blk, red, wv, wl, pabort);
 }
 
 // empty this block's sums of the round before (every block has read them)
@@ -74,7 +75,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     // quadratic residual, ones, the line search's A and B, J
     enum { R_ = 0, Y_, S_, Q_, M_, RO_, P_, RL_, ONE_, A_, B_, J_, NV_ };
     __shared__ double va[NV_][RB];
-    __shared__ double tot[SV_LINE], red[SV_NW][SV_LINE];
+    __shared__ double tot[SV_LINE], red[SVF_NW][SV_LINE];
     __shared__ SegState st;
     __shared__ int sab;
     const int tid = threadIdx.x, rl = tid / LPR, lane = tid % LPR, row = row0 + rl, wv = uni(tid >> 6), wl = tid & 63;
@@ -186,7 +187,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     __syncthreads();
     if (!sab) {
         if (wv == 0) {
-            const double mine = sv_total(tot, red, nblk, wl);
+            const double mine = sv_total<SVF_NW>(tot, red, nblk, wl);
             double t[3];
             for (int k = 0; k < 3; k++) t[k] = sv_lane(mine, k);
             if (wl == 0) {
@@ -219,7 +220,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     }
     if (!sab) {
         if (wv == 0) {
-            const double mine = sv_total(tot, red, nblk, wl);
+            const double mine = sv_total<SVF_NW>(tot, red, nblk, wl);
             double t[4];
             for (int k = 0; k < 4; k++) t[k] = sv_lane(mine, k);
             if (wl == 0) {
@@ -318,7 +319,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         __syncthreads();
         if (sab) break;
         if (wv == 0) {
-            const double mine = sv_total(tot, red, nblk, wl);
+            const double mine = sv_total<SVF_NW>(tot, red, nblk, wl);
             double t[4];
             for (int k = 0; k < 4; k++) t[k] = sv_lane(mine, k);
             if (wl == 0) {
@@ -349,7 +350,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         __syncthreads();
         if (sab) break;
         if (wv == 0) {
-            const double mine = sv_total(tot, red, nblk, wl);
+            const double mine = sv_total<SVF_NW>(tot, red, nblk, wl);
             double t[2];
             for (int k = 0; k < 2; k++) t[k] = sv_lane(mine, k);
             if (wl == 0) {
@@ -387,7 +388,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         __syncthreads();
         if (sab) break;
         if (wv == 0) {
-            const double mine = sv_total(tot, red, nblk, wl);
+            const double mine = sv_total<SVF_NW>(tot, red, nblk, wl);
             double t[7];
             for (int k = 0; k < 7; k++) t[k] = sv_lane(mine, k);
             if (wl == 0) {

@@ -434,13 +434,13 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
     if (total_tiles > S->max_tiles) return fail(CTBOP_E_NOMEM, "server tile table too small");
     Tile *hts = S->htiles, *hta = S->htiles + S->max_tiles;
     int *his = S->hids, *hia = S->hids + S->max_slots;
-    // Set-up tables: the systems of each one-launch class (8 and 4 lanes per
-    // row), then those of the multi-launch solve.  Active tables: the
-    // multi-launch systems first, which the iterations below run over.
-    constexpr int CLS[3] = {8, 4, 0};
-    int cls_tiles[3] = {0, 0, 0}, nis_many = 0, nta_many = 0, nia_many = 0;
-    auto cls_of = [&](const SrvSlot &sl) { return sl.many ? 0 : solve_lpr(ctx, sl.L.seg.n); };
-    for (int c = 0; c < 3; c++)
+    // Set-up tables: the systems of each one-launch kind, then those of the
+    // multi-launch solve.  Active tables: the multi-launch systems first,
+    // which the iterations below run over.
+    constexpr int NCLS = 4, CLS[NCLS] = {8, 4, SV_WIDE, 0};
+    int cls_tiles[NCLS] = {0, 0, 0, 0}, nis_many = 0, nis_fine = 0, nta_many = 0, nia_many = 0;
+    auto cls_of = [&](const SrvSlot &sl) { return sl.many ? 0 : solve_kind(ctx, sl.L.seg.n); };
+    for (int c = 0; c < NCLS; c++)
         for (int k : act) {
             SrvSlot &sl = S->slots[k];
             if (sl.phase != 0 || cls_of(sl) != CLS[c]) continue;
@@ -448,6 +448,7 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
             cls_tiles[c] += sl.L.ntile;
             his[nis++] = k;
             if (CLS[c] == 0) nis_many++;
+            if (fine_lists(CLS[c])) nis_fine++;
         }
     int nta_coarse = 0, nia_coarse = 0;
     for (int c = 0; c < 3; c++)        // multi-launch above and up to FINE_MAX, one-launch
@@ -487,19 +488,19 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, T, S->dsegs, -1);
         hipLaunchKernelGGL(k_fin_qshift, gs, b, 0, st, sid, S->dsegs);
         hipLaunchKernelGGL(k_qfix, g, b, 0, st, T, S->dsegs);
-        const int nto = nts - cls_tiles[2], nio = nis - nis_many;   // of the one-launch solve
-        if (nto) {
-            launch_build<R>(true, T, nto, S->dsegs, prm, st);
-            launch_rev(true, T, nto, S->dsegs, st);
-            launch_assemble<R>(true, T, nto, S->dsegs, ctx->pd, st);
+        const int ntf = cls_tiles[0] + cls_tiles[1], nic = nis - nis_fine;   // of fine lists; others
+        if (ntf) {
+            launch_build<R>(true, T, ntf, S->dsegs, prm, st);
+            launch_rev(true, T, ntf, S->dsegs, st);
         }
-        if (nis_many) {
-            launch_build<R>(false, T + nto, nts - nto, S->dsegs, prm, st);
-            launch_rev(false, T + nto, nts - nto, S->dsegs, st);
-            hipLaunchKernelGGL(k_mark_built, dim3((nis_many + 63) / 64), dim3(64), 0, st, sid + nio, S->dsegs,
-                               nis_many);
-            launch_assemble<R>(false, T + nto, nts - nto, S->dsegs, ctx->pd, st);
+        if (nic) {
+            launch_build<R>(false, T + ntf, nts - ntf, S->dsegs, prm, st);
+            launch_rev(false, T + ntf, nts - ntf, S->dsegs, st);
+            hipLaunchKernelGGL(k_mark_built, dim3((nic + 63) / 64), dim3(64), 0, st, sid + nis_fine, S->dsegs, nic);
         }
+        const int nto = nts - cls_tiles[NCLS - 1];                          // of the one-launch solve
+        if (nto) launch_assemble<R>(true, T, nto, S->dsegs, ctx->pd, st);
+        if (nis_many) launch_assemble<R>(false, T + nto, nts - nto, S->dsegs, ctx->pd, st);
         // covalent energy and forces need only the lists: side stream, forked
         // after the assembly so that they run beside the solve
         HIPCHK(hipEventRecord(S->ev_fork, st));
@@ -508,15 +509,15 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         launch_bond<R>(fine, T, nts, S->dsegs, ctx->pd, S->side);
         launch_force_cov<R>(fine, T, nts, S->dsegs, prm, S->side);
         HIPCHK(hipEventRecord(S->ev_join, S->side));
-        for (int c = 0, t0 = 0; c < 2; t0 += cls_tiles[c++])
+        for (int c = 0, t0 = 0; c < NCLS - 1; t0 += cls_tiles[c++])
             if (cls_tiles[c]) {
                 launch_solve_prep<R>(CLS[c], T + t0, cls_tiles[c], S->dsegs, st);
                 launch_solve<R>(CLS[c], ctx->ncu, T + t0, cls_tiles[c], S->dsegs,
                                 SolveCtl{ctx->opts.cg_tol, ctx->opts.cg_maxit, 0}, st);
             }
         if (nis_many) {
-            const dim3 gm(cls_tiles[2]);
-            const Tile *Tm = T + (nts - cls_tiles[2]);
+            const dim3 gm(cls_tiles[NCLS - 1]);
+            const Tile *Tm = T + nto;
             hipLaunchKernelGGL((k_hslice<R>), gm, b, 0, st, Tm, S->dsegs);
             hipLaunchKernelGGL(k_fin_w0, dim3(nis_many), b, 0, st, sid + (nis - nis_many), S->dsegs);
             hipLaunchKernelGGL((k_cg1_update<true>), gm, b, 0, st, Tm, S->dsegs);

@@ -89,3 +89,27 @@ def test_coupling_matches_oracle(ct, orc, theta, case, prec):
     assert np.linalg.norm(F - Fo) / np.linalg.norm(Fo) <= t["F"]
     assert np.abs(q - qo).max() <= t["q"]
     assert runs[1][0] == E and np.array_equal(runs[1][1], F) and np.array_equal(runs[1][2], q)
+
+
+# Blocks of 256 rows (32,769 to 49,152 atoms): one row in the last block, every
+# row of the last size, rows past what a lane keeps in registers (128 entries),
+# and a crystal whose blocks have more neighbours each than any other case.
+WIDE_CASES = {"32769": lambda: G.random_system(32769, 0.7, 2.4, True, seed=3101),
+              "49152": lambda: G.random_system(49152, 0.7, 2.8, False, seed=3102),
+              "dense 33000": lambda: G.random_system(33000, 0.9, 3.2, True, seed=3103),
+              "crystal 39304": lambda: G.zincblende(17, sigma=0.05, seed=3104)}
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("name", list(WIDE_CASES))
+def test_blocks_of_256_rows(ct, orc, theta, name, prec):
+    s = WIDE_CASES[name]()
+    print(f"[one launch] {name} n={s.n} {prec}", flush=True)
+    Eo, Fo, qo, _ = orc.evaluate(s.pos, s.types, s.box, s.pbc, theta, tol=1e-13)
+    pot = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=1e-9 if prec == "mixed" else 1e-13)
+    E, F, q, info = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)
+    F, q, t = F.cpu().numpy(), q.cpu().numpy(), TOL[prec]
+    assert info["status"] == 0
+    assert abs(E - Eo) / s.n <= t["E"]
+    assert np.linalg.norm(F - Fo) / np.linalg.norm(Fo) <= t["F"]
+    assert np.abs(q - qo).max() <= t["q"]
