@@ -663,8 +663,8 @@ void launch_force_cov(bool fine, const Tile *tiles, int nt, Seg *segs, const Par
 {
     const dim3 b(TILE);
     if (fine)
-        hipLaunchKernelGGL((k_force_cov<R, COV_FINE>), dim3(nt * (TILE / COV_FINE)), b, 0, st, tiles, segs, prm, 0);
-    else hipLaunchKernelGGL((k_force_cov<R, COV_ROWS>), dim3(nt * (TILE / COV_ROWS)), b, 0, st, tiles, segs, prm, 0);
+        hipLaunchKernelGGL((k_force_cov<R, COV_FINE>), dim3(nt * (TILE / COV_FINE)), b, 0, st, tiles, segs, prm);
+    else hipLaunchKernelGGL((k_force_cov<R, COV_ROWS>), dim3(nt * (TILE / COV_ROWS)), b, 0, st, tiles, segs, prm);
 }
 // (the energy's order of summation depends on the choice: fine is n <=
 // FINE_MAX, so that a system gives the same bits alone and in the server)

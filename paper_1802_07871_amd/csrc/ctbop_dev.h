@@ -516,7 +516,7 @@ __device__ __forceinline__ void block_total(const double *v_, int cnt, double *l
 }
 
 // Two-stage sum of partials 0 .. K-1 over a segment's tiles (the
-// single-reduction solve's finalize, 15 partials per tile): one block alone
+// single-reduction solve's finalize, 14 partials per tile): one block alone
 // reads them at ~50 GB/s, the rate of one CU's outstanding misses, so FIN_SPLIT
 // blocks first sum consecutive ranges of tiles (each thread about one tile),
 // and the finalize adds the FIN_SPLIT group sums in order.  The group sums

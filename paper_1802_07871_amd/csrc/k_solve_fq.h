@@ -2,7 +2,7 @@
 // one launch, for the systems that take the one-launch linear solve.
 //
 // The multi-launch form takes nine dependent launches per iteration (18,086
-// atoms: 73 us; five MD steps 11.4 ms, 5.2 with this solve, which takes 0.57
+// atoms: 73 us; five MD steps 11.4 ms, 4.25 with this solve, which takes 0.44
 // ms).  Here, as in k_solve.h, a block keeps its rows' matrix
 // entries in registers and exchanges through agent-scope slots that are their
 // own flags.  An iteration exchanges p once: the block keeps the charges of
@@ -10,7 +10,8 @@
 // (q += alpha p, bit for bit), so the line search and the coupling's gradient,
 // whose bonds reach rows of the halo only, need no other exchange.  Three sums
 // over the system remain: the two Newton steps on the step length and the
-// residual's.
+// residual's.  Bound, like k_solve, by its exchanges: four round trips past
+// the L2s per iteration, each with the wait for the slowest block.
 #pragma once
 #include "k_fq.h"
 #include "k_solve.h"
@@ -176,8 +177,6 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         y = row_sum<LPR>(y);
         if (lane == 0) va[Y_][rl] = y;
     };
-    // Bound, like k_solve, by its exchanges: four round trips past the L2s per
-    // iteration, each with the wait for the slowest block.
     // first pass over the starting residual: its shift (r m1, m1, entries)
     residual();
     if (lane == 0) va[A_][rl] = (double)cnt;

@@ -421,14 +421,13 @@ __device__ __forceinline__ R pair_dvdr(const Params<R> &P, int pp, R r, R b)
 // 20,000 atoms 519 -> 47, a chunk of 131,072 atoms of the 1M-atom slab beside
 // the solve 293 -> 241.
 template <typename R, int ROWS>
-__global__ void __launch_bounds__(TILE) k_force_cov(const Tile *tiles, Seg *segs, Params<R> Pk, int gate)
+__global__ void __launch_bounds__(TILE) k_force_cov(const Tile *tiles, Seg *segs, Params<R> Pk)
 {
     using V4 = typename Vec4<R>::type;
     constexpr int CAP = cov_cap<ROWS>() / (sizeof(R) / 4);
     const Tile T = my_rows<ROWS>(tiles);
     const Seg &S = segs[T.seg];
     // serving: only segments whose charge solve finished and whose forces are pending
-    if (gate && (!S.sst->done || S.sst->pabort || S.sst->forces_done)) return;
     __shared__ V4 dtab[NCODE];
     __shared__ Params<R> P;
     __shared__ RowItems<ROWS, CAP> it;

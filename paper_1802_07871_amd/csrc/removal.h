@@ -1,6 +1,7 @@
 // removal.h -- removal energies of single atoms (included by ctbop.hip after
 // server.h): the full system once, then every leave-one-out system as a
-// continuous batch through a server on the rest of the caller's arena.
+// continuous batch through a server on the rest of the caller's arena, which
+// makes their inputs from the full system's arrays on the device.
 #pragma once
 
 namespace {
