@@ -98,10 +98,15 @@ struct SegState {
     double nnz_slots;                         // entry slots the sliced product reads: 64 x longest row, per slice
     double nbond, ntrip;                      // bonds and ordered bond pairs (i; j, k) at the last evaluation
     // charge coupling (f_q) solve: p^T r, p^T H p and the coupling part of
-    // phi'(0) along the current direction (line search)
-    double pr, ps, A0;
-    double m1s;        // single-reduction solve: m1^T s of the current direction
-    double den;        // and its p^T H p
+    // phi'(0) along the current direction (line search); single-reduction
+    // solve: p^T H p and m1^T s of the current direction
+    union {
+        double pr, den;
+    };
+    union {
+        double ps, m1s;
+    };
+    double A0;
 };
 
 // ---------------------------------------------------------------------------
