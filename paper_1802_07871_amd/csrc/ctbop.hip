@@ -536,7 +536,8 @@ int start_mode(const Prep &P, int flags)
 // of one system have to be on the device together, one per CU.  Up to 64 rows
 // a CU take 8 lanes per row, up to SV_MAX_ATOMS 4, up to SV_MAX_ATOMS_W the
 // larger blocks (an evaluation of 48,640 atoms 2.26 ms in two launches per
-// iteration, 1.48 with them).  The lines at 128 and 192 tiles are not of speed
+// iteration, 1.48 with them, 1.17 since its lists are built in FINE-row blocks
+// and without halos, as the smaller systems').  The lines at 128 and 192 tiles are not of speed
 // (53,760 atoms would take 1.52 ms for 2.40): the multi-launch solve's 16-bit
 // offsets and full entries are checked on systems of 32,768 and 50,240 atoms,
 // which have to reach it.
@@ -555,8 +556,6 @@ int solve_kind(ctbop_ctx *ctx, int n)
     if (n <= std::min(sv_rows(4) * ctx->ncu, SV_MAX_ATOMS)) return 4;
     return n > 128 * TILE && 4 * n <= 3 * sv_rows(4, SV_TW) * ctx->ncu ? SV_WIDE : 0;
 }
-// the list build of the system leaves out the tiles' halos
-bool fine_lists(int kind) { return kind == 8 || kind == 4; }
 
 // The one-launch solve over nt tiles of systems of one kind, and the kernel
 // that prepares it.
@@ -709,7 +708,7 @@ void launch_lists(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags)
         hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
         hipLaunchKernelGGL(k_qfix, g, b, 0, st, P.dtiles, P.dseg);
     }
-    const bool fine = fine_lists(solve_kind(ctx, P.L.seg.n));
+    const bool fine = solve_kind(ctx, P.L.seg.n) != 0;
     {
         Timed t(ctx, 7, st);
         launch_build<R>(fine, P.dtiles, nt, P.dseg, prm, st);

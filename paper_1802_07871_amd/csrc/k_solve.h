@@ -32,13 +32,10 @@ namespace ctbop {
 
 constexpr int SV_T = 512;                   // threads per block
 constexpr int SV_MAX_ATOMS = 127 * TILE;    // blocks of SV_T threads (the bitmap of all rows, a word per thread)
-constexpr int SV_HALO = 6144;               // distinct neighbours such a block stages at most
-// Blocks of SV_TW threads keep 256 rows each.  A block whose rows have more
-// than HALO_MAX neighbours (the multi-launch product stages no more either)
-// gives up.
+constexpr int SV_HALO = 6144;               // distinct neighbours a block stages at most
+// Blocks of SV_TW threads keep 256 rows each.
 constexpr int SV_TW = 1024;
 constexpr int SV_MAX_ATOMS_W = 192 * TILE;
-constexpr int sv_halo(int t) { return t == SV_T ? SV_HALO : HALO_MAX; }
 constexpr unsigned long long SV_EMPTY = ~0ull;
 constexpr unsigned long long SV_NAN = 0x7ff8000000000000ull;
 #ifndef CTBOP_SOLVE_WAIT
@@ -314,7 +311,7 @@ __global__ void __launch_bounds__(T) k_solve_prep(const Tile *tiles, Seg *segs)
     }
     if (tid == 0) {
         region[(size_t)RB * Wl - 1] = (uint32_t)total;
-        if (total > sv_halo(T)) atomicOr(&S.sst->pabort, 2);   // (before the solve has changed anything)
+        if (total > SV_HALO) atomicOr(&S.sst->pabort, 2);   // (before the solve has changed anything)
     }
     // the FP32 block row, J on the diagonal; identity rows past n
     {
@@ -424,8 +421,8 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
     if (row0 < 0) return;
     const Seg &S = segs[seg];
     if (uni(S.sst->pabort)) return;
-    __shared__ double hp[sv_halo(T)];
-    __shared__ uint16_t hl[sv_halo(T)];
+    __shared__ double hp[SV_HALO];
+    __shared__ uint16_t hl[SV_HALO];
     // the rows' r, y, s, q, m1 and H y, ones, p and J (a row's first lane
     // takes its vector steps; the registers are the matrix's)
     __shared__ double va[9][RB];

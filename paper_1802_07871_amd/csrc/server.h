@@ -438,7 +438,7 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
     // multi-launch solve.  Active tables: the multi-launch systems first,
     // which the iterations below run over.
     constexpr int NCLS = 4, CLS[NCLS] = {8, 4, SV_WIDE, 0};
-    int cls_tiles[NCLS] = {0, 0, 0, 0}, nis_many = 0, nis_fine = 0, nta_many = 0, nia_many = 0;
+    int cls_tiles[NCLS] = {0, 0, 0, 0}, nis_many = 0, nta_many = 0, nia_many = 0;
     auto cls_of = [&](const SrvSlot &sl) { return sl.many ? 0 : solve_kind(ctx, sl.L.seg.n); };
     for (int c = 0; c < NCLS; c++)
         for (int k : act) {
@@ -448,7 +448,6 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
             cls_tiles[c] += sl.L.ntile;
             his[nis++] = k;
             if (CLS[c] == 0) nis_many++;
-            if (fine_lists(CLS[c])) nis_fine++;
         }
     int nta_coarse = 0, nia_coarse = 0;
     for (int c = 0; c < 3; c++)        // multi-launch above and up to FINE_MAX, one-launch
@@ -488,19 +487,19 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, T, S->dsegs, -1);
         hipLaunchKernelGGL(k_fin_qshift, gs, b, 0, st, sid, S->dsegs);
         hipLaunchKernelGGL(k_qfix, g, b, 0, st, T, S->dsegs);
-        const int ntf = cls_tiles[0] + cls_tiles[1], nic = nis - nis_fine;   // of fine lists; others
-        if (ntf) {
-            launch_build<R>(true, T, ntf, S->dsegs, prm, st);
-            launch_rev(true, T, ntf, S->dsegs, st);
+        const int nto = nts - cls_tiles[NCLS - 1], nio = nis - nis_many;   // of the one-launch solve
+        if (nto) {
+            launch_build<R>(true, T, nto, S->dsegs, prm, st);
+            launch_rev(true, T, nto, S->dsegs, st);
+            launch_assemble<R>(true, T, nto, S->dsegs, ctx->pd, st);
         }
-        if (nic) {
-            launch_build<R>(false, T + ntf, nts - ntf, S->dsegs, prm, st);
-            launch_rev(false, T + ntf, nts - ntf, S->dsegs, st);
-            hipLaunchKernelGGL(k_mark_built, dim3((nic + 63) / 64), dim3(64), 0, st, sid + nis_fine, S->dsegs, nic);
+        if (nis_many) {
+            launch_build<R>(false, T + nto, nts - nto, S->dsegs, prm, st);
+            launch_rev(false, T + nto, nts - nto, S->dsegs, st);
+            hipLaunchKernelGGL(k_mark_built, dim3((nis_many + 63) / 64), dim3(64), 0, st, sid + nio, S->dsegs,
+                               nis_many);
+            launch_assemble<R>(false, T + nto, nts - nto, S->dsegs, ctx->pd, st);
         }
-        const int nto = nts - cls_tiles[NCLS - 1];                          // of the one-launch solve
-        if (nto) launch_assemble<R>(true, T, nto, S->dsegs, ctx->pd, st);
-        if (nis_many) launch_assemble<R>(false, T + nto, nts - nto, S->dsegs, ctx->pd, st);
         // covalent energy and forces need only the lists: side stream, forked
         // after the assembly so that they run beside the solve
         HIPCHK(hipEventRecord(S->ev_fork, st));
