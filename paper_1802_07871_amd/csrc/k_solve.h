@@ -408,7 +408,8 @@ struct SolveCtl {
 // products (352 wave gathers), ~1200 block sums, ~4000 their exchange, ~2600
 // the scalar step.
 // 20,000 atoms: an iteration 48 -> 8.5 us, a cold solve 2.2 -> 0.41 ms; 512
-// atoms 26 -> 5.2 us; 36,864 atoms (SV_TW) 31 in two launches -> 11.5 us.  OCC 4 keeps two blocks on a CU in half the registers,
+// atoms 26 -> 5.2 us; 36,864 atoms (SV_TW) 31 in two launches -> 11.5 us.
+// OCC 4 keeps two blocks on a CU in half the registers,
 // for launches with more blocks than CUs.
 template <int LPR, typename R, int OCC, int T>
 __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, SolveCtl ctl)

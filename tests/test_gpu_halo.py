@@ -114,11 +114,13 @@ def test_rows_that_fill_their_stride(ct, theta, orc, prec):
 
 
 # The same forms above 65,536 atoms, where the product has a lane per row (the
-# systems above run it with eight waves per row slice).
+# 32,768 and 50,240 atoms above run it with eight waves per row slice), and
+# rows that fill their stride on both sides of that size.
 LARGE = {
     "stepped slab": (lambda: G.slab_4h(50, 50, 8, step=True, deplete=0.3, seed=177), ("halo", "full")),
     "3C-SiC 74088": (lambda: G.zincblende(21, sigma=0.05, seed=178), ("off16",)),
     "full rows": (lambda: G.slab_4h(54, 54, 6, seed=179), ("halo",)),
+    "full rows 60000": (lambda: G.slab_4h(50, 50, 6, seed=181), ("halo",)),
 }
 
 
@@ -126,10 +128,10 @@ LARGE = {
 def test_forms_of_a_large_system(ct, theta, orc, name):
     s = LARGE[name][0]()
     s.pos = s.pos + np.random.Generator(np.random.PCG64(180)).normal(0.0, 0.05, s.pos.shape)
-    assert s.n > 65536
+    assert s.n > 65536 or name == "full rows 60000" and 49152 < s.n < 65536
     Eo, Fo, qo, _ = orc.evaluate(s.pos, s.types, s.box, s.pbc, theta, tol=1e-13)
     t, opts = TOL["mixed"], {}
-    if name == "full rows":
+    if name.startswith("full rows"):
         # a stride of the longest row: its slice keeps 16-bit positions
         opts = dict(skin=0.0, long_cap=ct.Potential(theta, skin=0.0).compute(s.pos, s.types, s.box, s.pbc)[3]["max_long"])
     print(f"[halo] {name} n={s.n} {opts}", flush=True)

@@ -1,8 +1,8 @@
-"""The charge solve in one launch (systems of up to 32,512 atoms) against the
+"""The charge solve in one launch (systems of up to 49,152 atoms) against the
 oracle, at the sizes where its layout changes: one row block and its
 neighbours (64 rows of 8 lanes), the change from 8 to 4 lanes per row (16,384
-atoms on 256 CUs), the last size that takes it and the first that takes the
-multi-launch solve, and rows longer than the entries a lane keeps in
+atoms on 256 CUs), the last size of blocks of 128 rows and the first that takes
+the multi-launch solve, and rows longer than the entries a lane keeps in
 registers (192: dense carbon has ~340 neighbours inside the cutoff), with
 both numbers of lanes; at 4,096 atoms, the last size whose sorted frame is made
 by one block; and at 65,536 atoms, the last size whose row kernels
