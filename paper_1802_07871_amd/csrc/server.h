@@ -736,7 +736,8 @@ void server_loop(ctbop_server *S)
 }
 
 // A server with `stage` bytes of pinned room for inputs and results (0: each
-// is copied by itself).
+// is copied by itself).  A request's inputs are under 1/350 of its region at
+// the default list sizes, so 1/256 of the arena holds those of a full one.
 constexpr size_t STAGE_MAX = (size_t)8 << 20;
 int create_server(ctbop_ctx *ctx, void *arena, size_t arena_bytes, int max_slots, int cg_per_tick, void *stream,
                   size_t stage, ctbop_server **out)
@@ -822,7 +823,7 @@ int ctbop_server_create(ctbop_ctx *ctx, void *arena, size_t arena_bytes, int max
                         void *stream, ctbop_server **out)
 {
     return create_server(ctx, arena, arena_bytes, max_slots, cg_per_tick, stream,
-                         std::min(STAGE_MAX, align_up(arena_bytes / 64, 4096)), out);
+                         std::min(STAGE_MAX, align_up(arena_bytes / 256, 4096)), out);
 }
 
 int ctbop_server_submit(ctbop_server *S, const ctbop_request *rq, long *ticket)
