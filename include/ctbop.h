@@ -377,6 +377,20 @@ int ctbop_profile_classes(ctbop_ctx *ctx, unsigned mask);
 /* Message of the last error on the calling thread ("" if none). */
 const char *ctbop_last_error(void);
 
+/* The way that the charge solves of this context take from the next call on,
+ * for tests: small and middling systems solve in one launch, with the
+ * multi-launch solve of larger ones as the way out of a solve that gives up.
+ * Results are the same to the solve's tolerance.  give_ups (NULL or one
+ * long) gets the one-launch solves given up on this context so far.  E_INVAL
+ * for any other way. */
+#define CTBOP_SOLVE_DEFAULT 0  /* by size                                              */
+#define CTBOP_SOLVE_MULTI   1  /* every system by the multi-launch solve               */
+#define CTBOP_SOLVE_NO_WAIT 2  /* a one-launch solve gives up in its first iteration   */
+#define CTBOP_SOLVE_CROWDED 3  /* its preparation finds too many neighbours in a block */
+#define CTBOP_SOLVE_LATE    4  /* it ends after one iteration, and its last block gives
+                                  up when the others have finished                     */
+int ctbop_debug_solve(ctbop_ctx *ctx, int way, long *give_ups);
+
 /* Copy the lists of the last build to host memory, in user atom order, for
  * tests: for every atom i its long-list (Coulomb, r < rc + skin) and
  * short-list (covalent, r < S_ij + skin) neighbours as the user index j and

@@ -23,6 +23,7 @@ N_PARAMS = 56
 
 OK, E_INVAL, E_NOMEM, E_TOO_CLOSE, E_QEQ_NOCONV, E_QEQ_NOT_PD, E_NEIGH_OVERFLOW, E_HIP, E_BUSY = range(9)
 FLAG_WARM_START, FLAG_FORCE_REBUILD, FLAG_EXTRAPOLATE = 1, 2, 4
+SOLVE_DEFAULT, SOLVE_MULTI, SOLVE_NO_WAIT, SOLVE_CROWDED, SOLVE_LATE = range(5)
 _CODES = {1: "E_INVAL", 2: "E_NOMEM", 3: "E_TOO_CLOSE", 4: "E_QEQ_NOCONV", 5: "E_QEQ_NOT_PD",
           6: "E_NEIGH_OVERFLOW", 7: "E_HIP", 8: "E_BUSY"}
 
@@ -59,7 +60,7 @@ EXPORTS = ("ctbop_default_opts", "ctbop_create", "ctbop_destroy", "ctbop_system_
            "ctbop_debug_lists", "ctbop_profile", "ctbop_profile_classes", "ctbop_set_params", "ctbop_param_grad_bytes", "ctbop_param_grad",
            "ctbop_removal_bytes", "ctbop_removal_energies", "ctbop_md_run_nvt", "ctbop_relax_fire",
            "ctbop_rings_bytes", "ctbop_rings", "ctbop_system_reset",
-           "ctbop_compute_energy_forces_charges_static")
+           "ctbop_compute_energy_forces_charges_static", "ctbop_debug_solve")
 
 
 def lib():
@@ -84,6 +85,7 @@ def lib():
         L.ctbop_status.argtypes = [vp, vp, sz, vp, ctypes.POINTER(i32)]
         L.ctbop_last_error.restype = ctypes.c_char_p
         L.ctbop_debug_lists.argtypes = [vp, i32, vp, sz, i32, i32, vp, vp, vp, vp, vp, vp, vp]
+        L.ctbop_debug_solve.argtypes = [vp, i32, ctypes.POINTER(ctypes.c_long)]
         L.ctbop_profile.argtypes = [vp, i32, i32, vp, vp, vp, i32]
         L.ctbop_profile_classes.argtypes = [vp, ctypes.c_uint]
         L.ctbop_set_params.argtypes = [vp, vp, i32]
@@ -194,6 +196,14 @@ class Potential:
             raise ValueError("expected 56 parameters")
         _check(lib().ctbop_set_params(self.ctx, th.ctypes.data, N_PARAMS))
         self.params = th
+
+    def debug_solve(self, way: int = SOLVE_DEFAULT) -> int:
+        """For tests: the way that this context's charge solves take (SOLVE_*;
+        results are the same to the solve's tolerance).  Returns the number of
+        one-launch solves given up so far."""
+        k = ctypes.c_long()
+        _check(lib().ctbop_debug_solve(self.ctx, int(way), ctypes.byref(k)))
+        return int(k.value)
 
     def param_grad(self, sysbuf: System, box, pbc, dL_dE, dL_dF_soa, dL_dq=None, ws=None):
         """dL/dtheta (numpy [56]) at the last evaluation on `sysbuf`, for the

@@ -152,21 +152,22 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
     int *flag = ctx->host_flag;
     bool solved = false;
     if (const int kind = solve_kind(ctx, P.L.seg.n)) {
-        launch_solve_prep<R>(kind, P.dtiles, P.L.ntile, dadj, st);
-        launch_solve<R>(kind, ctx->ncu, P.dtiles, P.L.ntile, dadj, SolveCtl{ctx->opts.cg_tol, ctx->opts.cg_maxit, 1}, st);
+        launch_solve_prep<R>(ctx, kind, P.dtiles, P.L.ntile, dadj, st);
+        launch_solve<R>(kind, ctx->ncu, P.dtiles, P.L.ntile, dadj, solve_ctl(ctx, 1), st);
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(flag, &asst->done, 3 * sizeof(int), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         solved = flag[0] && !flag[2];
-        if (!solved) {
-                // given up: the solver's copy of the rows, which the forward
-                // evaluation did not make, then the multi-launch solve afresh
-                hipLaunchKernelGGL((k_hslice<R>), g, b, 0, st, P.dtiles, P.dseg);
-                hipLaunchKernelGGL(k_zero, g1, dim3(64), 0, st, (double *)asst, (int)(sizeof(SegState) / sizeof(double)));
-                hipLaunchKernelGGL(k_adj_init, g, b, 0, st, P.dtiles, dadj, A);
-            }
+        if (!solved) ctx->give_ups++;
+    }
+    if (!solved) {
+        if (size_kind(ctx, P.L.seg.n)) {
+            // the solver's copy of the rows, which the forward evaluation need
+            // not have made, and the start afresh
+            hipLaunchKernelGGL((k_hslice<R>), g, b, 0, st, P.dtiles, P.dseg);
+            hipLaunchKernelGGL(k_zero, g1, dim3(64), 0, st, (double *)asst, (int)(sizeof(SegState) / sizeof(double)));
+            hipLaunchKernelGGL(k_adj_init, g, b, 0, st, P.dtiles, dadj, A);
         }
-        if (!solved) {
         // first read the starting residual
         CgCtl ctl{1e-300, ctx->opts.cg_maxit};
         hipLaunchKernelGGL(k_fin_w0, g1, b, 0, st, sid, dadj);

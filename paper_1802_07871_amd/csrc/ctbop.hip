@@ -94,6 +94,9 @@ struct ctbop_ctx {
     // that they leave room for the solve's product beside them
     int side_chunk = 512;
     int ncu = 0;                 // compute units of the device, at most SV_MAX_BLOCKS (0: not asked yet)
+    // way of the charge solve (ctbop_debug_solve) and one-launch solves given up
+    std::atomic<int> way{CTBOP_SOLVE_DEFAULT};
+    std::atomic<long> give_ups{0};
     // optional per-kernel timing with HIP events on the caller's stream
     int profile = 0;
     unsigned profile_mask = 0xffffu;   // kernel classes timed while profiling is on
@@ -542,7 +545,7 @@ int start_mode(const Prep &P, int flags)
 // offsets and full entries are checked on systems of 32,768 and 50,240 atoms,
 // which have to reach it.
 constexpr int SV_WIDE = 1;
-int solve_kind(ctbop_ctx *ctx, int n)
+int size_kind(ctbop_ctx *ctx, int n)
 {
     if (n > SV_MAX_ATOMS_W || ctx->opts.long_cap < SV_MIN_WL) return 0;
     if (ctx->ncu == 0) {
@@ -557,16 +560,31 @@ int solve_kind(ctbop_ctx *ctx, int n)
     return n > 128 * TILE && 4 * n <= 3 * sv_rows(4, SV_TW) * ctx->ncu ? SV_WIDE : 0;
 }
 
+// The kind that a call's solve takes.
+int solve_kind(ctbop_ctx *ctx, int n) { return ctx->way == CTBOP_SOLVE_MULTI ? 0 : size_kind(ctx, n); }
+
+// What the one-launch solve is told: its tolerance, and the way out that the
+// context asks for.
+SolveCtl solve_ctl(const ctbop_ctx *ctx, int relative)
+{
+    const int way = ctx->way;
+    return {ctx->opts.cg_tol, way == CTBOP_SOLVE_LATE ? 1 : ctx->opts.cg_maxit, relative, way == CTBOP_SOLVE_LATE,
+            way == CTBOP_SOLVE_NO_WAIT ? -1 : SV_WAIT};
+}
+
 // The one-launch solve over nt tiles of systems of one kind, and the kernel
 // that prepares it.
 template <typename R>
-void launch_solve_prep(int kind, const Tile *tiles, int nt, Seg *segs, hipStream_t st)
+void launch_solve_prep(const ctbop_ctx *ctx, int kind, const Tile *tiles, int nt, Seg *segs, hipStream_t st)
 {
+    const int most = ctx->way == CTBOP_SOLVE_CROWDED ? -1 : SV_HALO;
     if (kind == 8)
-        hipLaunchKernelGGL((k_solve_prep<8, R, SV_T>), dim3(nt * (TILE / sv_rows(8))), dim3(SV_T), 0, st, tiles, segs);
+        hipLaunchKernelGGL((k_solve_prep<8, R, SV_T>), dim3(nt * (TILE / sv_rows(8))), dim3(SV_T), 0, st, tiles, segs,
+                           most);
     else if (kind == 4)
-        hipLaunchKernelGGL((k_solve_prep<4, R, SV_T>), dim3(nt * (TILE / sv_rows(4))), dim3(SV_T), 0, st, tiles, segs);
-    else hipLaunchKernelGGL((k_solve_prep<4, R, SV_TW>), dim3(nt), dim3(SV_TW), 0, st, tiles, segs);
+        hipLaunchKernelGGL((k_solve_prep<4, R, SV_T>), dim3(nt * (TILE / sv_rows(4))), dim3(SV_T), 0, st, tiles, segs,
+                           most);
+    else hipLaunchKernelGGL((k_solve_prep<4, R, SV_TW>), dim3(nt), dim3(SV_TW), 0, st, tiles, segs, most);
 }
 template <typename R>
 void launch_solve(int kind, int ncu, const Tile *tiles, int nt, Seg *segs, SolveCtl ctl, hipStream_t st)
@@ -587,7 +605,7 @@ void launch_solve(int kind, int ncu, const Tile *tiles, int nt, Seg *segs, Solve
 
 // The coupling's (one system per launch).
 template <typename R>
-void launch_solve_fq(int lpr, const Tile *tiles, int nt, Seg *segs, CgCtl ctl, hipStream_t st)
+void launch_solve_fq(int lpr, const Tile *tiles, int nt, Seg *segs, SolveCtl ctl, hipStream_t st)
 {
     const dim3 g(nt * (TILE / sv_rows(lpr))), b(SV_T), gt(nt), bt(TILE);
     if (lpr == 8) {
@@ -785,16 +803,16 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         }
         {
             Timed t(ctx, 8, st);
-            launch_solve_prep<R>(kind, P.dtiles, nt, P.dseg, st);
+            launch_solve_prep<R>(ctx, kind, P.dtiles, nt, P.dseg, st);
         }
         if (fq) {
             // the bonds and their weights
             if (P.own) HIPCHK(hipStreamWaitEvent(st, ctx->ev_join, 0));
             Timed t(ctx, 0, st);
-            launch_solve_fq<R>(kind, P.dtiles, nt, P.dseg, ctl, st);
+            launch_solve_fq<R>(kind, P.dtiles, nt, P.dseg, solve_ctl(ctx, 0), st);
         } else {
             Timed t(ctx, 0, st);
-            launch_solve<R>(kind, ctx->ncu, P.dtiles, nt, P.dseg, SolveCtl{ctl.tol, ctl.maxit, 0}, st);
+            launch_solve<R>(kind, ctx->ncu, P.dtiles, nt, P.dseg, solve_ctl(ctx, 0), st);
         }
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(flag, &P.L.seg.sst->done, 3 * sizeof(int), hipMemcpyDeviceToHost, st));
@@ -805,6 +823,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
             // given up: the starting charges again (unless the solve never
             // began), then the multi-launch solve
             assembled = flag[2] == 2;
+            ctx->give_ups++;
             if (!assembled) {
                 hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, P.dtiles, P.dseg, start_mode(P, flags));
                 hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
@@ -1367,6 +1386,14 @@ int ctbop_profile_classes(ctbop_ctx *ctx, unsigned mask)
 {
     if (!ctx) return fail(CTBOP_E_INVAL, "null context");
     ctx->profile_mask = mask & 0xffffu;
+    return CTBOP_OK;
+}
+
+int ctbop_debug_solve(ctbop_ctx *ctx, int way, long *give_ups)
+{
+    if (!ctx || way < CTBOP_SOLVE_DEFAULT || way > CTBOP_SOLVE_LATE) return fail(CTBOP_E_INVAL, "bad argument");
+    ctx->way = way;
+    if (give_ups) *give_ups = ctx->give_ups;
     return CTBOP_OK;
 }
 

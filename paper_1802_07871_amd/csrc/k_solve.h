@@ -38,10 +38,7 @@ constexpr int SV_TW = 1024;
 constexpr int SV_MAX_ATOMS_W = 192 * TILE;
 constexpr unsigned long long SV_EMPTY = ~0ull;
 constexpr unsigned long long SV_NAN = 0x7ff8000000000000ull;
-#ifndef CTBOP_SOLVE_WAIT
-#define CTBOP_SOLVE_WAIT 5000000
-#endif
-constexpr long long SV_WAIT = CTBOP_SOLVE_WAIT;   // ticks of the 100 MHz clock: 50 ms per wait (< 0: none waits, a check of the way out)
+constexpr long long SV_WAIT = 5000000;      // ticks of the 100 MHz clock: 50 ms per wait
 constexpr int SV_NSUM = 14;
 constexpr int SV_MAX_BLOCKS = 256;          // blocks of one system
 constexpr int SV_LINE = 16;                 // a block's sums: one 128-byte line,
@@ -75,7 +72,7 @@ __device__ __forceinline__ unsigned long long sv_get(const __attribute__((addres
 // Load a slot until its value is there; false when the wait ran out or
 // another block of the system gave up.
 __device__ __forceinline__ bool sv_wait(const __attribute__((address_space(1))) unsigned long long *p,
-                                        unsigned long long &v, const int *pabort)
+                                        unsigned long long &v, const int *pabort, long long bound)
 {
     if (v != SV_EMPTY) return true;
     const long long t0 = wall_clock64();
@@ -83,9 +80,9 @@ __device__ __forceinline__ bool sv_wait(const __attribute__((address_space(1))) 
         v = sv_get(p);
         if (v != SV_EMPTY) return true;
         __builtin_amdgcn_s_sleep(1);
-        if ((k & 63) == (SV_WAIT < 0 ? 0 : 63)) {
+        if ((k & 63) == 63) {
             if (__hip_atomic_load(pabort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
-            if (wall_clock64() - t0 > SV_WAIT) return false;
+            if (wall_clock64() - t0 > bound) return false;
         }
     }
 }
@@ -157,7 +154,8 @@ sv_line(__attribute__((address_space(1))) unsigned long long *slots, int buf, in
 // .. 4 w + 3 of every 4 NW); false when a wait ran out.
 template <int NW>
 __device__ __forceinline__ bool sv_collect(__attribute__((address_space(1))) unsigned long long *slots, int buf, int nblk,
-                                           int blk, double (*red)[SV_LINE], int wv, int wl, const int *pabort)
+                                           int blk, double (*red)[SV_LINE], int wv, int wl, const int *pabort,
+                                           long long bound)
 {
     constexpr int PB = SV_MAX_BLOCKS / (4 * NW);
     const auto line = slots + (unsigned)((buf * SV_REP + (blk & (SV_REP - 1))) * nblk * SV_LINE + (wl & 15));
@@ -172,7 +170,7 @@ __device__ __forceinline__ bool sv_collect(__attribute__((address_space(1))) uns
     for (int i = 0; i < PB; i++)
         if ((i * NW + wv) * 4 < nblk) {
             const int b = (i * NW + wv) * 4 + (wl >> 4);
-            ok = ok && sv_wait(line + (unsigned)(min(b, nblk - 1) * SV_LINE), x[i], pabort);
+            ok = ok && sv_wait(line + (unsigned)(min(b, nblk - 1) * SV_LINE), x[i], pabort, bound);
             t += b < nblk ? __longlong_as_double((long long)x[i]) : 0.0;
         }
     t += __shfl_xor(t, 16, 64);
@@ -210,10 +208,11 @@ __global__ void k_solve_retry(const int *seg_ids, Seg *segs)
 // rows its entries name, ascending), each entry's position in it (hs16, row-
 // major like hidx), the inverses of the BK x BK diagonal blocks (as k_hslice
 // makes them) with their row sums, and the sums of the first shift.  Also
-// empties the exchange slots.  Bound by latency (two passes over the rows, a
+// empties the exchange slots.  A block of more than `most` neighbours (SV_HALO
+// at most) sends the system to the multi-launch solve.  Bound by latency (two passes over the rows, a
 // scan, 16 elimination steps).
 template <int LPR, typename R, int T>
-__global__ void __launch_bounds__(T) k_solve_prep(const Tile *tiles, Seg *segs)
+__global__ void __launch_bounds__(T) k_solve_prep(const Tile *tiles, Seg *segs, int most)
 {
     constexpr int RB = sv_rows(LPR, T), EPT = BK / LPR;
     static_assert(LPR == 4 || LPR == 8 || LPR == 16, "a row's lanes share a 16-lane DPP row");
@@ -311,7 +310,7 @@ __global__ void __launch_bounds__(T) k_solve_prep(const Tile *tiles, Seg *segs)
     }
     if (tid == 0) {
         region[(size_t)RB * Wl - 1] = (uint32_t)total;
-        if (total > SV_HALO) atomicOr(&S.sst->pabort, 2);   // (before the solve has changed anything)
+        if (total > most) atomicOr(&S.sst->pabort, 2);   // (before the solve has changed anything)
     }
     // the FP32 block row, J on the diagonal; identity rows past n
     {
@@ -393,11 +392,15 @@ __global__ void __launch_bounds__(T) k_solve_prep(const Tile *tiles, Seg *segs)
 }
 
 // Tolerance of a solve; relative: times the starting residual (the adjoint,
-// whose source has the caller's scale).
+// whose source has the caller's scale).  wait: the bound of a wait in ticks
+// (< 0: the solve gives up in its first iteration).  late: its last block
+// gives up at the end, when the others have finished.
 struct SolveCtl {
     double tol;
     int maxit;
     int relative;
+    int late;
+    long long wait;
 };
 
 // The whole projected PCG of one system (the single-reduction form of
@@ -480,7 +483,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
     for (int u = 0; u < EPT; u++) bv[u] = (float)gbl(S.binv + (size_t)row * BK)[lane * EPT + u];
     static_assert(sizeof(SegState) % 4 == 0 && sizeof(SegState) / 4 <= T, "a word per thread");
     if (tid < (int)(sizeof(SegState) / 4)) reinterpret_cast<int *>(&st)[tid] = reinterpret_cast<const int *>(sst)[tid];
-    if (tid == 0) sab = 0;
+    if (tid == 0) sab = ctl.wait < 0 ? 1 : 0;
     if (tid < SV_LINE) tot[tid] = 0.0;
     if (lane == 0) {
         vr[rl] = live ? S.r[row] : 0.0;
@@ -567,7 +570,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
                 }
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    ok = ok && sv_wait(ys + (unsigned)hl[k[u]], v[u], pabort);
+                    ok = ok && sv_wait(ys + (unsigned)hl[k[u]], v[u], pabort, ctl.wait);
                     hp[k[u]] = __longlong_as_double((long long)v[u]);
                 }
             }
@@ -616,7 +619,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
         if (nblk > 1) {
             __syncthreads();
             if (wv == 0) sv_put(sv_line(slots_p, it % 3, nblk, blk, wl), tot[wl & 15]);
-            if (!sv_collect<NW>(slots_p, it % 3, nblk, blk, red, wv, wl, pabort)) sab = 1;
+            if (!sv_collect<NW>(slots_p, it % 3, nblk, blk, red, wv, wl, pabort, ctl.wait)) sab = 1;
         }
         __syncthreads();
         if (sab) break;
@@ -652,7 +655,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
             vr[rl] = (vr[rl] - alpha * s) - c;
         }
     }
-    if (sab) {
+    if (sab || (ctl.late && blk == nblk - 1)) {
         if (tid == 0) __hip_atomic_store(pabort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }

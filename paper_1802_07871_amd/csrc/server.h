@@ -510,9 +510,8 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         HIPCHK(hipEventRecord(S->ev_join, S->side));
         for (int c = 0, t0 = 0; c < NCLS - 1; t0 += cls_tiles[c++])
             if (cls_tiles[c]) {
-                launch_solve_prep<R>(CLS[c], T + t0, cls_tiles[c], S->dsegs, st);
-                launch_solve<R>(CLS[c], ctx->ncu, T + t0, cls_tiles[c], S->dsegs,
-                                SolveCtl{ctx->opts.cg_tol, ctx->opts.cg_maxit, 0}, st);
+                launch_solve_prep<R>(ctx, CLS[c], T + t0, cls_tiles[c], S->dsegs, st);
+                launch_solve<R>(CLS[c], ctx->ncu, T + t0, cls_tiles[c], S->dsegs, solve_ctl(ctx, 0), st);
             }
         if (nis_many) {
             const dim3 gm(cls_tiles[NCLS - 1]);
@@ -590,6 +589,7 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         } else if (cls_of(sl) != 0) {
             // its one-launch solve gave up: set up again, multi-launch
             sl.many = true;
+            ctx->give_ups++;
             sl.phase = 0;
         }
     }

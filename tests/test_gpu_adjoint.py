@@ -245,3 +245,29 @@ def test_error_paths(ct, theta):
                                    ctypes.c_void_p(small.data_ptr()), 64, 1.0, ctypes.c_void_p(vF.data_ptr()),
                                    None, g.ctypes.data, None, None)
     assert rc == ct.E_NOMEM
+
+
+@pytest.mark.parametrize("fp64", [True, False], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("way", [1, 2, 3], ids=["multi", "no wait", "crowded"])
+def test_gradient_by_the_multi_launch_solve(ct, oracle_grads, way, fp64):
+    """The adjoint solve in many launches: after a one-launch forward solve,
+    asked for or where its own one-launch solve gave up, and after a forward
+    evaluation that took the same way."""
+    s, th, (w, v, u), ref = oracle_grads["cluster_all_terms"]
+    print(f"[adjoint] way {way} fp64={fp64}", flush=True)
+    import torch
+    vF = torch.as_tensor(np.ascontiguousarray(v.T).reshape(-1), device="cuda")
+    vq = torch.as_tensor(u, device="cuda")
+    rtol, atol = (1e-6, 1e-8) if fp64 else (1e-4, 2e-6)
+    pot = ct.Potential(th, fp64=fp64, cg_tol=1e-12 if fp64 else 1e-9)
+    g, it, sysb = _gpu_grad(ct, pot, s, w, v, u)
+    pot.debug_solve(way)
+    g2, it2 = pot.param_grad(sysb, s.box, s.pbc, w, vF, vq)
+    assert it2 > 0 and pot.debug_solve(way) == (0 if way == 1 else 1)
+    _compare(g2, ref, th, rtol, atol, f"way {way}, one-launch forward")
+    g3, it3, sysb = _gpu_grad(ct, pot, s, w, v, u)
+    assert pot.debug_solve() == (0 if way == 1 else 3)
+    _compare(g3, ref, th, rtol, atol, f"way {way}")
+    # and the one-launch adjoint after a multi-launch forward
+    g4, _ = pot.param_grad(sysb, s.box, s.pbc, w, vF, vq)
+    _compare(g4, ref, th, rtol, atol, f"one-launch adjoint after way {way}")

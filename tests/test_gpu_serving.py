@@ -225,3 +225,30 @@ def test_inputs_past_the_pinned_room(ct, theta):
     # solved again from its own charges: at once, to the solver's tolerance
     assert got[t[2]]["status"] == 0 and got[t[2]]["cg_iters"] <= 2
     assert np.abs(got[t[2]]["q"] - q0).max() <= 1e-8
+
+
+@pytest.mark.parametrize("way", [1, 2, 3], ids=["multi", "no wait", "crowded"])
+def test_requests_by_the_multi_launch_solve(ct, orc, theta, way):
+    """Requests whose one-launch solve gives up are set up again and solved in
+    many launches, beside larger ones that always are (57,600 atoms: two
+    launches per iteration)."""
+    from paper_1802_07871_amd.serving import Server
+    pot = ct.Potential(theta)
+    structs = _requests(10, seed=9) + [G.random_system(33000, 0.7, 2.4, True, seed=93), G.slab_4h(60, 40, 6, seed=94)]
+    assert structs[-1].n == 57600
+    print(f"[serving] way {way}: {[s.n for s in structs]}", flush=True)
+    ref = [pot.compute(s.pos, s.types, s.box, s.pbc, warm=False) for s in structs]
+    pot.debug_solve(way)
+    srv = Server(pot, 6 << 30, max_slots=16)
+    tickets = [srv.submit(s.pos, s.types, s.box, s.pbc) for s in structs]
+    got = srv.wait_all(tickets)
+    srv.close()
+    assert pot.debug_solve() == (0 if way == 1 else len(structs) - 1)
+    for s, t, (E, F, q, _) in zip(structs, tickets, ref):
+        a = got[t]
+        F = F.cpu().numpy()
+        assert a["status"] == 0
+        assert abs(a["E"] - E) / s.n < 1e-6
+        if np.linalg.norm(F) > 0:
+            assert np.linalg.norm(a["F"] - F) / np.linalg.norm(F) < 1e-5
+        assert np.abs(a["q"] - q.cpu().numpy()).max() < 1e-6
