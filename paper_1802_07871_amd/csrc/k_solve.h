@@ -22,8 +22,10 @@
 // the device and hold at most one CU each, later blocks of a launch are
 // never waited for by earlier systems, and every wait is bounded (SV_WAIT);
 // a wait that runs out (the device shared with other work for that long)
-// marks the system (SegState::pabort), all its blocks leave, nothing is
-// written back, and the host takes the multi-launch path from the assembly.
+// marks the system (SegState::pabort), all its blocks leave, and the host takes
+// the multi-launch path from the starting charges on.  A wait can run out in one
+// block when the others have finished, charges, state and status written, so
+// nothing that a solve leaves counts unless pabort is clear.
 #pragma once
 #include "ctbop_dev.h"
 #include "k_qeq.h"
@@ -195,13 +197,15 @@ __device__ __forceinline__ double sv_lane(double v, int k)
                             __builtin_amdgcn_readlane(__double2loint(v), k));
 }
 
-// before the multi-launch solve of a system whose one-launch solve gave up
+// Before the multi-launch solve of a system whose one-launch solve gave up: the
+// state and the status of a part of its blocks that may have finished.
 __global__ void k_solve_retry(const int *seg_ids, Seg *segs)
 {
     SegState *st = segs[seg_ids[blockIdx.x]].sst;
     st->done = 0;
     st->iters = 0;
     st->pabort = 0;
+    st->status &= ~(ST_NOCONV | ST_NOT_PD);
 }
 
 // What the solve needs of the assembled rows: the block's halo (the distinct

@@ -248,7 +248,7 @@ def test_error_paths(ct, theta):
 
 
 @pytest.mark.parametrize("fp64", [True, False], ids=["fp64", "mixed"])
-@pytest.mark.parametrize("way", [1, 2, 3], ids=["multi", "no wait", "crowded"])
+@pytest.mark.parametrize("way", [1, 2, 3, 4], ids=["multi", "no wait", "crowded", "late"])
 def test_gradient_by_the_multi_launch_solve(ct, oracle_grads, way, fp64):
     """The adjoint solve in many launches: after a one-launch forward solve,
     asked for or where its own one-launch solve gave up, and after a forward

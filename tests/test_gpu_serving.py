@@ -227,7 +227,7 @@ def test_inputs_past_the_pinned_room(ct, theta):
     assert np.abs(got[t[2]]["q"] - q0).max() <= 1e-8
 
 
-@pytest.mark.parametrize("way", [1, 2, 3], ids=["multi", "no wait", "crowded"])
+@pytest.mark.parametrize("way", [1, 2, 3, 4], ids=["multi", "no wait", "crowded", "late"])
 def test_requests_by_the_multi_launch_solve(ct, orc, theta, way):
     """Requests whose one-launch solve gives up are set up again and solved in
     many launches, beside larger ones that always are (57,600 atoms: two

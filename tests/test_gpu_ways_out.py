@@ -65,7 +65,7 @@ def _both(ct, theta, s, ref, way, prec, kappa):
 
 
 @pytest.mark.parametrize("prec", ["mixed", "fp64"])
-@pytest.mark.parametrize("way", ["multi", "no wait", "crowded"])
+@pytest.mark.parametrize("way", ["multi", "no wait", "crowded", "late"])
 @pytest.mark.parametrize("case", CASES, ids=[str(c[0]) for c in CASES])
 def test_evaluation(ct, theta, reference, case, way, prec):
     s, ref = reference(case, 0.0)
@@ -74,7 +74,7 @@ def test_evaluation(ct, theta, reference, case, way, prec):
 
 
 @pytest.mark.parametrize("prec", ["mixed", "fp64"])
-@pytest.mark.parametrize("way", ["multi", "no wait", "crowded"])
+@pytest.mark.parametrize("way", ["multi", "no wait", "crowded", "late"])
 @pytest.mark.parametrize("case", FQ_CASES, ids=[str(c[0]) for c in FQ_CASES])
 def test_coupling(ct, theta, reference, case, way, prec):
     s, ref = reference(case, 1.0)
