@@ -22,7 +22,10 @@ __global__ void k_call_init(const int *seg_ids, Seg *segs, int nseg, int force_r
     int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nseg) return;
     SegState *st = segs[seg_ids[k]].sst;
-    st->rebuild = (force_rebuild || !st->built) ? 1 : 0;
+    // (a system of the server whose one-launch solve gave up is set up a second
+    // time: from the lists on, as their status is cleared here and the
+    // multi-launch solve reads halos that the first set-up left out)
+    st->rebuild = (force_rebuild || !st->built || st->pabort) ? 1 : 0;
     st->done = 0;
     st->iters = 0;
     st->status = 0;

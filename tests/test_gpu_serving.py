@@ -252,3 +252,25 @@ def test_requests_by_the_multi_launch_solve(ct, orc, theta, way):
         if np.linalg.norm(F) > 0:
             assert np.linalg.norm(a["F"] - F) / np.linalg.norm(F) < 1e-5
         assert np.abs(a["q"] - q.cpu().numpy()).max() < 1e-6
+
+
+@pytest.mark.parametrize("way", [0, 2, 3], ids=["one launch", "no wait", "crowded"])
+def test_errors_of_the_lists_are_kept(ct, theta, way):
+    """Errors that the lists' build finds (two atoms 0.35 A apart, a Coulomb
+    list that overflows) reach a request that is set up a second time too,
+    and no other one."""
+    from paper_1802_07871_amd.serving import Server
+    pot = ct.Potential(theta, long_cap=320)          # (a row of the good crystal holds 274, of the dense cell 376)
+    pot.debug_solve(way)
+    good = G.zincblende(2, sigma=0.05, seed=95)
+    close = good.pos.copy()
+    close[1] = close[0] + 0.2
+    dense = G.random_system(900, 0.9, 3.2, True, seed=96)
+    print(f"[serving] errors of the lists, way {way}", flush=True)
+    srv = Server(pot, 1 << 28, max_slots=8)
+    t = [srv.submit(good.pos, good.types, good.box, good.pbc), srv.submit(close, good.types, good.box, good.pbc),
+         srv.submit(dense.pos, dense.types, dense.box, dense.pbc)]
+    got = srv.wait_all(t)
+    srv.close()
+    assert pot.debug_solve() == (3 if way else 0)
+    assert [got[k]["status"] for k in t] == [0, ct.E_TOO_CLOSE, ct.E_NEIGH_OVERFLOW]
