@@ -563,6 +563,14 @@ int size_kind(ctbop_ctx *ctx, int n)
 // The kind that a call's solve takes.
 int solve_kind(ctbop_ctx *ctx, int n) { return ctx->way == CTBOP_SOLVE_MULTI ? 0 : size_kind(ctx, n); }
 
+// The kind of an evaluation's solve.  The coupling's one-launch solve has no
+// SV_TW blocks, and keeps its bonds' halo positions beside the halo list.
+int eval_kind(ctbop_ctx *ctx, const Seg &S)
+{
+    const int kind = solve_kind(ctx, S.n);
+    return S.fqk > 0.0 && (kind == SV_WIDE || S.Wl <= S.Wb) ? 0 : kind;
+}
+
 // What the one-launch solve is told: its tolerance, and the way out that the
 // context asks for.
 SolveCtl solve_ctl(const ctbop_ctx *ctx, int relative)
@@ -647,7 +655,8 @@ void launch_cg1(ctbop_ctx *ctx, bool split, const Tile *tiles, int nt, const int
 
 // The row kernels over nt tiles, a tile or FINE rows per block.  The list
 // build of FINE-row blocks leaves out the halos, which only the multi-launch
-// solve reads; lists, reverse slots and Coulomb rows are the same either way.
+// product reads (without them it takes 16-bit offsets); lists, reverse slots
+// and Coulomb rows are the same either way.
 template <typename R>
 void launch_build(bool fine, const Tile *tiles, int nt, Seg *segs, const Params<R> &prm, hipStream_t st)
 {
@@ -726,6 +735,11 @@ void launch_lists(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags)
         hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
         hipLaunchKernelGGL(k_qfix, g, b, 0, st, P.dtiles, P.dseg);
     }
+    // FINE-row blocks and no halos up to the largest one-launch solve, also with
+    // the coupling, whose own ends at 128 tiles: its multi-launch product then
+    // gathers p by 16-bit offsets, no slower at these sizes (36,864 atoms, an
+    // evaluation 2.71 ms and 2.81 with new lists; with halos 2.75 and 3.21;
+    // 49,152 atoms 2.75 and 2.87, 2.79 and 3.25)
     const bool fine = solve_kind(ctx, P.L.seg.n) != 0;
     {
         Timed t(ctx, 7, st);
@@ -786,9 +800,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         if (P.own) HIPCHK(hipEventRecord(ctx->ev_join, ctx->side));
         return CTBOP_OK;
     };
-    // (the coupling's one-launch solve keeps its bonds' halo positions beside the halo list)
-    int kind = solve_kind(ctx, P.L.seg.n);
-    if (fq && (kind == SV_WIDE || P.L.seg.Wl <= P.L.seg.Wb)) kind = 0;
+    const int kind = eval_kind(ctx, P.L.seg);
     if (fq || kind) {
         const int rc = side_launch();
         if (rc) return rc;

@@ -146,3 +146,28 @@ def test_unsupported_entry_points_refuse(ct, theta):
     with pytest.raises(ct.CtbopError) as e:
         ct.Potential(theta, fq_kappa=-1.0)
     assert e.value.code == ct.E_INVAL
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("cells,n", [((36, 32, 8), 36864), ((50, 42, 6), 50400)])
+def test_coupling_of_large_systems(ct, orc, theta, cells, n, prec):
+    """Past the one-launch solve of the coupling (32,512 atoms): where the
+    linear solve still runs in one launch (36,864) the lists have no halos and
+    the product takes 16-bit offsets and full entries, or on request halo
+    positions; above, halo positions for most tiles."""
+    s = G.slab_4h(*cells, seed=165)
+    s.pos = s.pos + np.random.Generator(np.random.PCG64(166)).normal(0, 0.05, s.pos.shape)
+    assert s.n == n
+    print(f"[fq parity] slab n={n} {prec}", flush=True)
+    pot = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=1e-9 if prec == "mixed" else 1e-13, fq_kappa=0.5)
+    Eo, Fo, qo, _ = orc.evaluate_fq(s.pos, s.types, s.box, s.pbc, theta, 0.5, tol=1e-13)
+    t = TOL[prec]
+    for way in (0, 1):
+        pot.debug_solve(way)
+        E, F, q, info = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False, force_rebuild=True)
+        assert info["status"] == 0
+        halo = 2 * info["nnz_coul_halo"] > info["nnz_coul"]
+        assert halo == (way == 1 or n > 49152)
+        assert abs(E - Eo) / s.n <= t["E"]
+        assert np.linalg.norm(F.cpu().numpy() - Fo) / np.linalg.norm(Fo) <= t["F"]
+        assert np.abs(q.cpu().numpy() - qo).max() <= t["q"]
