@@ -47,6 +47,9 @@
  *              stops on a device-side test, so the host waits on that stream
  *              between batches of solver iterations (cg_check) to read the
  *              flag; with info != NULL it also waits at the end to report.
+ *              Calls on several streams and threads of a process (a context
+ *              each) share a device: charge solves that do not fit on it
+ *              together take turns there.
  *   errors     every function returns a status; 0 = CTBOP_OK.  Errors found on
  *              the device (close contacts, list overflow, charge solve not
  *              converged or not positive definite) land in a status word in
@@ -380,8 +383,9 @@ const char *ctbop_last_error(void);
 /* The way that the charge solves of this context take from the next call on,
  * for tests: small and middling systems solve in one launch, with the
  * multi-launch solve of larger ones as the way out of a solve that gives up.
- * Results are the same to the solve's tolerance.  give_ups (NULL or one
- * long) gets the one-launch solves given up on this context so far.  E_INVAL
+ * Results are the same to the solve's tolerance.  After a wait that ran out a
+ * context takes the multi-launch solve for its next 256 evaluations; this call
+ * ends that.  give_ups (NULL or one long) gets the one-launch solves given up on this context so far.  E_INVAL
  * for any other way. */
 #define CTBOP_SOLVE_DEFAULT 0  /* by size                                              */
 #define CTBOP_SOLVE_MULTI   1  /* every system by the multi-launch solve               */

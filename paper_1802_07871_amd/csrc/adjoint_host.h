@@ -153,12 +153,18 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
     bool solved = false;
     if (const int kind = solve_kind(ctx, P.L.seg.n)) {
         launch_solve_prep<R>(ctx, kind, P.dtiles, P.L.ntile, dadj, st);
+        SolvePass pass;
+        const int prc = pass.enter(solve_blocks(kind, P.L.ntile), ctx->ncu, st);
+        if (prc) return prc;
         launch_solve<R>(kind, ctx->ncu, P.dtiles, P.L.ntile, dadj, solve_ctl(ctx, 1), st);
         HIPCHK(hipGetLastError());
+        const int lrc = pass.launched();
+        if (lrc) return lrc;
         HIPCHK(hipMemcpyAsync(flag, &asst->done, 3 * sizeof(int), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
+        pass.leave();
         solved = flag[0] && !flag[2];
-        if (!solved) ctx->give_ups++;
+        if (!solved) gave_up(ctx, flag[2]);
     }
     if (!solved) {
         if (size_kind(ctx, P.L.seg.n)) {

@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -93,10 +94,12 @@ struct ctbop_ctx {
     // tiles per launch of the side stream's kernels: two blocks per CU, so
     // that they leave room for the solve's product beside them
     int side_chunk = 512;
-    int ncu = 0;                 // compute units of the device, at most SV_MAX_BLOCKS (0: not asked yet)
+    std::atomic<int> ncu{0};     // compute units of the device, at most SV_MAX_BLOCKS (0: not asked yet)
+    int turn_dev = -1;           // device of join_turn
     // way of the charge solve (ctbop_debug_solve) and one-launch solves given up
     std::atomic<int> way{CTBOP_SOLVE_DEFAULT};
     std::atomic<long> give_ups{0};
+    std::atomic<int> rest{0};    // evaluations to come by the multi-launch solve, after a wait that ran out
     // optional per-kernel timing with HIP events on the caller's stream
     int profile = 0;
     unsigned profile_mask = 0xffffu;   // kernel classes timed while profiling is on
@@ -437,6 +440,12 @@ void ev_harvest(ctbop_ctx *ctx)
     ctx->ev_pending.swap(keep);
 }
 
+} // namespace
+
+#include "solve_turn.h"
+
+namespace {
+
 // the side stream and its two events, created on first use
 int side_stream(ctbop_ctx *ctx)
 {
@@ -448,7 +457,7 @@ int side_stream(ctbop_ctx *ctx)
     HIPCHK(hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
     HIPCHK(hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
     HIPCHK(hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming));
-    return CTBOP_OK;
+    return join_turn(ctx->turn_dev);
 }
 
 int map_status(int st)
@@ -548,20 +557,46 @@ constexpr int SV_WIDE = 1;
 int size_kind(ctbop_ctx *ctx, int n)
 {
     if (n > SV_MAX_ATOMS_W || ctx->opts.long_cap < SV_MIN_WL) return 0;
-    if (ctx->ncu == 0) {
-        int dev = 0, ncu = 0;
+    int ncu = ctx->ncu;
+    if (ncu == 0) {
+        int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
-        ctx->ncu = std::min(ncu, SV_MAX_BLOCKS);
+        ctx->ncu = ncu = std::min(ncu, SV_MAX_BLOCKS);
     }
-    if (n <= sv_rows(8) * ctx->ncu) return 8;
-    if (n <= std::min(sv_rows(4) * ctx->ncu, SV_MAX_ATOMS)) return 4;
-    return n > 128 * TILE && 4 * n <= 3 * sv_rows(4, SV_TW) * ctx->ncu ? SV_WIDE : 0;
+    if (n <= sv_rows(8) * ncu) return 8;
+    if (n <= std::min(sv_rows(4) * ncu, SV_MAX_ATOMS)) return 4;
+    return n > 128 * TILE && 4 * n <= 3 * sv_rows(4, SV_TW) * ncu ? SV_WIDE : 0;
 }
 
-// The kind that a call's solve takes.
-int solve_kind(ctbop_ctx *ctx, int n) { return ctx->way == CTBOP_SOLVE_MULTI ? 0 : size_kind(ctx, n); }
+// The kind that a call's solve takes: by size, but for SOLVE_REST evaluations
+// of a context after a wait that ran out.  That takes work outside this
+// process (or kernels of it that hold the CUs) for 10 ms, which then costs each
+// evaluation little, and is the one case where a system is solved in another
+// order than elsewhere: the results agree to the solve's tolerance, not bit
+// for bit.
+constexpr int SOLVE_REST = 256;
+int solve_kind(ctbop_ctx *ctx, int n)
+{
+    return ctx->way == CTBOP_SOLVE_MULTI || ctx->rest > 0 ? 0 : size_kind(ctx, n);
+}
+
+// A one-launch solve of the context gave up, for the reasons in pabort.
+void gave_up(ctbop_ctx *ctx, int pabort)
+{
+    ctx->give_ups++;
+    if (pabort & PA_WAIT) ctx->rest = SOLVE_REST;
+}
+
+// An evaluation by the multi-launch solve that would have taken one launch.
+void rested(ctbop_ctx *ctx)
+{
+    int r = ctx->rest;
+    while (r > 0 && !ctx->rest.compare_exchange_weak(r, r - 1)) {
+    }
+}
+int solve_blocks(int kind, int nt) { return kind == SV_WIDE ? nt : nt * (TILE / sv_rows(kind)); }
 
 // The kind of an evaluation's solve.  The coupling's one-launch solve has no
 // SV_TW blocks, and keeps its bonds' halo positions beside the halo list.
@@ -817,9 +852,11 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
             Timed t(ctx, 8, st);
             launch_solve_prep<R>(ctx, kind, P.dtiles, nt, P.dseg, st);
         }
+        SolvePass pass;
+        if (fq && P.own) HIPCHK(hipStreamWaitEvent(st, ctx->ev_join, 0));   // the bonds and their weights
+        const int prc = pass.enter(solve_blocks(kind, nt), ctx->ncu, st);
+        if (prc) return prc;
         if (fq) {
-            // the bonds and their weights
-            if (P.own) HIPCHK(hipStreamWaitEvent(st, ctx->ev_join, 0));
             Timed t(ctx, 0, st);
             launch_solve_fq<R>(kind, P.dtiles, nt, P.dseg, solve_ctl(ctx, 0), st);
         } else {
@@ -827,15 +864,18 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
             launch_solve<R>(kind, ctx->ncu, P.dtiles, nt, P.dseg, solve_ctl(ctx, 0), st);
         }
         HIPCHK(hipGetLastError());
+        const int lrc = pass.launched();
+        if (lrc) return lrc;
         HIPCHK(hipMemcpyAsync(flag, &P.L.seg.sst->done, 3 * sizeof(int), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
+        pass.leave();
         if (ctx->profile) ev_harvest(ctx);
         solved = flag[0] && !flag[2];
         if (!solved) {
             // given up: the starting charges again (unless the solve never
             // began), then the multi-launch solve
-            assembled = flag[2] == 2;
-            ctx->give_ups++;
+            assembled = !(flag[2] & PA_WAIT);
+            gave_up(ctx, flag[2]);
             if (!assembled) {
                 hipLaunchKernelGGL(k_gather<R>, g, b, 0, st, P.dtiles, P.dseg, start_mode(P, flags));
                 hipLaunchKernelGGL(k_fin_qshift, g1, b, 0, st, sid, P.dseg);
@@ -843,6 +883,8 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
             }
             hipLaunchKernelGGL(k_solve_retry, g1, g1, 0, st, sid, P.dseg);
         }
+    } else if (size_kind(ctx, P.L.seg.n)) {
+        rested(ctx);
     }
     if (!solved) {
         if (!assembled) {
@@ -1060,6 +1102,7 @@ int ctbop_destroy(ctbop_ctx *ctx)
         (void)hipStreamDestroy(ctx->side);
         (void)hipEventDestroy(ctx->ev_fork);
         (void)hipEventDestroy(ctx->ev_join);
+        leave_turn(ctx->turn_dev);
     }
     if (ctx->host_flag) (void)hipHostFree(ctx->host_flag);
     for (auto e : ctx->ev_free) (void)hipEventDestroy(e);
@@ -1405,6 +1448,7 @@ int ctbop_debug_solve(ctbop_ctx *ctx, int way, long *give_ups)
 {
     if (!ctx || way < CTBOP_SOLVE_DEFAULT || way > CTBOP_SOLVE_LATE) return fail(CTBOP_E_INVAL, "bad argument");
     ctx->way = way;
+    ctx->rest = 0;
     if (give_ups) *give_ups = ctx->give_ups;
     return CTBOP_OK;
 }

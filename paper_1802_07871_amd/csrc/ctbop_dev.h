@@ -38,6 +38,9 @@ constexpr uint8_t SL_HALO = 0, SL_FULL = 1, SL_OFF16 = 2, SL_HALO16 = 3;
 constexpr int GRP = 8;                 // entries per group of a 12-bit halo slice
 static_assert(HALO_MAX <= 4096, "halo positions of a group are 12 bits each");
 
+// why a one-launch solve was given up: a wait ran out; before it began, a block
+// has too many neighbours, or a bond's partner is not among them
+constexpr int PA_WAIT = 1, PA_CROWDED = 2, PA_BOND = 4;
 // status bits (mapped to CTBOP_E_* codes on the host)
 constexpr int ST_TOO_CLOSE = 1, ST_NOCONV = 2, ST_NOT_PD = 4, ST_OVERFLOW = 8, ST_REV = 16;
 
@@ -71,7 +74,7 @@ struct SegState {
     int par;           // split iteration: which set of the update's partials is current
     int done;          // charge solve finished
     int iters;
-    int pabort;        // one-launch solve: given up (the host takes the multi-launch path)
+    int pabort;        // one-launch solve: given up (PA_* bits; the host takes the multi-launch path)
     int status;        // ST_* bits, sticky until the next rebuild/call reset
     int maxl, maxs;    // largest list rows at the last build
     int built;         // lists exist

@@ -1430,7 +1430,7 @@ __global__ void k_collect(const int *seg_ids, Seg *segs, int nseg, int4 *out)
     int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nseg) return;
     const SegState *st = segs[seg_ids[k]].sst;
-    out[k] = make_int4(st->done && !st->pabort, st->forces_done, st->status, st->iters);
+    out[k] = make_int4(st->done && !st->pabort, st->pabort ? -st->pabort : st->forces_done, st->status, st->iters);
 }
 
 } // namespace ctbop

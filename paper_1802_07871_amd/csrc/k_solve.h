@@ -20,9 +20,10 @@
 //
 // No block may wait forever: the blocks of one system are at most the CUs of
 // the device and hold at most one CU each, later blocks of a launch are
-// never waited for by earlier systems, and every wait is bounded (SV_WAIT);
-// a wait that runs out (the device shared with other work for that long)
-// marks the system (SegState::pabort), all its blocks leave, and the host takes
+// never waited for by earlier systems, the host lets no more solves of the
+// process run at once than fit (solve_turn.h), and every wait is bounded
+// (SV_WAIT); a wait that runs out (the device shared with other processes, or
+// with kernels that long) marks the system (SegState::pabort), all its blocks leave, and the host takes
 // the multi-launch path from the starting charges on.  A wait can run out in one
 // block when the others have finished, charges, state and status written, so
 // nothing that a solve leaves counts unless pabort is clear.
@@ -40,7 +41,7 @@ constexpr int SV_TW = 1024;
 constexpr int SV_MAX_ATOMS_W = 192 * TILE;
 constexpr unsigned long long SV_EMPTY = ~0ull;
 constexpr unsigned long long SV_NAN = 0x7ff8000000000000ull;
-constexpr long long SV_WAIT = 5000000;      // ticks of the 100 MHz clock: 50 ms per wait
+constexpr long long SV_WAIT = 1000000;      // ticks of the 100 MHz clock: 10 ms per wait
 constexpr int SV_NSUM = 14;
 constexpr int SV_MAX_BLOCKS = 256;          // blocks of one system
 constexpr int SV_LINE = 16;                 // a block's sums: one 128-byte line,
@@ -314,7 +315,7 @@ __global__ void __launch_bounds__(T) k_solve_prep(const Tile *tiles, Seg *segs, 
     }
     if (tid == 0) {
         region[(size_t)RB * Wl - 1] = (uint32_t)total;
-        if (total > most) atomicOr(&S.sst->pabort, 2);   // (before the solve has changed anything)
+        if (total > most) atomicOr(&S.sst->pabort, PA_CROWDED);   // (before the solve has changed anything)
     }
     // the FP32 block row, J on the diagonal; identity rows past n
     {
@@ -660,7 +661,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
         }
     }
     if (sab || (ctl.late && blk == nblk - 1)) {
-        if (tid == 0) __hip_atomic_store(pabort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(pabort, PA_WAIT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
     if (lane == 0 && live) S.q[row] = vq[rl];

@@ -416,7 +416,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         __syncthreads();
     }
     if (sab || (ctl.late && blk == nblk - 1)) {
-        if (tid == 0) __hip_atomic_store(pabort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(pabort, PA_WAIT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
     if (lane == 0 && live) S.q[row] = va[Q_][rl];
@@ -469,7 +469,7 @@ __global__ void __launch_bounds__(TILE) k_solve_fq_bonds(const Tile *tiles, Seg 
             else hi = mid;
         }
         if (nh == 0 || (int)list[lo] != j) {
-            atomicOr(&S.sst->pabort, 1);
+            atomicOr(&S.sst->pabort, PA_BOND);
             return;
         }
         out[e] = (uint16_t)lo;

@@ -20,7 +20,9 @@
 //      retain) their regions.
 // Requests that arrive during a tick join at the next one, so work of
 // requests of any size and phase overlaps on the device.  Each segment's
-// arithmetic and reduction order do not depend on the other segments, so a
+// arithmetic and reduction order do not depend on the other segments (but for a
+// one-launch solve that gives up because work outside this process, or a
+// kernel that holds the CUs for 10 ms, keeps its blocks waiting), so a
 // result is bitwise the same alone and in the mix.
 #pragma once
 #include <chrono>
@@ -69,6 +71,7 @@ struct SrvSlot {
     bool placed = false;            // placed since the last tick, its inputs not yet on the device
     bool fresh = false;             // in a new region
     bool many = false;              // its one-launch solve gave up: multi-launch solve
+    int kind = 0;                   // of its solve, from its set-up on (solve_kind)
     long sys_id = -1;
     double last_use = 0;
     Sig sig;
@@ -165,6 +168,8 @@ struct ctbop_server {
     // Coulomb forces (as the single-system path does)
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    hipEvent_t ev_solve = nullptr;    // after a tick's one-launch solves
+    int turn_dev = -1;
     // device tables at the head of the arena
     Seg *dsegs = nullptr;
     Tile *dtiles_setup = nullptr, *dtiles_act = nullptr;
@@ -424,6 +429,7 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         act.push_back(k);
     }
     if (act.empty()) return CTBOP_OK;
+    SolvePass pass;
     // the largest first: of a batch that fills the device more than once the
     // last systems to run are then the smallest
     std::stable_sort(act.begin(), act.end(), [&](int a, int b) { return S->slots[a].req.n > S->slots[b].req.n; });
@@ -439,7 +445,13 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
     // which the iterations below run over.
     constexpr int NCLS = 4, CLS[NCLS] = {8, 4, SV_WIDE, 0};
     int cls_tiles[NCLS] = {0, 0, 0, 0}, nis_many = 0, nta_many = 0, nia_many = 0;
-    auto cls_of = [&](const SrvSlot &sl) { return sl.many ? 0 : solve_kind(ctx, sl.L.seg.n); };
+    for (int k : act) {
+        SrvSlot &sl = S->slots[k];
+        if (sl.phase != 0) continue;
+        sl.kind = sl.many ? 0 : solve_kind(ctx, sl.L.seg.n);
+        if (!sl.many && !sl.kind && size_kind(ctx, sl.L.seg.n)) rested(ctx);
+    }
+    auto cls_of = [](const SrvSlot &sl) { return sl.kind; };
     for (int c = 0; c < NCLS; c++)
         for (int k : act) {
             SrvSlot &sl = S->slots[k];
@@ -508,11 +520,22 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         launch_bond<R>(fine, T, nts, S->dsegs, ctx->pd, S->side);
         launch_force_cov<R>(fine, T, nts, S->dsegs, prm, S->side);
         HIPCHK(hipEventRecord(S->ev_join, S->side));
+        if (nto) {
+            // (the kinds' launches run one after another)
+            int most = 0;
+            for (int c = 0; c < NCLS - 1; c++) most = std::max(most, solve_blocks(CLS[c], cls_tiles[c]));
+            const int prc = pass.enter(most, ctx->ncu, st);
+            if (prc) return prc;
+        }
         for (int c = 0, t0 = 0; c < NCLS - 1; t0 += cls_tiles[c++])
             if (cls_tiles[c]) {
                 launch_solve_prep<R>(ctx, CLS[c], T + t0, cls_tiles[c], S->dsegs, st);
                 launch_solve<R>(CLS[c], ctx->ncu, T + t0, cls_tiles[c], S->dsegs, solve_ctl(ctx, 0), st);
             }
+        if (nto) {
+            const int lrc = pass.launched(S->ev_solve);
+            if (lrc) return lrc;
+        }
         if (nis_many) {
             const dim3 gm(cls_tiles[NCLS - 1]);
             const Tile *Tm = T + nto;
@@ -584,13 +607,13 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
     for (int a = 0; a < nia; a++) {
         SrvSlot &sl = S->slots[hia[a]];
         sl.phase = 1;
-        if (S->hflags[a].y) {
+        if (S->hflags[a].y > 0) {
             fin.push_back(a);
         } else if (cls_of(sl) != 0) {
             // its one-launch solve gave up: set up again, multi-launch
             sl.many = true;
-            ctx->give_ups++;
             sl.phase = 0;
+            gave_up(ctx, -S->hflags[a].y);
         }
     }
     bool copies = false;
@@ -674,6 +697,8 @@ void release_handles(ctbop_server *S)
     }
     if (S->ev_fork) (void)hipEventDestroy(S->ev_fork);
     if (S->ev_join) (void)hipEventDestroy(S->ev_join);
+    if (S->ev_solve) (void)hipEventDestroy(S->ev_solve);
+    leave_turn(S->turn_dev);
     if (S->htiles) (void)hipHostFree(S->htiles);
     if (S->hids) (void)hipHostFree(S->hids);
     if (S->hflags) (void)hipHostFree(S->hflags);
@@ -778,6 +803,8 @@ int create_server(ctbop_ctx *ctx, void *arena, size_t arena_bytes, int max_slots
         hipStreamCreateWithFlags(&S->side, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&S->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&S->ev_join, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&S->ev_solve, hipEventDisableTiming) != hipSuccess ||
+        join_turn(S->turn_dev) != CTBOP_OK ||
         hipHostMalloc((void **)&S->htiles, sizeof(Tile) * 2 * S->max_tiles, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&S->hids, sizeof(int) * 2 * max_slots, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&S->hflags, per_slot * max_slots, hipHostMallocDefault) != hipSuccess) {

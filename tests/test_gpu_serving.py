@@ -243,7 +243,9 @@ def test_requests_by_the_multi_launch_solve(ct, orc, theta, way):
     tickets = [srv.submit(s.pos, s.types, s.box, s.pbc) for s in structs]
     got = srv.wait_all(tickets)
     srv.close()
-    assert pot.debug_solve() == (0 if way == 1 else len(structs) - 1)
+    # (after a wait that ran out, later requests take the multi-launch solve at once)
+    gave_up = pot.debug_solve()
+    assert gave_up == (len(structs) - 1 if way == 3 else 0) if way in (1, 3) else 0 < gave_up < len(structs)
     for s, t, (E, F, q, _) in zip(structs, tickets, ref):
         a = got[t]
         F = F.cpu().numpy()
@@ -272,5 +274,6 @@ def test_errors_of_the_lists_are_kept(ct, theta, way):
          srv.submit(dense.pos, dense.types, dense.box, dense.pbc)]
     got = srv.wait_all(t)
     srv.close()
-    assert pot.debug_solve() == (3 if way else 0)
+    gave_up = pot.debug_solve()
+    assert gave_up == way if way != 2 else 0 < gave_up <= 3
     assert [got[k]["status"] for k in t] == [0, ct.E_TOO_CLOSE, ct.E_NEIGH_OVERFLOW]

@@ -54,6 +54,7 @@ def _both(ct, theta, s, ref, way, prec, kappa):
     """A cold call, and a second one from its charges."""
     pot = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=1e-9 if prec == "mixed" else 1e-13, fq_kappa=kappa)
     assert pot.debug_solve(WAYS[way]) == 0
+    # (asked again before each call: after a wait that ran out a context rests)
     _check(pot.compute(s.pos, s.types, s.box, s.pbc, warm=False), ref, s.n, prec)
     gave_up = pot.debug_solve(WAYS[way])
     assert gave_up == (0 if way == "multi" else 1)
@@ -112,11 +113,84 @@ def test_molecular_dynamics(ct, theta, kappa):
         pot.debug_solve(way)
         x, v, F, q, th, info = pot.md_run(s.pos, vel, s.types, s.box, s.pbc, 0.5, 10, thermo_every=1)
         assert info["status"] == 0
-        assert pot.debug_solve() == (11 if way > 1 else 0)
+        # (after a wait that ran out the next evaluations take the multi-launch solve)
+        assert pot.debug_solve() == (0, 0, 1, 11)[way]
         out.append((th, q.cpu().numpy()))
     for th, q in out[1:]:
         assert np.abs(th - out[0][0]).max() / s.n < 1e-10
         assert np.abs(q - out[0][1]).max() < 1e-8
+
+
+def test_rest_after_a_wait_that_ran_out(ct, theta):
+    """A context whose solve gave up waiting takes the multi-launch solve for
+    its next 256 evaluations, then the one-launch solve again."""
+    s = G.random_system(300, 0.7, 2.6, True, seed=4500)
+    pot = ct.Potential(theta)
+    print("[ways out] rest", flush=True)
+    usual = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)[0]
+    pot.debug_solve(WAYS["no wait"])
+    E = [pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)[0] for _ in range(258)]
+    assert pot.debug_solve() == 2
+    assert max(abs(e - usual) for e in E) / s.n < 1e-9
+    fresh = pot.system(s.n, s.box, s.pbc)
+    assert pot.compute(s.pos, s.types, s.box, s.pbc, warm=False, sysbuf=fresh)[0] == usual
+
+
+def test_callers_on_one_device(ct, theta):
+    """Four threads with a stream and a context each, and a server beside them,
+    with solves that fit the device one at a time only, one that always fits
+    and one with 1024 threads per block: none gives up, and every result is bit
+    for bit the lone caller's."""
+    import threading
+
+    import torch
+    from paper_1802_07871_amd.serving import Server
+    systems = [G.random_system(n, 0.7, 2.6, True, seed=4600 + n) for n in (12000, 20000, 600, 33000)]
+    requests = [G.random_system(n, 0.7, 2.6, True, seed=4700 + n) for n in (9000, 300, 17000, 2500)]
+    pot = ct.Potential(theta)
+    alone = [pot.compute(s.pos, s.types, s.box, s.pbc, warm=False) for s in systems + requests]
+    torch.cuda.synchronize()
+    print("[ways out] callers on one device", flush=True)
+    errors = []
+
+    def same(got, ref):
+        return got[0] == ref[0] and bool((got[1] == ref[1]).all()) and bool((got[2] == ref[2]).all())
+
+    def caller(k):
+        try:
+            s = systems[k]
+            mine = ct.Potential(theta)
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                buf = mine.system(s.n, s.box, s.pbc).buf
+                for _ in range(25):
+                    # (a new system each time: its state starts the sums of the next solve)
+                    got = mine.compute(s.pos, s.types, s.box, s.pbc, warm=False,
+                                       sysbuf=mine.system(s.n, s.box, s.pbc, buf=buf))
+                    stream.synchronize()
+                    if not same(got, alone[k]):
+                        raise AssertionError(f"caller {k}: other bits than alone")
+            if mine.debug_solve() != 0:
+                raise AssertionError(f"caller {k}: {mine.debug_solve()} solves given up")
+        except BaseException as e:
+            errors.append(e)
+
+    threads = [threading.Thread(target=caller, args=(k,)) for k in range(len(systems))]
+    for t in threads:
+        t.start()
+    theirs = ct.Potential(theta)
+    srv = Server(theirs, 2 << 30, max_slots=8)
+    for _ in range(8):
+        tickets = [srv.submit(s.pos, s.types, s.box, s.pbc) for s in requests]
+        got = srv.wait_all(tickets)
+        for t, (E, F, q, _) in zip(tickets, alone[len(systems):]):
+            assert got[t]["status"] == 0 and got[t]["E"] == E
+            assert np.array_equal(got[t]["F"], F.cpu().numpy()) and np.array_equal(got[t]["q"], q.cpu().numpy())
+    srv.close()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    assert theirs.debug_solve() == 0
 
 
 def test_bad_way_is_refused(ct, theta):
