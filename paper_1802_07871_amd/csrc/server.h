@@ -414,7 +414,9 @@ int send_placed(ctbop_server *S, const std::vector<int> &act)
 // chunk: the tick goes on until an active system has converged (or the
 // iteration limit), so that it is harvested at once, unless a request
 // arrives, which ends it at the next check once cg_iters have run.  A lone
-// request is then served in one tick, like a plain call.
+// request is then served in one tick, like a plain call.  Systems solved in one
+// launch have converged by then: a tick that holds one does not poll, so that
+// its result does not wait for a large system's solve.
 template <typename R>
 int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
 {
@@ -551,6 +553,7 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         CgCtl ctl{ctx->opts.cg_tol, ctx->opts.cg_maxit};
         // single-reduction solve: a solve of n iterations takes n + 1 rounds
         // (its first finalize counts none)
+        poll = poll && nia == nia_many;
         const int limit = nia_many == 0 ? 0 : poll ? ctx->opts.cg_maxit + 2 : cg_iters;
         for (int c = 0; c < limit;) {
             const int first = std::max(ctx->opts.cg_check, std::min(S->iters_hint, ctx->opts.cg_maxit) + 1);
@@ -584,10 +587,11 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
         hipLaunchKernelGGL(k_collect, dim3((nia + 63) / 64), dim3(64), 0, st, sid, S->dsegs, nia, S->dflags);
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(S->hflags, S->dflags, sizeof(int4) * nia, hipMemcpyDeviceToHost, st));
-        // results of those finished, for which there is pinned room
+        // results of those finished, for which there is pinned room: handed
+        // out to the systems solved in one launch first, the smallest first
         size_t at = 0;
         int most = 1;
-        for (int a = 0; a < nia; a++) {
+        for (int a = nia - 1; a >= 0; a--) {
             const SrvReq &r = S->slots[hia[a]].req;
             const size_t f = r.F_out ? 24 * (size_t)r.n : 0, b = f + (r.q_out ? 8 * (size_t)r.n : 0);
             SrvOut &o = S->hout[a];

@@ -277,3 +277,23 @@ def test_errors_of_the_lists_are_kept(ct, theta, way):
     gave_up = pot.debug_solve()
     assert gave_up == way if way != 2 else 0 < gave_up <= 3
     assert [got[k]["status"] for k in t] == [0, ct.E_TOO_CLOSE, ct.E_NEIGH_OVERFLOW]
+
+
+def test_small_requests_do_not_wait_for_a_large_one(ct, theta):
+    """Requests solved in one launch beside one that takes many (74,088
+    atoms): they are delivered in an earlier tick, with the results of a plain
+    call."""
+    from paper_1802_07871_amd.serving import Server
+    pot = ct.Potential(theta)
+    big = G.zincblende(21, sigma=0.05, seed=97)
+    small = [G.zincblende(k, sigma=0.05, seed=98 + k) for k in (2, 4)]
+    print(f"[serving] small requests beside n={big.n}", flush=True)
+    ref = [pot.compute(s.pos, s.types, s.box, s.pbc, warm=False) for s in [big] + small]
+    srv = Server(pot, 3 << 30, max_slots=8)
+    t = [srv.submit(s.pos, s.types, s.box, s.pbc) for s in [big] + small]
+    got = srv.wait_all(t)
+    srv.close()
+    for k, (E, F, q, _) in zip(t, ref):
+        assert got[k]["status"] == 0 and got[k]["E"] == E
+        assert np.array_equal(got[k]["F"], F.cpu().numpy()) and np.array_equal(got[k]["q"], q.cpu().numpy())
+    assert all(got[k]["t_done"] < got[t[0]]["t_done"] for k in t[1:])
