@@ -148,7 +148,11 @@ typedef struct {
                                          solver's sliced copy (the rest: halo positions
                                          or 16-bit offsets)                            */
     unsigned long long nnz_coul_slots; /* entry slots the solver's product reads: per
-                                          slice of 64 rows, 64 x its longest row */
+                                          slice of 64 rows, 64 x its longest row; where
+                                          the solve runs in one launch, the longest of
+                                          the rows that share a wave, in groups of eight
+                                          entries per lane, and single entries past what
+                                          a lane's registers hold                   */
     unsigned long long n_bonds;        /* covalent bonds (ordered pairs inside S_ij) at the
                                           last evaluation                              */
     unsigned long long n_triplets;     /* ordered bond pairs (i; j, k), j != k, sharing

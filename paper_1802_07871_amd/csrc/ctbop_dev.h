@@ -98,7 +98,7 @@ struct SegState {
     double nnz_coul;                          // Coulomb entries inside rc at the last assembly
     double nnz_wide;                          // of which in slices that keep full entries
     double nnz_halo;                          // of which in slices of halo positions
-    double nnz_slots;                         // entry slots the sliced product reads: 64 x longest row, per slice
+    double nnz_slots;                         // entry slots the product reads (ctbop_info)
     double nbond, ntrip;                      // bonds and ordered bond pairs (i; j, k) at the last evaluation
     // charge coupling (f_q) solve: p^T r, p^T H p and the coupling part of
     // phi'(0) along the current direction (line search); single-reduction

@@ -43,6 +43,7 @@ constexpr unsigned long long SV_EMPTY = ~0ull;
 constexpr unsigned long long SV_NAN = 0x7ff8000000000000ull;
 constexpr long long SV_WAIT = 1000000;      // ticks of the 100 MHz clock: 10 ms per wait
 constexpr int SV_NSUM = 14;
+constexpr int SV_SLOTS = SV_NSUM;           // and, in the first iteration, the slots that a product reads
 constexpr int SV_MAX_BLOCKS = 256;          // blocks of one system
 constexpr int SV_LINE = 16;                 // a block's sums: one 128-byte line,
 constexpr int SV_REP = 4;                   // in as many copies, a quarter of the blocks reading each
@@ -101,6 +102,18 @@ template <typename T> __device__ __forceinline__ T *uni(T *p)
     const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b);
     const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
     return (T *)(((unsigned long long)hi << 32) | lo);
+}
+
+// Entry slots that a product of the block's rows reads, into tot[SV_SLOTS]: of
+// every wave the groups of eight per lane of its longest row, and what longer
+// rows than the registers hold stream.  All threads; n is zero before.
+template <int E, int LPR>
+__device__ __forceinline__ void sv_slot_count(int nch, int cnt, int lane, int wl, int *n, double *tot)
+{
+    if (wl == 0) atomicAdd(n, 64 * min(8 * nch, E));
+    if (lane == 0 && cnt > E * LPR) atomicAdd(n, cnt - E * LPR);
+    __syncthreads();
+    if (threadIdx.x == 0) tot[SV_SLOTS] = (double)*n;
 }
 
 // sum over the LPR lanes of a row, in every lane (DPP moves within 16 lanes)
@@ -439,7 +452,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
            *const vp = va[7], *const vj = va[8];
     __shared__ double tot[SV_LINE], red[NW][SV_LINE];   // the block's sums, the waves' shares of all blocks'
     __shared__ SegState st;
-    __shared__ int sab;
+    __shared__ int sab, nslot;
     const int tid = threadIdx.x, rl = tid / LPR, lane = tid % LPR, row = row0 + rl, wv = uni(tid >> 6), wl = tid & 63;
     const int n = uni(S.n), Wl = uni(S.Wl), blk = row0 / RB, nblk = (n + RB - 1) / RB;
     const bool live = row < n;
@@ -488,7 +501,10 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
     for (int u = 0; u < EPT; u++) bv[u] = (float)gbl(S.binv + (size_t)row * BK)[lane * EPT + u];
     static_assert(sizeof(SegState) % 4 == 0 && sizeof(SegState) / 4 <= T, "a word per thread");
     if (tid < (int)(sizeof(SegState) / 4)) reinterpret_cast<int *>(&st)[tid] = reinterpret_cast<const int *>(sst)[tid];
-    if (tid == 0) sab = ctl.wait < 0 ? 1 : 0;
+    if (tid == 0) {
+        sab = ctl.wait < 0 ? 1 : 0;
+        nslot = 0;
+    }
     if (tid < SV_LINE) tot[tid] = 0.0;
     if (lane == 0) {
         vr[rl] = live ? S.r[row] : 0.0;
@@ -519,7 +535,6 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
         st.nnz_coul = tot[2];
         st.nnz_wide = 0.0;
         st.nnz_halo = tot[2];
-        st.nnz_slots = (double)nblk * RB * LPR * sv_regs<R, LPR, 2>();
         st.mshift = st.mu_prev - st.w;
         st.iters = 0;
         st.qshift = 0.0;
@@ -529,6 +544,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
         st.cg_last = 0;
         st.rho = st.alpha = st.beta = st.m1s = 0.0;
     }
+    sv_slot_count<E, LPR>(nch, cnt, lane, wl, &nslot, tot);
     __syncthreads();
     if (lane == 0 && live) vr[rl] -= st.w;
     const double inv_n = 1.0 / n, inv_sd = 1.0 / st.sdinv;
@@ -634,6 +650,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
             double t[P_CG1];
 #pragma unroll
             for (int k = 0; k < P_CG1; k++) t[k] = sv_lane(mine, k);
+            if (wl == SV_SLOTS) st.nnz_slots = mine;
             if (wl == 0 && st.cg_first == 2) {
                 st.w = t[P_UPD + 0] * inv_sd;
                 st.mshift -= st.w;

@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     __shared__ double va[NV_][RB];
     __shared__ double tot[SV_LINE], red[SVF_NW][SV_LINE];
     __shared__ SegState st;
-    __shared__ int sab;
+    __shared__ int sab, nslot;
     const int tid = threadIdx.x, rl = tid / LPR, lane = tid % LPR, row = row0 + rl, wv = uni(tid >> 6), wl = tid & 63;
     const int n = uni(S.n), Wl = uni(S.Wl), Wb = uni(S.Wb), blk = row0 / RB, nblk = (n + RB - 1) / RB;
     const bool live = row < n;
@@ -149,7 +149,10 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     };
     static_assert(sizeof(SegState) % 4 == 0 && sizeof(SegState) / 4 <= SV_T, "a word per thread");
     if (tid < (int)(sizeof(SegState) / 4)) reinterpret_cast<int *>(&st)[tid] = reinterpret_cast<const int *>(sst)[tid];
-    if (tid == 0) sab = ctl.wait < 0 ? 1 : 0;
+    if (tid == 0) {
+        sab = ctl.wait < 0 ? 1 : 0;
+        nslot = 0;
+    }
     if (tid < SV_LINE) tot[tid] = 0.0;
     if (lane == 0) {
         va[Q_][rl] = live ? S.q[row] : 0.0;
@@ -180,6 +183,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     // first pass over the starting residual: its shift (r m1, m1, entries)
     residual();
     if (lane == 0) va[A_][rl] = (double)cnt;
+    sv_slot_count<E, LPR>(nch, cnt, lane, wl, &nslot, tot);
     __syncthreads();
     bool ok = svf_sum<3, RB>(va, 0x940ull, 0x884ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort, ctl.wait);
     if (!ok) sab = 1;
@@ -189,13 +193,14 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
             const double mine = sv_total<SVF_NW>(tot, red, nblk, wl);
             double t[3];
             for (int k = 0; k < 3; k++) t[k] = sv_lane(mine, k);
+            const double slots = sv_lane(mine, SV_SLOTS);
             if (wl == 0) {
                 st.sdinv = t[1];
                 st.w = t[0] / t[1];
                 st.nnz_coul = t[2];
                 st.nnz_wide = 0.0;
                 st.nnz_halo = t[2];
-                st.nnz_slots = (double)nblk * RB * LPR * E;
+                st.nnz_slots = slots;
                 st.mshift = st.mu_prev - st.w;
                 st.iters = 0;
                 st.qshift = 0.0;

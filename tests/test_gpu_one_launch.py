@@ -113,3 +113,24 @@ def test_blocks_of_256_rows(ct, orc, theta, name, prec):
     assert abs(E - Eo) / s.n <= t["E"]
     assert np.linalg.norm(F - Fo) / np.linalg.norm(Fo) <= t["F"]
     assert np.abs(q - qo).max() <= t["q"]
+
+
+# Lanes per row and entries that a lane keeps in registers
+SLOT_CASES = [("small", 4, 0.0, 8, 24), ("small, coupling", 4, 1.0, 8, 24), ("middling", 13, 0.0, 4, 48),
+              ("middling, coupling", 13, 1.0, 4, 48), ("blocks of 256 rows", 17, 0.0, 4, 32)]
+
+
+@pytest.mark.parametrize("name,cells,kappa,lanes,regs", SLOT_CASES, ids=[c[0] for c in SLOT_CASES])
+def test_slots_of_the_product(ct, theta, name, cells, kappa, lanes, regs):
+    """The slots that a product reads, in a perfect crystal, where every row
+    has the same length: groups of eight entries per lane up to what the
+    registers hold, then single entries; the last wave's rows past the last
+    atom are read with it."""
+    s = G.zincblende(cells, sigma=0.0)
+    print(f"[one launch] slots, {name} n={s.n}", flush=True)
+    info = ct.Potential(theta, fq_kappa=kappa).compute(s.pos, s.types, s.box, s.pbc, warm=False)[3]
+    row = info["nnz_coul"] // s.n
+    assert row * s.n == info["nnz_coul"] and row > 100
+    in_regs = min((row + 8 * lanes - 1) // (8 * lanes) * 8, regs) * lanes
+    rows = (s.n + 64 // lanes - 1) // (64 // lanes) * (64 // lanes)
+    assert info["nnz_coul_slots"] == rows * in_regs + s.n * max(0, row - regs * lanes)
