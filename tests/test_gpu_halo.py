@@ -143,3 +143,21 @@ def test_forms_of_a_large_system(ct, theta, orc, name):
     assert abs(E - Eo) / s.n <= t["E"]
     assert np.linalg.norm(F.cpu().numpy() - Fo) / np.linalg.norm(Fo) <= t["F"]
     assert np.abs(q.cpu().numpy() - qo).max() <= t["q"]
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+def test_halo_positions_of_a_small_system(ct, theta, systems, oracle_results, prec):
+    """The "periodic 1000" system by the multi-launch solve (its own takes one launch,
+    which has no slices): halo positions for every entry."""
+    s = systems["periodic 1000"]
+    print(f"[halo] multi-launch, periodic 1000 {prec}", flush=True)
+    pot = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=1e-9 if prec == "mixed" else 1e-13)
+    pot.debug_solve(ct.SOLVE_MULTI)
+    E, F, q, info = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)
+    Eo, Fo, qo, _ = oracle_results["periodic 1000"]
+    t = TOL[prec]
+    assert info["status"] == 0 and info["nnz_coul_halo"] == info["nnz_coul"] <= info["nnz_coul_slots"]
+    assert info["nnz_coul_slots"] % 64 == 0
+    assert abs(E - Eo) / s.n <= t["E"]
+    assert np.linalg.norm(F.cpu().numpy() - Fo) / np.linalg.norm(Fo) <= t["F"]
+    assert np.abs(q.cpu().numpy() - qo).max() <= t["q"]

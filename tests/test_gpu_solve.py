@@ -120,3 +120,40 @@ def test_iteration_batching_does_not_change_results(ct, theta, prec):
     for E, F, q, it in out[1:]:
         assert it == out[0][3]
         assert E == out[0][0] and np.array_equal(F, out[0][1]) and np.array_equal(q, out[0][2])
+
+
+MANY = {"split": (lambda: CASES["stepped slab"], 0.0), "coupling": (lambda: CASES["stepped slab"], 0.5),
+        "3C-SiC 74088": (lambda: G.zincblende(21, sigma=0.05, seed=188), 0.0)}
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("name", list(MANY))
+def test_iteration_batching_of_the_multi_launch_solve(ct, theta, name, prec):
+    """The same where the host does launch iterations in batches: on request
+    for a small system (two launches per iteration, and the coupling's nine), by
+    size above 65,536 atoms (four)."""
+    s, kappa = MANY[name][0](), MANY[name][1]
+    out = []
+    for check in (1, 4, 64):
+        print(f"[solve] batches of {check}, {name} ({prec})", flush=True)
+        pot = ct.Potential(theta, fp64=(prec == "fp64"), cg_check=check, fq_kappa=kappa)
+        pot.debug_solve(ct.SOLVE_MULTI)
+        E, F, q, info = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)
+        assert info["status"] == 0
+        out.append((E, F.cpu().numpy(), q.cpu().numpy(), info["cg_iters"]))
+    for E, F, q, it in out[1:]:
+        assert it == out[0][3] > 1
+        assert E == out[0][0] and np.array_equal(F, out[0][1]) and np.array_equal(q, out[0][2])
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_residual_of_the_multi_launch_solve(ct, orc, theta, name):
+    """The multi-launch solve's reported residual is the true one, too."""
+    s = CASES[name]
+    print(f"[solve] multi-launch, {name} n={s.n}", flush=True)
+    pot = ct.Potential(theta, fp64=True, cg_tol=TOL)
+    pot.debug_solve(ct.SOLVE_MULTI)
+    _, _, q, info = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)
+    res = _true_residual(orc, theta, s, q.cpu().numpy())
+    assert info["status"] == 0 and info["cg_residual"] < TOL and res < TOL
+    assert abs(res - info["cg_residual"]) < 0.05 * TOL
