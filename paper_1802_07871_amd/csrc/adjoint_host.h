@@ -190,7 +190,7 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
         int done_it = 0;
         for (;;) {
             for (int c = 0; c < ctx->opts.cg_check; c++)
-                launch_cg1<R>(nullptr, P.L.ntile <= SPLIT_TILES, P.dtiles, P.L.ntile, sid, 1, dadj, ctl, st);
+                launch_cg1<R>(nullptr, split_iteration(ctx, P.L.seg.n), P.dtiles, P.L.ntile, sid, 1, dadj, ctl, st);
             done_it += ctx->opts.cg_check;
             HIPCHK(hipGetLastError());
             HIPCHK(hipMemcpyAsync(ctx->host_flag, &asst->done, 2 * sizeof(int), hipMemcpyDeviceToHost, st));

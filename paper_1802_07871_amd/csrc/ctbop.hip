@@ -660,10 +660,31 @@ void launch_solve_fq(int lpr, const Tile *tiles, int nt, Seg *segs, SolveCtl ctl
     }
 }
 
-// One iteration of the multi-launch solve over nt tiles of nid systems: in
-// two launches where every system has at most SPLIT_TILES tiles (the rule is
-// on n alone, as a system's sums depend on it), in four otherwise.  ctx (the
-// profile's events, of the caller's thread alone) may be null.
+// Whether an iteration of the multi-launch solve of n atoms takes two launches
+// (k_spmv_split, k_cg1_step) rather than four.  The rule is on n and the context
+// (a system's sums depend on it).  Up to 128 tiles, two of the split product's
+// blocks per CU, it always does (30,000 atoms with 253, 1,091 and 2,441 entries
+// per row, an evaluation 1.9, 8.0 and 35 ms, in four launches 3.4, 16 and 43).
+// Above, while the matrix stays in the 256 MB cache behind the L2s between
+// iterations: where the rows' neighbours are too many to stage, eight waves per
+// slice gather with less reuse than one (65,000 atoms, random cells: 253
+// entries per row 3.6 and 3.8 ms, 425 6.3 and 6.2, 660 14.8 and 10.1; 48,000
+// atoms: 660 8.6 and 9.7, 858 13.8 and 13.1; FP64, 65,000: 253 3.8 and 4.2, 425
+// 7.6 and 7.0).  Row lengths are not known before the lists are, so the list
+// stride stands for them, less the skin's shell.
+bool split_iteration(const ctbop_ctx *ctx, int n)
+{
+    const int nt = (n + TILE - 1) / TILE;
+    if (nt > SPLIT_TILES) return false;
+    if (nt <= 128) return true;
+    const double in = ctx->theta[54] / (ctx->theta[54] + ctx->opts.skin);
+    const double entries = (double)nt * TILE * ctx->opts.long_cap * in * in * in;
+    return ctx->opts.fp64 ? entries * 10 <= 256.0 * (1 << 20) : entries * 6 <= 176.0 * (1 << 20);
+}
+
+// One iteration of the multi-launch solve over nt tiles of nid systems, in two
+// launches (split) or in four.  ctx (the profile's events, of the caller's
+// thread alone) may be null.
 template <typename R>
 void launch_cg1(ctbop_ctx *ctx, bool split, const Tile *tiles, int nt, const int *ids, int nid, Seg *segs, CgCtl ctl,
                 hipStream_t st)
@@ -915,6 +936,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         }
         HIPCHK(hipGetLastError());
         // charge solve: launch iterations in batches, then read the convergence flag
+        const bool split = split_iteration(ctx, P.L.seg.n);
         int done_it = 0;
         int chunk = ctx->opts.cg_check;
         // (the single-reduction solve's first finalize counts no iteration: n
@@ -923,7 +945,7 @@ int launch_eval(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, int flags, int *i
         for (;;) {
             for (int c = 0; c < chunk; c++) {
                 if (!fq) {
-                    launch_cg1<R>(ctx, nt <= SPLIT_TILES, P.dtiles, nt, sid, 1, P.dseg, ctl, st);
+                    launch_cg1<R>(ctx, split, P.dtiles, nt, sid, 1, P.dseg, ctl, st);
                     continue;
                 }
                 {

@@ -822,8 +822,9 @@ __global__ void __launch_bounds__(TILE) k_spmv(const Tile *tiles, Seg *segs)
 
 // ---------------------------------------------------------------------------
 // Systems of up to SPLIT_TILES tiles that no one-launch solve takes (or whose
-// own gave up): the product with eight waves per row slice, and the finalize
-// in the update (two launches per iteration instead of four).  There a lane per row leaves most of the card idle and an
+// own gave up), where the host finds that it pays (split_iteration): the product
+// with eight waves per row slice, and the finalize in the update (two launches
+// per iteration instead of four).  There a lane per row leaves most of the card idle and an
 // iteration is a chain of launches that each wait for memory once or twice:
 // with 36,864 atoms 50 us (product 29.5, its sums 8.8, update 4.5, gaps) and
 // 31 this way (18, 7.3, gaps), ten MD steps 19.4 and 12.8 ms (8.2 in one launch).

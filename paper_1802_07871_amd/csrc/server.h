@@ -463,11 +463,11 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
             his[nis++] = k;
             if (CLS[c] == 0) nis_many++;
         }
-    int nta_coarse = 0, nia_coarse = 0;
-    for (int c = 0; c < 3; c++)        // multi-launch above and up to FINE_MAX, one-launch
+    int nta_coarse = 0, nia_coarse = 0, nta_whole = 0, nia_whole = 0;
+    for (int c = 0; c < 4; c++)        // multi-launch above and up to FINE_MAX, in two launches, one-launch
         for (int k : act) {
             SrvSlot &sl = S->slots[k];
-            const int mine = cls_of(sl) != 0 ? 2 : sl.L.seg.n > FINE_MAX ? 0 : 1;
+            const int n = sl.L.seg.n, mine = cls_of(sl) != 0 ? 3 : n > FINE_MAX ? 0 : split_iteration(ctx, n) ? 2 : 1;
             if (mine != c) continue;
             for (int t = 0; t < sl.L.ntile; t++) hta[nta++] = Tile{k, t * TILE};
             hia[nia++] = k;
@@ -476,6 +476,10 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
                 nia_coarse = nia;
             }
             if (c <= 1) {
+                nta_whole = nta;
+                nia_whole = nia;
+            }
+            if (c <= 2) {
                 nta_many = nta;
                 nia_many = nia;
             }
@@ -559,10 +563,10 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
             const int first = std::max(ctx->opts.cg_check, std::min(S->iters_hint, ctx->opts.cg_maxit) + 1);
             const int chunk = poll ? std::min(limit - c, c == 0 ? first : ctx->opts.cg_check) : cg_iters;
             for (int k = 0; k < chunk; k++) {
-                if (nia_coarse) launch_cg1<R>(nullptr, false, T, nta_coarse, sid, nia_coarse, S->dsegs, ctl, st);
-                if (nia_many > nia_coarse)
-                    launch_cg1<R>(nullptr, true, T + nta_coarse, nta_many - nta_coarse, sid + nia_coarse,
-                                  nia_many - nia_coarse, S->dsegs, ctl, st);
+                if (nia_whole) launch_cg1<R>(nullptr, false, T, nta_whole, sid, nia_whole, S->dsegs, ctl, st);
+                if (nia_many > nia_whole)
+                    launch_cg1<R>(nullptr, true, T + nta_whole, nta_many - nta_whole, sid + nia_whole,
+                                  nia_many - nia_whole, S->dsegs, ctl, st);
             }
             c += chunk;
             if (!poll || c >= limit) break;

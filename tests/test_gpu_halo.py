@@ -161,3 +161,20 @@ def test_halo_positions_of_a_small_system(ct, theta, systems, oracle_results, pr
     assert abs(E - Eo) / s.n <= t["E"]
     assert np.linalg.norm(F.cpu().numpy() - Fo) / np.linalg.norm(Fo) <= t["F"]
     assert np.abs(q.cpu().numpy() - qo).max() <= t["q"]
+
+
+@pytest.mark.parametrize("prec,cap", [("mixed", 752), ("mixed", 768), ("fp64", 656), ("fp64", 672)])
+def test_sides_of_the_split_product(ct, theta, systems, oracle_results, prec, cap):
+    """50,240 atoms with list strides on both sides of the rule that gives the
+    product eight waves per row slice.
+    """
+    s = systems["stepped slab"]
+    print(f"[halo] stride {cap} {prec}", flush=True)
+    pot = ct.Potential(theta, fp64=(prec == "fp64"), cg_tol=1e-9 if prec == "mixed" else 1e-13, long_cap=cap)
+    E, F, q, info = pot.compute(s.pos, s.types, s.box, s.pbc, warm=False)
+    Eo, Fo, qo, _ = oracle_results["stepped slab"]
+    t = TOL[prec]
+    assert info["status"] == 0
+    assert abs(E - Eo) / s.n <= t["E"]
+    assert np.linalg.norm(F.cpu().numpy() - Fo) / np.linalg.norm(Fo) <= t["F"]
+    assert np.abs(q.cpu().numpy() - qo).max() <= t["q"]

@@ -297,3 +297,23 @@ def test_small_requests_do_not_wait_for_a_large_one(ct, theta):
         assert got[k]["status"] == 0 and got[k]["E"] == E
         assert np.array_equal(got[k]["F"], F.cpu().numpy()) and np.array_equal(got[k]["q"], q.cpu().numpy())
     assert all(got[k]["t_done"] < got[t[0]]["t_done"] for k in t[1:])
+
+
+def test_every_form_of_the_solve_in_one_batch(ct, theta):
+    """One launch, two and four launches per iteration (a stride of 640 takes
+    60,000 atoms past the size for two), and systems above 65,536 atoms: each
+    request gets the bits of the plain call."""
+    from paper_1802_07871_amd.serving import Server
+    pot = ct.Potential(theta, long_cap=640)
+    structs = [G.slab_4h(50, 42, 6, seed=101), G.zincblende(21, sigma=0.05, seed=102), G.slab_4h(50, 50, 6, seed=103),
+               G.zincblende(5, sigma=0.05, seed=104), G.slab_4h(34, 42, 6, seed=105)]
+    assert [s.n for s in structs] == [50400, 74088, 60000, 1000, 34272]
+    print("[serving] every form of the solve", flush=True)
+    ref = [pot.compute(s.pos, s.types, s.box, s.pbc, warm=False) for s in structs]
+    srv = Server(pot, 8 << 30, max_slots=8)
+    tickets = [srv.submit(s.pos, s.types, s.box, s.pbc) for s in structs]
+    got = srv.wait_all(tickets)
+    srv.close()
+    for t, (E, F, q, _) in zip(tickets, ref):
+        assert got[t]["status"] == 0 and got[t]["E"] == E
+        assert np.array_equal(got[t]["F"], F.cpu().numpy()) and np.array_equal(got[t]["q"], q.cpu().numpy())
