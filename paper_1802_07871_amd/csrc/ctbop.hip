@@ -611,8 +611,8 @@ int eval_kind(ctbop_ctx *ctx, const Seg &S)
 SolveCtl solve_ctl(const ctbop_ctx *ctx, int relative)
 {
     const int way = ctx->way;
-    return {ctx->opts.cg_tol, way == CTBOP_SOLVE_LATE ? 1 : ctx->opts.cg_maxit, relative, way == CTBOP_SOLVE_LATE,
-            way == CTBOP_SOLVE_NO_WAIT ? -1 : SV_WAIT};
+    return {ctx->opts.cg_tol, way == CTBOP_SOLVE_LATE ? 1 : ctx->opts.cg_maxit, relative,
+            way == CTBOP_SOLVE_NO_WAIT ? 1 : way == CTBOP_SOLVE_LATE ? 2 : 0};
 }
 
 // The one-launch solve over nt tiles of systems of one kind, and the kernel

@@ -76,7 +76,7 @@ __device__ __forceinline__ unsigned long long sv_get(const __attribute__((addres
 // Load a slot until its value is there; false when the wait ran out or
 // another block of the system gave up.
 __device__ __forceinline__ bool sv_wait(const __attribute__((address_space(1))) unsigned long long *p,
-                                        unsigned long long &v, const int *pabort, long long bound)
+                                        unsigned long long &v, const int *pabort)
 {
     if (v != SV_EMPTY) return true;
     const long long t0 = wall_clock64();
@@ -86,7 +86,7 @@ __device__ __forceinline__ bool sv_wait(const __attribute__((address_space(1))) 
         __builtin_amdgcn_s_sleep(1);
         if ((k & 63) == 63) {
             if (__hip_atomic_load(pabort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
-            if (wall_clock64() - t0 > bound) return false;
+            if (wall_clock64() - t0 > SV_WAIT) return false;
         }
     }
 }
@@ -170,8 +170,7 @@ sv_line(__attribute__((address_space(1))) unsigned long long *slots, int buf, in
 // .. 4 w + 3 of every 4 NW); false when a wait ran out.
 template <int NW>
 __device__ __forceinline__ bool sv_collect(__attribute__((address_space(1))) unsigned long long *slots, int buf, int nblk,
-                                           int blk, double (*red)[SV_LINE], int wv, int wl, const int *pabort,
-                                           long long bound)
+                                           int blk, double (*red)[SV_LINE], int wv, int wl, const int *pabort)
 {
     constexpr int PB = SV_MAX_BLOCKS / (4 * NW);
     const auto line = slots + (unsigned)((buf * SV_REP + (blk & (SV_REP - 1))) * nblk * SV_LINE + (wl & 15));
@@ -186,7 +185,7 @@ __device__ __forceinline__ bool sv_collect(__attribute__((address_space(1))) uns
     for (int i = 0; i < PB; i++)
         if ((i * NW + wv) * 4 < nblk) {
             const int b = (i * NW + wv) * 4 + (wl >> 4);
-            ok = ok && sv_wait(line + (unsigned)(min(b, nblk - 1) * SV_LINE), x[i], pabort, bound);
+            ok = ok && sv_wait(line + (unsigned)(min(b, nblk - 1) * SV_LINE), x[i], pabort);
             t += b < nblk ? __longlong_as_double((long long)x[i]) : 0.0;
         }
     t += __shfl_xor(t, 16, 64);
@@ -410,15 +409,14 @@ __global__ void __launch_bounds__(T) k_solve_prep(const Tile *tiles, Seg *segs, 
 }
 
 // Tolerance of a solve; relative: times the starting residual (the adjoint,
-// whose source has the caller's scale).  wait: the bound of a wait in ticks
-// (< 0: the solve gives up in its first iteration).  late: its last block
-// gives up at the end, when the others have finished.
+// whose source has the caller's scale).  way, on request alone: the solve gives
+// up in its first iteration (1), or its last block does at the end, when the
+// others have finished (2).
 struct SolveCtl {
     double tol;
     int maxit;
     int relative;
-    int late;
-    long long wait;
+    int way;
 };
 
 // The whole projected PCG of one system (the single-reduction form of
@@ -502,7 +500,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
     static_assert(sizeof(SegState) % 4 == 0 && sizeof(SegState) / 4 <= T, "a word per thread");
     if (tid < (int)(sizeof(SegState) / 4)) reinterpret_cast<int *>(&st)[tid] = reinterpret_cast<const int *>(sst)[tid];
     if (tid == 0) {
-        sab = ctl.wait < 0 ? 1 : 0;
+        sab = ctl.way & 1;
         nslot = 0;
     }
     if (tid < SV_LINE) tot[tid] = 0.0;
@@ -591,7 +589,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
                 }
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    ok = ok && sv_wait(ys + (unsigned)hl[k[u]], v[u], pabort, ctl.wait);
+                    ok = ok && sv_wait(ys + (unsigned)hl[k[u]], v[u], pabort);
                     hp[k[u]] = __longlong_as_double((long long)v[u]);
                 }
             }
@@ -640,7 +638,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
         if (nblk > 1) {
             __syncthreads();
             if (wv == 0) sv_put(sv_line(slots_p, it % 3, nblk, blk, wl), tot[wl & 15]);
-            if (!sv_collect<NW>(slots_p, it % 3, nblk, blk, red, wv, wl, pabort, ctl.wait)) sab = 1;
+            if (!sv_collect<NW>(slots_p, it % 3, nblk, blk, red, wv, wl, pabort)) sab = 1;
         }
         __syncthreads();
         if (sab) break;
@@ -677,7 +675,7 @@ __global__ void __launch_bounds__(T, OCC) k_solve(const Tile *tiles, Seg *segs, 
             vr[rl] = (vr[rl] - alpha * s) - c;
         }
     }
-    if (sab || (ctl.late && blk == nblk - 1)) {
+    if (sab || ((ctl.way & 2) && blk == nblk - 1)) {
         if (tid == 0) __hip_atomic_store(pabort, PA_WAIT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }

@@ -37,7 +37,7 @@ template <int K, int RB>
 __device__ __forceinline__ bool svf_sum(const double (*va)[RB], unsigned long long fa, unsigned long long fb, int wv,
                                         int wl, int nblk, int blk, int ex,
                                         __attribute__((address_space(1))) unsigned long long *slots_p, double *tot,
-                                        double (*red)[SV_LINE], const int *pabort, long long bound)
+                                        double (*red)[SV_LINE], const int *pabort)
 {
     static_assert(K <= SVF_NW, "a sum per wave");
     if (wv < K) {
@@ -51,7 +51,7 @@ __device__ __forceinline__ bool svf_sum(const double (*va)[RB], unsigned long lo
     if (nblk == 1) return true;
     __syncthreads();
     if (wv == 0) sv_put(sv_line(slots_p, ex % 3, nblk, blk, wl), tot[wl & 15]);
-    return sv_collect<SVF_NW>(slots_p, ex % 3, nblk, blk, red, wv, wl, pabort, bound);
+    return sv_collect<SVF_NW>(slots_p, ex % 3, nblk, blk, red, wv, wl, pabort);
 }
 
 // empty this block's sums of the round before (every block has read them)
@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     static_assert(sizeof(SegState) % 4 == 0 && sizeof(SegState) / 4 <= SV_T, "a word per thread");
     if (tid < (int)(sizeof(SegState) / 4)) reinterpret_cast<int *>(&st)[tid] = reinterpret_cast<const int *>(sst)[tid];
     if (tid == 0) {
-        sab = ctl.wait < 0 ? 1 : 0;
+        sab = ctl.way & 1;
         nslot = 0;
     }
     if (tid < SV_LINE) tot[tid] = 0.0;
@@ -185,7 +185,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
     if (lane == 0) va[A_][rl] = (double)cnt;
     sv_slot_count<E, LPR>(nch, cnt, lane, wl, &nslot, tot);
     __syncthreads();
-    bool ok = svf_sum<3, RB>(va, 0x940ull, 0x884ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort, ctl.wait);
+    bool ok = svf_sum<3, RB>(va, 0x940ull, 0x884ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
     if (!ok) sab = 1;
     __syncthreads();
     if (!sab) {
@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         precond();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        ok = svf_sum<4, RB>(va, 0x0000ull, 0x0814ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort, ctl.wait);
+        ok = svf_sum<4, RB>(va, 0x0000ull, 0x0814ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
         if (!ok) sab = 1;
         __syncthreads();
     }
@@ -274,7 +274,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
             }
 #pragma unroll
             for (int u = 0; u < 4; u++) {
-                ok = ok && sv_wait(ps + (unsigned)hl[k[u]], v[u], pabort, ctl.wait);
+                ok = ok && sv_wait(ps + (unsigned)hl[k[u]], v[u], pabort);
                 hp[k[u]] = __longlong_as_double((long long)v[u]);
             }
         }
@@ -318,7 +318,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         // p H p, p r, A, B
-        ok = svf_sum<4, RB>(va, 0xa966ull, 0x8802ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort, ctl.wait);
+        ok = svf_sum<4, RB>(va, 0xa966ull, 0x8802ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
         if (!ok) sab = 1;
         __syncthreads();
         if (sab) break;
@@ -349,7 +349,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         line(st.alpha);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        ok = svf_sum<2, RB>(va, 0xa9ull, 0x88ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort, ctl.wait);
+        ok = svf_sum<2, RB>(va, 0xa9ull, 0x88ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
         if (!ok) sab = 1;
         __syncthreads();
         if (sab) break;
@@ -387,7 +387,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         // r m1, r y, r, r r, q, y r_old, m1 r_old
-        ok = svf_sum<7, RB>(va, 0x4130000ull, 0x5580814ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort, ctl.wait);
+        ok = svf_sum<7, RB>(va, 0x4130000ull, 0x5580814ull, wv, wl, nblk, blk, ex, slots_p, tot, red, pabort);
         if (!ok) sab = 1;
         __syncthreads();
         if (sab) break;
@@ -420,7 +420,7 @@ __global__ void __launch_bounds__(SV_T, 2) k_solve_fq(const Tile *tiles, Seg *se
         ex++;
         __syncthreads();
     }
-    if (sab || (ctl.late && blk == nblk - 1)) {
+    if (sab || ((ctl.way & 2) && blk == nblk - 1)) {
         if (tid == 0) __hip_atomic_store(pabort, PA_WAIT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
