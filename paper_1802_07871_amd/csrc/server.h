@@ -168,8 +168,7 @@ struct ctbop_server {
     // Coulomb forces (as the single-system path does)
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    hipEvent_t ev_solve = nullptr;    // after a tick's one-launch solves
-    int turn_dev = -1;
+    int turn_dev = -1;                // device of join_turn
     // device tables at the head of the arena
     Seg *dsegs = nullptr;
     Tile *dtiles_setup = nullptr, *dtiles_act = nullptr;
@@ -539,7 +538,7 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
                 launch_solve<R>(CLS[c], ctx->ncu, T + t0, cls_tiles[c], S->dsegs, solve_ctl(ctx, 0), st);
             }
         if (nto) {
-            const int lrc = pass.launched(S->ev_solve);
+            const int lrc = pass.launched(S->ev_fork);   // (its own wait is on the side stream already)
             if (lrc) return lrc;
         }
         if (nis_many) {
@@ -705,7 +704,6 @@ void release_handles(ctbop_server *S)
     }
     if (S->ev_fork) (void)hipEventDestroy(S->ev_fork);
     if (S->ev_join) (void)hipEventDestroy(S->ev_join);
-    if (S->ev_solve) (void)hipEventDestroy(S->ev_solve);
     leave_turn(S->turn_dev);
     if (S->htiles) (void)hipHostFree(S->htiles);
     if (S->hids) (void)hipHostFree(S->hids);
@@ -811,7 +809,6 @@ int create_server(ctbop_ctx *ctx, void *arena, size_t arena_bytes, int max_slots
         hipStreamCreateWithFlags(&S->side, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&S->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&S->ev_join, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&S->ev_solve, hipEventDisableTiming) != hipSuccess ||
         join_turn(S->turn_dev) != CTBOP_OK ||
         hipHostMalloc((void **)&S->htiles, sizeof(Tile) * 2 * S->max_tiles, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&S->hids, sizeof(int) * 2 * max_slots, hipHostMallocDefault) != hipSuccess ||
