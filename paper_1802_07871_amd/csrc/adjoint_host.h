@@ -226,18 +226,27 @@ int launch_param_grad(ctbop_ctx *ctx, Prep &P, const Params<R> &prm, char *adj, 
         const int m = (int)std::min<size_t>(AL.chunk, cov.size() - c0);
         HIPCHK(hipMemcpyAsync(dpk, &hpk[c0], sizeof(Params<Dual>) * m, hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(dk, &hk[c0], sizeof(int) * m, hipMemcpyHostToDevice, st));
-        const int nb = P.L.ntile * (TILE / DUAL_ROWS);
-        hipLaunchKernelGGL(k_bond_dual, dim3(nb, m), b, 0, st, P.dtiles, P.dseg, A);
-        hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, nb);
-        hipLaunchKernelGGL(k_force_cov_dual, dim3(nb, m, 2), b, 0, st, P.dtiles, P.dseg, A);
-        hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, 2 * nb);
+        const int nb = P.L.ntile * DUAL_L;
+        if (P.L.ntile * m < DUAL_FILL) {
+            hipLaunchKernelGGL(k_bond_dual<DUAL_L>, dim3(nb, m), b, 0, st, P.dtiles, P.dseg, A);
+            hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, nb);
+            hipLaunchKernelGGL(k_force_cov_dual<DUAL_L>, dim3(nb, m, 2), b, 0, st, P.dtiles, P.dseg, A);
+            hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, 2 * nb);
+        } else {
+            hipLaunchKernelGGL(k_bond_dual<1>, dim3(P.L.ntile, m), b, 0, st, P.dtiles, P.dseg, A);
+            hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, P.L.ntile);
+            hipLaunchKernelGGL(k_force_cov_dual<1>, dim3(P.L.ntile, m), b, 0, st, P.dtiles, P.dseg, A);
+            hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, P.L.ntile);
+        }
     }
     {
         const int m = (int)coul.size();
         HIPCHK(hipMemcpyAsync(dpk, &hpk[cov.size()], sizeof(Params<Dual>) * m, hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(dk, &hk[cov.size()], sizeof(int) * m, hipMemcpyHostToDevice, st));
-        const int nb = P.L.ntile * (TILE / FINE);
-        hipLaunchKernelGGL((k_coul_dual<R, LPR>), dim3(nb, m), b, 0, st, P.dtiles, P.dseg, A);
+        const bool fine = P.L.ntile * m < COUL_FILL;
+        const int nb = fine ? P.L.ntile * (TILE / FINE) : P.L.ntile;
+        if (fine) hipLaunchKernelGGL((k_coul_dual<R, LPR, FINE>), dim3(nb, m), b, 0, st, P.dtiles, P.dseg, A);
+        else hipLaunchKernelGGL((k_coul_dual<R, LPR, TILE>), dim3(nb, m), b, 0, st, P.dtiles, P.dseg, A);
         hipLaunchKernelGGL(k_fin_grad_members, dim3(m), b, 0, st, A, nb);
     }
     HIPCHK(hipGetLastError());

@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(TILE) k_adj_seed(const Tile *tiles, Seg *segs,
 }
 
 // a_s = u_s + sum_j q_j C'(r_sj) (v_s - v_j) . r_hat_sj   (self images: v_s - v_s = 0)
-// (FINE rows per block: the systems of a fit are small; 64 to 1,728 atoms 120 -> 14 us)
+// (FINE rows per block: 64 to 1,728 atoms 120 -> 14 us, 300,000 367 -> 268)
 template <typename R, int LPR>
 __global__ void __launch_bounds__(TILE) k_adj_source(const Tile *tiles, Seg *segs, Params<double> PD, AdjWs A)
 {
@@ -154,10 +154,14 @@ __global__ void k_adj_keep_lam_shift(const int *seg_ids, Seg *segs, AdjWs A)
 // dual passes (a chunk of parameters per launch, one per blockIdx.y)
 // ---------------------------------------------------------------------------
 
-// The covalent passes give a lane a bond: DUAL_L lanes per atom take its
-// bonds in turn (an atom per lane walked its bond pairs in dual FP64 numbers
-// one after another, in a handful of blocks for the systems of a fit).
-constexpr int DUAL_L = 4, DUAL_ROWS = TILE / DUAL_L;
+// The covalent passes give an atom L lanes that take its bonds in turn: DUAL_L
+// where the launch would leave the chip idle otherwise (an atom per lane walks
+// its bond pairs in dual FP64 numbers one after another, in a handful of blocks
+// for the systems of a fit), one where a block per tile and member makes
+// DUAL_FILL blocks (a gradient of 2,880 atoms 0.64 ms with four lanes and 0.67
+// with one, 19,488 and 48,000 the same, 64,512 5.28 and 5.05, 300,000 20.9 and
+// 19.4, 960,000 65.2 and 56.2).
+constexpr int DUAL_L = 4, DUAL_FILL = 1024;
 
 __device__ __forceinline__ R3<double> bond_vec64(const Seg &S, const double4 &a, const double4 &b, uint32_t ent)
 {
@@ -165,17 +169,35 @@ __device__ __forceinline__ R3<double> bond_vec64(const Seg &S, const double4 &a,
     return {(b.x - a.x) + D.x, (b.y - a.y) + D.y, (b.z - a.z) + D.z};
 }
 
+// geometry of a bond: the block's table of offsets with a lane per atom
+template <int L> struct DualGeom {
+    double4 dtab[L == 1 ? NCODE : 1];
+    __device__ __forceinline__ void load(const Seg &S)
+    {
+        if constexpr (L == 1) load_dtab2<double>(S, dtab);
+    }
+    __device__ __forceinline__ R3<double> vec(const Seg &S, const double4 &a, const double4 &b, uint32_t ent) const
+    {
+        if constexpr (L == 1) return pair_vec<double>(a, b, dtab[ent >> CODE_SHIFT]);
+        else return bond_vec64(S, a, b, ent);
+    }
+};
+
 // Covalent bond pass in dual numbers: per-bond b, P1, P2 and the block's
 // w dEcov/dtheta, for the chunk member blockIdx.y (64 to 1,728 atoms, 44
 // members: 111 -> 52 us).
+template <int L>
 __global__ void __launch_bounds__(TILE) k_bond_dual(const Tile *tiles, Seg *segs, AdjWs A)
 {
-    const Tile T = my_rows<DUAL_ROWS>(tiles);
+    constexpr int ROWS = TILE / L;
+    const Tile T = my_rows<ROWS>(tiles);
     const Seg &S = segs[T.seg];
+    __shared__ DualGeom<L> geo;
     __shared__ double lds[4];
     __shared__ __align__(16) unsigned char pbuf[sizeof(Params<Dual>)];
     const Params<Dual> &P = load_member_params(A, pbuf);
-    const int s = T.row0 + threadIdx.x / DUAL_L;
+    geo.load(S);
+    const int s = T.row0 + threadIdx.x / L;
     double ew = 0.0;
     if (s < S.n) {
         const double4 *xs = S.xs64;
@@ -184,11 +206,11 @@ __global__ void __launch_bounds__(TILE) k_bond_dual(const Tile *tiles, Seg *segs
         const double4 li = xs[s];
         const int ti = (int)li.w;
         const int ns = S.bcnt[s];
-        for (int e = threadIdx.x % DUAL_L; e < ns; e += DUAL_L) {
+        for (int e = threadIdx.x % L; e < ns; e += L) {
             const uint32_t ent = row[e];
             const double4 lj = xs[ent & J_MASK];
             const int pp = ti * 2 + (int)lj.w;
-            const R3<double> d = bond_vec64(S, li, lj, ent);
+            const R3<double> d = geo.vec(S, li, lj, ent);
             const double r2 = d.x * d.x + d.y * d.y + d.z * d.z;
             Dual b(0.0), P1(0.0), P2(0.0);
             if (r2 < P.Sc[pp].v * P.Sc[pp].v) {
@@ -199,7 +221,7 @@ __global__ void __launch_bounds__(TILE) k_bond_dual(const Tile *tiles, Seg *segs
                     const uint32_t ent2 = row[e2];
                     const double4 lk = xs[ent2 & J_MASK];
                     const int pk = ti * 2 + (int)lk.w;
-                    const R3<double> dk = bond_vec64(S, li, lk, ent2);
+                    const R3<double> dk = geo.vec(S, li, lk, ent2);
                     const double rk2 = dk.x * dk.x + dk.y * dk.y + dk.z * dk.z;
                     if (rk2 >= P.Sc[pk].v * P.Sc[pk].v) continue;
                     const double rk = ::sqrt(rk2);
@@ -232,7 +254,7 @@ __global__ void __launch_bounds__(TILE) k_bond_dual(const Tile *tiles, Seg *segs
         }
         ew *= A.w;
     }
-    member_partial(A, T.row0 / DUAL_ROWS, ew, lds);
+    member_partial(A, T.row0 / ROWS, ew, lds);
 }
 
 __device__ __forceinline__ Dual slotd_get(const double *p) { return Dual(p[0], p[1]); }
@@ -241,15 +263,19 @@ __device__ __forceinline__ Dual slotd_get(const double *p) { return Dual(p[0], p
 // over its atoms' bonds: with the atom as their centre (blockIdx.z = 0), or
 // as the partner and environment of its neighbours' bonds (1).  64 to 1,728
 // atoms, 44 members: 249 -> 94 us.
+template <int L>
 __global__ void __launch_bounds__(TILE) k_force_cov_dual(const Tile *tiles, Seg *segs, AdjWs A)
 {
-    const Tile T = my_rows<DUAL_ROWS>(tiles);
+    constexpr int ROWS = TILE / L;
+    const Tile T = my_rows<ROWS>(tiles);
     const Seg &S = segs[T.seg];
+    __shared__ DualGeom<L> geo;
     __shared__ double lds[4];
     __shared__ __align__(16) unsigned char pbuf[sizeof(Params<Dual>)];
     const Params<Dual> &P = load_member_params(A, pbuf);
+    geo.load(S);
     const double *slotd = A.slotd + blockIdx.y * A.slot_stride;
-    const int m = T.row0 + threadIdx.x / DUAL_L;
+    const int m = T.row0 + threadIdx.x / L;
     double vf = 0.0;
     if (m < S.n) {
         const double4 *xs = S.xs64;
@@ -258,12 +284,12 @@ __global__ void __launch_bounds__(TILE) k_force_cov_dual(const Tile *tiles, Seg 
         const int ns = S.bcnt[m];
         const SRow<const uint32_t> row = srow<const uint32_t>(S.bidx, m, S.Wb);
         double fx = 0.0, fy = 0.0, fz = 0.0;
-        if (blockIdx.z == 0)
-            for (int e = threadIdx.x % DUAL_L; e < ns; e += DUAL_L) {
+        if (L == 1 || blockIdx.z == 0)
+            for (int e = threadIdx.x % L; e < ns; e += L) {
                 const uint32_t ent = row[e];
                 const double4 lj = xs[ent & J_MASK];
                 const int pp = tm * 2 + (int)lj.w;
-                const R3<double> d = bond_vec64(S, lm, lj, ent);
+                const R3<double> d = geo.vec(S, lm, lj, ent);
                 const double r2 = d.x * d.x + d.y * d.y + d.z * d.z;
                 if (r2 >= P.Sc[pp].v * P.Sc[pp].v) continue;
                 const double r = ::sqrt(r2), ir = 1.0 / r;
@@ -276,7 +302,7 @@ __global__ void __launch_bounds__(TILE) k_force_cov_dual(const Tile *tiles, Seg 
                     const uint32_t ent2 = row[e2];
                     const double4 lk = xs[ent2 & J_MASK];
                     const int pk = tm * 2 + (int)lk.w;
-                    const R3<double> dk = bond_vec64(S, lm, lk, ent2);
+                    const R3<double> dk = geo.vec(S, lm, lk, ent2);
                     const double rk2 = dk.x * dk.x + dk.y * dk.y + dk.z * dk.z;
                     if (rk2 >= P.Sc[pk].v * P.Sc[pk].v) continue;
                     R3<Dual> gj[2], gk[2];
@@ -290,13 +316,13 @@ __global__ void __launch_bounds__(TILE) k_force_cov_dual(const Tile *tiles, Seg 
                 fy += ay.d;
                 fz += az.d;
             }
-        else
-            for (int e = threadIdx.x % DUAL_L; e < ns; e += DUAL_L) {
+        if (L == 1 || blockIdx.z == 1)
+            for (int e = threadIdx.x % L; e < ns; e += L) {
                 const uint32_t ent = row[e];
                 const int i = (int)(ent & J_MASK);
                 const double4 li = xs[i];
                 const int ti = (int)li.w, pp = ti * 2 + tm;
-                const R3<double> dmi = bond_vec64(S, lm, li, ent);
+                const R3<double> dmi = geo.vec(S, lm, li, ent);
                 const double r2 = dmi.x * dmi.x + dmi.y * dmi.y + dmi.z * dmi.z;
                 if (r2 >= P.Sc[pp].v * P.Sc[pp].v) continue;
                 const double r = ::sqrt(r2), ir = 1.0 / r;
@@ -315,7 +341,7 @@ __global__ void __launch_bounds__(TILE) k_force_cov_dual(const Tile *tiles, Seg 
                     const uint32_t ent2 = rowi[t];
                     const double4 lk = xs[ent2 & J_MASK];
                     const int pk = ti * 2 + (int)lk.w;
-                    const R3<double> dk = bond_vec64(S, li, lk, ent2);
+                    const R3<double> dk = geo.vec(S, li, lk, ent2);
                     const double rk2 = dk.x * dk.x + dk.y * dk.y + dk.z * dk.z;
                     if (rk2 >= P.Sc[pk].v * P.Sc[pk].v) continue;
                     const double rk = ::sqrt(rk2);
@@ -338,7 +364,7 @@ __global__ void __launch_bounds__(TILE) k_force_cov_dual(const Tile *tiles, Seg 
             }
         vf = A.v[m] * fx + A.v[S.npad + m] * fy + A.v[2 * S.npad + m] * fz;
     }
-    member_partial(A, blockIdx.z * gridDim.x + T.row0 / DUAL_ROWS, vf, lds);
+    member_partial(A, blockIdx.z * gridDim.x + T.row0 / ROWS, vf, lds);
 }
 
 // Coulomb kernel in dual numbers (parameters gamma, ke, rc may carry the
@@ -357,12 +383,15 @@ __device__ __forceinline__ Dual coul_dual(const Params<Dual> &P, int pp, double 
 }
 
 // Per row: w/2 q_s q_j dC/dtheta + q_s q_j d(C')/dtheta (v_s . r_hat) - lambda_s q_j dC/dtheta
-// (FINE rows per block; 64 to 1,728 atoms, 4 members: 182 -> 18 us)
-template <typename R, int LPR>
+// (FINE rows per block; 64 to 1,728 atoms, 4 members: 182 -> 18 us.  A tile per
+// block where that makes COUL_FILL blocks: a gradient of 99,600 atoms 7.97 ms and
+// 8.12, 300,000 19.40 and 19.31, 960,000 56.2 and 55.4)
+constexpr int COUL_FILL = 4096;
+template <typename R, int LPR, int ROWS>
 __global__ void __launch_bounds__(TILE) k_coul_dual(const Tile *tiles, Seg *segs, AdjWs A)
 {
     using V4 = typename Vec4<R>::type;
-    const Tile T = my_rows<FINE>(tiles);
+    const Tile T = my_rows<ROWS>(tiles);
     const Seg &S = segs[T.seg];
     __shared__ V4 dtab[NCODE];
     __shared__ double lds[4];
@@ -374,7 +403,7 @@ __global__ void __launch_bounds__(TILE) k_coul_dual(const Tile *tiles, Seg *segs
     constexpr int G = TILE / LPR;
     const int lane = threadIdx.x % LPR;
     double tot = 0.0;
-    for (int k = threadIdx.x / LPR; k < FINE; k += G) {
+    for (int k = threadIdx.x / LPR; k < ROWS; k += G) {
         const int s = T.row0 + k;
         if (s >= S.n) continue;
         const V4 li = xs[s];
@@ -400,7 +429,7 @@ __global__ void __launch_bounds__(TILE) k_coul_dual(const Tile *tiles, Seg *segs
         acc = group_sum<LPR>(acc);
         if (lane == 0) tot += acc;
     }
-    member_partial(A, T.row0 / FINE, tot, lds);
+    member_partial(A, T.row0 / ROWS, tot, lds);
 }
 
 // Closed-form self-energy and diagonal terms, per species t:

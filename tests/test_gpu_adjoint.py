@@ -275,24 +275,27 @@ def test_gradient_by_the_multi_launch_solve(ct, oracle_grads, way, fp64):
     _compare(g4, ref, th, rtol, atol, f"one-launch adjoint after way {way}")
 
 
-# a pair strength, an electronegativity, a Coulomb width and its strength
-LARGE_PARAMS = (0, 21, 49, 53)
-LARGE = {"slab 50400": lambda: G.slab_4h(50, 42, 6, seed=41), "3C-SiC 74088": lambda: G.zincblende(21, sigma=0.05, seed=42)}
+# a pair strength, an electronegativity, a Coulomb width and its strength (one
+# of these for the system whose Coulomb pass takes a tile per block)
+LARGE = {"slab 50400": (lambda: G.slab_4h(50, 42, 6, seed=41), (0, 21, 49, 53)),
+         "3C-SiC 74088": (lambda: G.zincblende(21, sigma=0.05, seed=42), (0, 21, 49, 53)),
+         "slab 271200": (lambda: G.slab_4h(113, 100, 6, seed=45), (49,))}
 
 
 @pytest.mark.parametrize("name", list(LARGE))
 def test_gradient_of_large_systems(ct, orc, theta, name):
     """Systems whose adjoint takes the multi-launch solve, in two and in four
-    launches per iteration, for one parameter of each class."""
-    s = LARGE[name]()
+    launches per iteration, and whose dual passes have a lane per atom, for one
+    parameter of each class."""
+    s, params = LARGE[name][0](), LARGE[name][1]
     s.pos = s.pos + np.random.Generator(np.random.PCG64(43)).normal(0, 0.05, s.pos.shape)
     w, v, u = _seeds(s.n, 44)
     print(f"[adjoint] {name} n={s.n}", flush=True)
-    ref = np.zeros(len(LARGE_PARAMS))
-    for i, k in enumerate(LARGE_PARAMS):
+    ref = np.zeros(len(params))
+    for i, k in enumerate(params):
         d = orc.param_derivative(s.pos, s.types, s.box, s.pbc, theta, k, tol=1e-13)
         ref[i] = w * d["dE"] + np.sum(v * d["dF"]) + np.sum(u * d["dq"])
-    sel = np.array(LARGE_PARAMS)
+    sel = np.array(params)
     for fp64, rtol, atol in ((True, 1e-6, 1e-8), (False, 1e-4, 2e-6)):
         pot = ct.Potential(theta, fp64=fp64, cg_tol=1e-12 if fp64 else 1e-9)
         g, it, _ = _gpu_grad(ct, pot, s, w, v, u)
