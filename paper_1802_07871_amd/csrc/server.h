@@ -538,7 +538,9 @@ int server_tick(ctbop_server *S, const Params<R> &prm, int cg_iters, bool poll)
                 launch_solve<R>(CLS[c], ctx->ncu, T + t0, cls_tiles[c], S->dsegs, solve_ctl(ctx, 0), st);
             }
         if (nto) {
-            const int lrc = pass.launched(S->ev_fork);   // (its own wait is on the side stream already)
+            // (where multi-launch iterations follow, others wait for the solves
+            // alone; the event's own wait is on the side stream by now)
+            const int lrc = pass.launched(nia_many ? S->ev_fork : nullptr);
             if (lrc) return lrc;
         }
         if (nis_many) {
