@@ -369,10 +369,11 @@ int ctbop_status(ctbop_ctx *ctx, void *sys_dev, size_t sys_bytes, void *stream, 
  * finished timings in, copies accumulated milliseconds and launch counts of
  * the first nk kernel classes to ms_out / count_out (host, may be NULL),
  * clears them if reset != 0, then turns timing on (enable != 0) or off.
- * Classes: 0 charge-solve matrix-vector product, 1 Coulomb force/energy
- * gather, 2 Coulomb matrix assembly, 3 covalent bond pass, 4 covalent force
- * gather, 5 charge-solve update, 6 charge-solve direction, 7 list build,
- * 8 sliced copy of the Coulomb rows, 9 carbon adjacency, 10 ring search,
+ * Classes: 0 charge-solve matrix-vector product (the whole solve where it runs
+ * in one launch), 1 Coulomb force/energy gather, 2 Coulomb matrix assembly,
+ * 3 covalent bond pass, 4 covalent force gather, 5 charge-solve update,
+ * 6 charge-solve direction, 7 list build, 8 sliced copy of the Coulomb rows (or
+ * the one-launch solve's preparation), 9 carbon adjacency, 10 ring search,
  * 11 chain bonds. */
 int ctbop_profile(ctbop_ctx *ctx, int enable, int reset, void *stream, double *ms_out, long *count_out, int nk);
 

@@ -532,8 +532,8 @@ __device__ __forceinline__ void write_halo(const Seg &S, const Tile &T, const un
 // their coordinates); group ballots place the accepted ones in list order.
 // Per-row statistics are reduced over the block before one atomic each.
 // ROWS = TILE: also the tile's halo, for the multi-launch solve.  ROWS = FINE
-// (systems of the one-launch solve, which finds its blocks' neighbours
-// itself): a block per 16 rows with 16 lanes each, the rows' statistics left
+// (systems up to the largest one-launch solve, which finds its blocks'
+// neighbours itself): a block per 16 rows with 16 lanes each, the rows' statistics left
 // in S.Fcov for k_mark_built; 20,000 atoms 535 -> 78 us.
 template <typename R, int L, int ROWS>
 __global__ void __launch_bounds__(TILE) k_build(const Tile *tiles, Seg *segs, Params<R> P)
